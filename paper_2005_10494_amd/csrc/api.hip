@@ -1325,7 +1325,7 @@ bmd_status tune_phase(bmd_problem* const* ps, std::vector<BatchPlan> pl, int pre
     auto consider = [&](BatchSettings c) -> bmd_status {
         // candidates whose LDS does not fit are skipped
         for (int i = 0; i < n; ++i)
-            if (batch_phase_lds(ps[i], prec, c.chunk) > 64 * 1024) return BMD_OK;
+            if (batch_phase_lds(ps[i], prec, c.chunk) + batch_static_lds(prec) > 64 * 1024) return BMD_OK;
         double t = 0.0;
         const bmd_status s2 = time_of(c, &t);
         if (s2 != BMD_OK) return s2;

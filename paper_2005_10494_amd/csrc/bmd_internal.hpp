@@ -269,6 +269,7 @@ size_t batch_record_bytes(int prec);
 void batch_fill_record(int prec, void* dst, const bmd_problem* p, void* draws_ws, int64_t M, int64_t slice_len,
                        double* partials, int scenario, int chunk);
 size_t batch_phase_lds(const bmd_problem* p, int prec, int chunk);
+size_t batch_static_lds(int prec);   // the kernel's own LDS beside it (the FP64 table of Phi)
 int batch_variants(const bmd_problem* p, int prec);
 int batch_variant_waves(const bmd_problem* p, int prec, int variant);
 int batch_phase_blocks_per_cu(const bmd_problem* p, int prec, size_t lds, int variant);

@@ -1,8 +1,9 @@
 // Device-side numerics for the design-objective kernels (gfx950).
 //
-// The FP64 normal CDF and quantile come from the device math library (ocml:
-// erfc, normcdfinv); the FP32 normal CDF is a fitted tail form (see
-// norm_cdf(float)); the bivariate normal CDF is evaluated from Plackett's identity
+// The FP64 normal CDF and quantile of the setup kernels come from the device
+// math library (ocml: erfc, normcdfinv); the FP64 integrands take the CDF from
+// a table in LDS (CdfTable) and 2^x from a polynomial (exp2_fast); the FP32
+// normal CDF is a fitted tail form (see norm_cdf(float)); the bivariate normal CDF is evaluated from Plackett's identity
 // d Phi_2 / d rho = phi_2 integrated over the angle theta = asin(rho)
 // (Drezner & Wesolowsky 1990, as organised by Genz 2004, Stat. Comput. 14:251),
 // with a Gauss-Legendre rule whose node count grows with the correlation.
@@ -10,6 +11,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "exp2_fit.hpp"
 #include "normal_cdf_fit.hpp"
 
 namespace bmd {
@@ -94,8 +96,8 @@ __device__ __forceinline__ double norm_cdf(double x) { return 0.5 * erfc(-x * 0.
 // full-rate operations.  Callers that can fold the factor into constants they
 // already hold pass xs directly.  xs must be finite: beyond |x| = 14.8 the
 // exponent underflows and Phi saturates to 0 or 1.
-__device__ __forceinline__ float norm_cdf_scaled(float xs) {
-    const float r = __builtin_amdgcn_rcpf(fabsf(xs) + kPhiShift);
+__device__ __forceinline__ float norm_cdf_scaled(float xs, float shift = kPhiShift) {
+    const float r = __builtin_amdgcn_rcpf(fabsf(xs) + shift);
     float p = kPhiFit[kPhiFitDeg];
 #pragma unroll
     for (int i = kPhiFitDeg - 1; i >= 0; --i) p = fmaf(p, r, kPhiFit[i]);
@@ -107,6 +109,97 @@ __device__ __forceinline__ double norm_pdf(double x) { return 0.3989422804014326
 __device__ __forceinline__ float norm_pdf(float x) {
     return 0.39894228040143267794f * __builtin_amdgcn_exp2f(-0.72134752044448170368f * x * x);
 }
+
+// 2^t in double precision for finite t (NaN stays NaN): t = n + f with n the
+// nearest integer, the polynomial of exp2_fit.hpp in f (1.1e-16 relative), the
+// power of two by the exponent (0 or infinity outside the range).  15
+// operations at four to five SIMD cycles each, against 92 cycles of the
+// library's exp, which also handles the special cases with selects.
+__device__ __forceinline__ double exp2_fast(double t) {
+    const double n = __builtin_rint(t);
+    const double f = t - n;
+    double p = kExp2Fit[kExp2Deg];
+#pragma unroll
+    for (int i = kExp2Deg - 1; i >= 0; --i) p = fma(p, f, kExp2Fit[i]);
+    return __builtin_amdgcn_ldexp(p, static_cast<int>(n));
+}
+
+// The FP64 integrands' Phi from a table in LDS: cell j holds
+// (Phi(x_j) - 1/2, phi(x_j)) at x_j = j / 64, and with d = |x| - x_j, u = x_j d,
+// v = d^2 (|d| <= 1/128) the Taylor series of the integral of phi from x_j,
+//   Phi(|x|) - 1/2 = F_j + phi_j d sum_n (-1)^n He_n(x_j) d^n / (n + 1)!,
+// is summed through n = 5 as a polynomial in u whose coefficients are
+// polynomials in v; the first term left out is below 6e-18.  Beyond the last
+// cell (x = 8.5, Phi = 1 to rounding) its density is taken as 0.  Absolute
+// error 1.2e-16 (the integrands subtract Phi from 1, so the tail's relative
+// error does not matter).  Why a table: the library's erfc costs 346 SIMD
+// cycles a wavefront, this 22 operations of four to five and one 16-byte LDS
+// read; without a division or an exponential there is nothing left to branch
+// on.  A cell of 1/64 needs two polynomial terms fewer than 1/32 and keeps the
+// table at 8.7 KB.  Infinite x gives 0 or 1; a NaN is clamped like a large
+// value, so callers whose designs may have no critical value mask their sums.
+struct alignas(16) CdfCell {
+    double F, p;
+};
+constexpr int kCdfPerUnit = 64;
+constexpr int kCdfCells = 8 * kCdfPerUnit + kCdfPerUnit / 2 + 1;   // x_j = 0 .. 8.5
+
+// Fill a workgroup's table (every thread of the block calls it; the caller
+// synchronises before the first use).
+__device__ __forceinline__ void cdf_table_fill(CdfCell* t) {
+    for (int j = threadIdx.x; j < kCdfCells; j += blockDim.x) {
+        const double x = static_cast<double>(j) / kCdfPerUnit;
+        t[j].F = 0.5 * erf(x * 0.70710678118654752440);
+        t[j].p = j < kCdfCells - 1 ? 0.39894228040143267794 * exp(-0.5 * x * x) : 0.0;
+    }
+}
+
+__device__ __forceinline__ double norm_cdf_table(double x, const CdfCell* t) {
+    // adding 1.5 * 2^52 / 64 rounds to a multiple of 1/64 and leaves its index in the low word
+    constexpr double kRound = 6755399441055744.0 / kCdfPerUnit;
+    const double y = fmin(fabs(x), static_cast<double>(kCdfCells - 1) / kCdfPerUnit);
+    const double s = y + kRound;
+    const CdfCell c = t[static_cast<uint32_t>(__double2loint(s))];
+    const double xj = s - kRound;
+    const double d = y - xj;
+    const double u = xj * d, v = d * d;
+    const double c0 = fma(v, fma(v, 1.0 / 40.0, -1.0 / 6.0), 1.0);
+    const double c1 = fma(v, fma(v, -1.0 / 48.0, 1.0 / 8.0), -0.5);
+    const double c2 = fma(v, -1.0 / 20.0, 1.0 / 6.0);
+    const double c3 = fma(v, 1.0 / 72.0, -1.0 / 24.0);
+    double q = fma(u, -1.0 / 720.0, 1.0 / 120.0);
+    q = fma(u, q, c3);
+    q = fma(u, q, c2);
+    q = fma(u, q, c1);
+    q = fma(u, q, c0);
+    return 0.5 + copysign(fma(c.p * d, q, c.F), x);
+}
+
+// Where an integrand's Phi comes from: the FP32 fit, the FP64 table in LDS, or
+// (setup kernels) the library.
+template <typename T>
+struct NormCdf;
+template <>
+struct NormCdf<float> {
+    float shift = kPhiShift;   // in a vector register: |x| + shift cannot take a literal, and a scalar costs twice
+    __device__ explicit NormCdf(const CdfCell*) { asm volatile("" : "+v"(shift)); }
+    __device__ __forceinline__ float operator()(float x) const { return norm_cdf(x); }
+    __device__ __forceinline__ float scaled(float xs) const { return norm_cdf_scaled(xs, shift); }   // xs = x sqrt(log2(e)/2)
+};
+template <>
+struct NormCdf<double> {
+    const CdfCell* t;
+    __device__ explicit NormCdf(const CdfCell* table) : t(table) {}
+    __device__ __forceinline__ double operator()(double x) const { return norm_cdf_table(x, t); }
+    __device__ __forceinline__ double scaled(double x) const { return norm_cdf_table(x, t); }   // FP64 is not prescaled
+};
+struct LibraryCdf {
+    __device__ __forceinline__ double operator()(double x) const { return norm_cdf(x); }
+    __device__ __forceinline__ double scaled(double x) const { return norm_cdf(x); }
+};
+// Cells of the table a kernel in T keeps in static LDS (one unused cell in FP32).
+template <typename T>
+constexpr int kCdfTableSize = sizeof(T) == 8 ? kCdfCells : 1;
 
 // Phi^-1(p): the library quantile, then one Newton step on a residual that
 // keeps relative accuracy (erf form near 1/2, where p - 1/2 is exact; erfc
@@ -127,7 +220,8 @@ __device__ __forceinline__ double norm_quantile(double p) {
 // Phi_2(h,k;rho) = Phi(h) Phi(k) + (1/2pi) int_0^{asin rho}
 //                      exp(-(h^2 + k^2 - 2 h k sin t) / (2 cos^2 t)) dt.
 // With Gauss-Legendre nodes x_i on [-1,1], s_i = sin(asin(rho)(1 + x_i)/2):
-//   integrand_i = exp(b_i h k - a_i (h^2 + k^2)),  a_i = 1/(2 (1 - s_i^2)), b_i = 2 s_i a_i,
+//   integrand_i = exp(b_i h k - a_i (h^2 + k^2)),  a_i = 1/(2 (1 - s_i^2)), b_i = 2 s_i a_i
+// (evaluated as a power of two, log2(e) folded into a_i and b_i),
 // and the integral is asin(rho)/(4 pi) sum_i w_i integrand_i.
 // The per-design constants (a_i, b_i, scale) live in registers; the weights w_i
 // belong to the n-point rule shared by the wavefront.
@@ -151,14 +245,18 @@ __device__ __forceinline__ int gl_offset(int n) {
          : n == 16 ? 80 : n == 20 ? 112 : 152;
 }
 
+// A Gauss-Legendre rule is symmetric: nodes p and n - 1 - p share a weight, so
+// the constants are held pair by pair (entries 2 p and 2 p + 1) and a pair
+// needs one weight.
 template <typename T, int NMAX>
 struct BvnConst {
     T a[NMAX], b[NMAX];
     T scale;  // asin(rho) / (4 pi)
 
-    // gl: packed table; n: wave-uniform rule size (<= NMAX).  FP32 evaluates
-    // exp2 on arguments prescaled by sqrt(log2(e)/2) (norm_cdf_scaled's), so
-    // its exponent coefficients become 1/(1 - s^2) and 2 s/(1 - s^2).
+    // gl: packed table; n: wave-uniform rule size (<= NMAX).  Both precisions
+    // evaluate powers of two.  FP32 arguments come prescaled by sqrt(log2(e)/2)
+    // (norm_cdf_scaled's), so its exponent coefficients become 1/(1 - s^2) and
+    // 2 s/(1 - s^2); FP64 arguments are plain, so it folds log2(e) in.
     __device__ __forceinline__ void init(double rho, int n, const double* __restrict__ gl) {
         const double th = asin(rho);
         scale = static_cast<T>(th * 0.079577471545947667884);  // 1/(4 pi)
@@ -166,10 +264,12 @@ struct BvnConst {
 #pragma unroll
         for (int i = 0; i < NMAX; ++i) {
             if (i < n) {
-                const double s = sin(0.5 * th * (1.0 + x[i]));
+                const int node = i % 2 == 0 ? i / 2 : n - 1 - i / 2;
+                const double s = sin(0.5 * th * (1.0 + x[node]));
                 const double ai = 1.0 / ((1.0 - s) * (1.0 + s));
-                a[i] = static_cast<T>(sizeof(T) == 4 ? ai : 0.5 * ai);
-                b[i] = static_cast<T>(sizeof(T) == 4 ? 2.0 * s * ai : s * ai);
+                constexpr double l2e = 1.4426950408889634074;
+                a[i] = static_cast<T>(sizeof(T) == 4 ? ai : 0.5 * l2e * ai);
+                b[i] = static_cast<T>(sizeof(T) == 4 ? 2.0 * s * ai : l2e * s * ai);
             } else {
                 a[i] = T(0);
                 b[i] = T(0);
@@ -178,84 +278,95 @@ struct BvnConst {
     }
 };
 
-// Node sum  sum_{i<n} w_i exp(b_i hk - a_i hs)  (FP32: exp2 of prescaled
-// arguments, log2(e) folded into a_i, b_i).  Every rule size is even and n is
-// wave-uniform, so the nodes go in pairs behind a scalar exit test, unrolled by template
-// recursion: only n nodes are evaluated and every coefficient index is a
-// compile-time constant (registers, no indexed scratch).  (A guard per node in
-// a loop is if-converted into evaluating all NMAX exponentials; a loop with an
-// early exit is kept rolled for FP64, its coefficients then indexed in scratch.)
-__device__ __forceinline__ double node_exp(double x) { return exp(x); }
+// The pair weights of a wavefront's rule, read once per design: FP64 in scalar
+// registers (an FP64 operation costs the same with a scalar operand), FP32 in
+// vector registers (an FP32 multiply-add takes 2.5 SIMD cycles a wavefront
+// from vector registers or a literal, 4.4 with a scalar register operand).
+// VEC = false keeps FP32 weights scalar too, for a kernel without vector
+// registers to spare.
+template <typename T, int NMAX, bool VEC = sizeof(T) == 4>
+struct BvnWeights {
+    T w[NMAX / 2];
+    __device__ __forceinline__ void load(const T* __restrict__ src, int n) {
+#pragma unroll
+        for (int i = 0; i < NMAX / 2; ++i) {
+            T v = 2 * i < n ? src[i] : T(0);
+            if constexpr (sizeof(T) == 8) {
+                v = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                                     __builtin_amdgcn_readfirstlane(__double2loint(v)));
+            } else if constexpr (VEC) {
+                asm volatile("" : "+v"(v));   // a vector register
+            } else {
+                v = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+            }
+            w[i] = v;
+        }
+    }
+    __device__ __forceinline__ T operator[](int i) const { return w[i]; }
+};
+
+// Node sums  sum_{i<n} w_i 2^(b_i hk - a_i hs)  of R argument pairs at once.
+// Every rule size is even and n is wave-uniform, so the nodes go in pairs
+// behind a scalar exit test, unrolled by template recursion: only n nodes are
+// evaluated and every coefficient index is a compile-time constant (registers,
+// no indexed scratch).  (A guard per node in a loop is if-converted into
+// evaluating all NMAX exponentials; a loop with an early exit is kept rolled
+// for FP64, its coefficients then indexed in scratch.)  The R sums share the
+// tests and give the scheduler independent chains.
+__device__ __forceinline__ double node_exp(double x) { return exp2_fast(x); }
 __device__ __forceinline__ float node_exp(float x) { return __builtin_amdgcn_exp2f(x); }
 
-template <int I, typename T, int NMAX, typename W>
-__device__ __forceinline__ void bvn_node_pairs(int n, T hk, T hs, const BvnConst<T, NMAX>& c, const W& w, T& acc0,
-                                               T& acc1) {
+template <int I, int R, typename T, int NMAX, typename W>
+__device__ __forceinline__ void bvn_node_pairs(int n, const T (&hk)[R], const T (&hs)[R], const BvnConst<T, NMAX>& c,
+                                               const W& w, T (&acc)[R]) {
     // smallest rule: 4 nodes (FP32 table) or 6 (FP64 table); those need no test
     constexpr int kMinRule = sizeof(T) == 4 ? 4 : 6;
     if constexpr (I < NMAX) {
         if (I >= kMinRule && I >= n) return;
-        acc0 = fma(w[I], node_exp(c.b[I] * hk - c.a[I] * hs), acc0);
-        acc1 = fma(w[I + 1], node_exp(c.b[I + 1] * hk - c.a[I + 1] * hs), acc1);
-        bvn_node_pairs<I + 2>(n, hk, hs, c, w, acc0, acc1);
-    }
-}
-
-template <typename T, int NMAX, typename W>
-__device__ __forceinline__ T bvn_node_sum(int n, T hk, T hs, const BvnConst<T, NMAX>& c, const W& w) {
-    T acc0 = T(0), acc1 = T(0);
-    bvn_node_pairs<0>(n, hk, hs, c, w, acc0, acc1);
-    return acc0 + acc1;
-}
-
-// FP64: Phi(h) Phi(k) + asin(rho)/(4 pi) sum_i w_i exp(b_i hk - a_i hs), hs = h^2 + k^2
-template <int NMAX>
-__device__ __forceinline__ double bvn_cdf(double h, double k, const BvnConst<double, NMAX>& c,
-                                          const double* __restrict__ w, int n) {
-    const double hk = h * k, hs = fma(h, h, k * k);
-    return norm_cdf(h) * norm_cdf(k) + c.scale * bvn_node_sum(n, hk, hs, c, w);
-}
-
-// FP32: the same with exp2.  The weights are wave-uniform (one rule per
-// wavefront); BvnWeights holds them in scalar registers, read once per design.
-template <int NMAX>
-struct BvnWeights {
-    float w[NMAX];
-    __device__ __forceinline__ void load(const float* __restrict__ src, int n) {
 #pragma unroll
-        for (int i = 0; i < NMAX; ++i)
-            w[i] = i < n ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(src[i]))) : 0.0f;
+        for (int r = 0; r < R; ++r) {
+            const T e0 = node_exp(fma(c.b[I], hk[r], -(c.a[I] * hs[r])));
+            const T e1 = node_exp(fma(c.b[I + 1], hk[r], -(c.a[I + 1] * hs[r])));
+            acc[r] = I == 0 ? w[0] * (e0 + e1) : fma(w[I / 2], e0 + e1, acc[r]);
+        }
+        bvn_node_pairs<I + 2, R>(n, hk, hs, c, w, acc);
     }
-    __device__ __forceinline__ float operator[](int i) const { return w[i]; }
-};
-
-// Arguments prescaled by sqrt(log2(e)/2) (kPhiScale), as norm_cdf_scaled.
-template <int NMAX, typename W>
-__device__ __forceinline__ float bvn_cdf_scaled(float h, float k, const BvnConst<float, NMAX>& c, const W& w, int n) {
-    const float hk = h * k, hs = fmaf(h, h, k * k);
-    return fmaf(norm_cdf_scaled(h), norm_cdf_scaled(k), c.scale * bvn_node_sum(n, hk, hs, c, w));
-}
-template <int NMAX, typename W>
-__device__ __forceinline__ float bvn_cdf(float h, float k, const BvnConst<float, NMAX>& c, const W& w, int n) {
-    return bvn_cdf_scaled(h * kPhiScale, k * kPhiScale, c, w, n);
 }
 
-// Upper complement 1 - Phi_2(h, k; rho) = (1 - scale S) - Phi(h) Phi(k), S the
-// node sum: two fused multiply-adds.
-template <int NMAX>
-__device__ __forceinline__ double bvn_sf(double h, double k, const BvnConst<double, NMAX>& c,
-                                         const double* __restrict__ w, int n) {
-    const double hk = h * k, hs = fma(h, h, k * k);
-    return fma(-norm_cdf(h), norm_cdf(k), fma(-c.scale, bvn_node_sum(n, hk, hs, c, w), 1.0));
+// 1 - Phi_2(h_r, k_r; rho) = (1 - scale S_r) - Phi(h_r) Phi(k_r), r < R, S_r the
+// node sums: two fused multiply-adds.  FP32 arguments are prescaled
+// (norm_cdf_scaled's); cdf: NormCdf<T>, or LibraryCdf in the setup kernels.
+template <int NMAX, int R, typename T, typename W, typename Cdf>
+__device__ __forceinline__ void bvn_sf_many(const T (&h)[R], const T (&k)[R], const BvnConst<T, NMAX>& c, const W& w,
+                                            int n, const Cdf& cdf, T (&sf)[R]) {
+    T hk[R], hs[R], acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        hk[r] = h[r] * k[r];
+        hs[r] = fma(h[r], h[r], k[r] * k[r]);
+        acc[r] = T(0);
+    }
+    bvn_node_pairs<0, R>(n, hk, hs, c, w, acc);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        sf[r] = fma(-cdf.scaled(h[r]), cdf.scaled(k[r]), fma(-c.scale, acc[r], T(1)));
 }
-template <int NMAX, typename W>
-__device__ __forceinline__ float bvn_sf_scaled(float h, float k, const BvnConst<float, NMAX>& c, const W& w, int n) {
-    const float hk = h * k, hs = fmaf(h, h, k * k);
-    return fmaf(-norm_cdf_scaled(h), norm_cdf_scaled(k), fmaf(-c.scale, bvn_node_sum(n, hk, hs, c, w), 1.0f));
+
+// Phi_2(h, k; rho), arguments as above.
+template <int NMAX, typename T, typename W, typename Cdf>
+__device__ __forceinline__ T bvn_cdf_scaled(T h, T k, const BvnConst<T, NMAX>& c, const W& w, int n, const Cdf& cdf) {
+    const T hk[1] = {h * k}, hs[1] = {fma(h, h, k * k)};
+    T acc[1] = {T(0)};
+    bvn_node_pairs<0, 1>(n, hk, hs, c, w, acc);
+    return fma(cdf.scaled(h), cdf.scaled(k), c.scale * acc[0]);
 }
-template <int NMAX, typename W>
-__device__ __forceinline__ float bvn_sf(float h, float k, const BvnConst<float, NMAX>& c, const W& w, int n) {
-    return bvn_sf_scaled(h * kPhiScale, k * kPhiScale, c, w, n);
+// Plain arguments in both precisions.
+template <int NMAX, typename T, typename W, typename Cdf>
+__device__ __forceinline__ T bvn_cdf(T h, T k, const BvnConst<T, NMAX>& c, const W& w, int n, const Cdf& cdf) {
+    if constexpr (sizeof(T) == 4)
+        return bvn_cdf_scaled<NMAX>(h * kPhiScale, k * kPhiScale, c, w, n, cdf);
+    else
+        return bvn_cdf_scaled<NMAX>(h, k, c, w, n, cdf);
 }
 
 // Row of the 16x16 result held in accumulator element v of a lane in quarter

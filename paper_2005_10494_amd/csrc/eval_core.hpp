@@ -46,7 +46,7 @@ struct DesignState {
     double q[D];
     BvnConst<T, NMAX> bc;
     int n;                 // Gauss-Legendre nodes (wave-uniform)
-    const T* w;            // their weights
+    BvnWeights<T, NMAX> w; // their weights
     T z1, z2, srI, invr, rT, omq, c0, c1, c2;
     // FP32 matrix-core sweep: the critical values and drift factors times
     // sqrt(log2(e)/2), so the bivariate normal's arguments arrive prescaled
@@ -74,7 +74,7 @@ struct DesignState {
         const double rho = sqrt(r);
         n = wave_max_int(sizeof(T) == 8 ? bvn_nodes_fp64(rho) : bvn_nodes_fp32(rho));
         bc.init(rho, n, gl);
-        w = glw + gl_offset(n) + n;
+        w.load(glw + gl_offset(n) + n, n);
         const double srI_d = sqrt(r * P.info);
         z1 = static_cast<T>(z1_arr[g]);
         z2 = static_cast<T>(z2_arr[g]);
@@ -123,12 +123,15 @@ struct DesignState {
 // without its 1/sqrt(2 pi) (carried by da1, da2); a second critical value at
 // +infinity (zinf bit 1) leaves phi(h) alone, as the one-test derivative of
 // Appendix A.3.
+__device__ __forceinline__ float gauss_factor(float x) { return exp(-0.5f * x * x); }
+__device__ __forceinline__ double gauss_factor(double x) { return exp2_fast(x * x * -0.72134752044448170368); }
+
 template <typename T, int D, int NMAX>
-__device__ __forceinline__ T dalpha_term(const DevProblem& P, const DesignState<T, D, NMAX>& s, T h, T kq) {
-    const T g = T(-0.5);
-    if (P.zinf & 2) return s.da1 * exp(g * h * h);
-    const T ph = exp(g * h * h) * norm_cdf(fma(kq, s.is, -s.rs * h));
-    const T pk = exp(g * kq * kq) * norm_cdf(fma(h, s.is, -s.rs * kq));
+__device__ __forceinline__ T dalpha_term(const DevProblem& P, const DesignState<T, D, NMAX>& s, T h, T kq,
+                                         const NormCdf<T>& cdf) {
+    if (P.zinf & 2) return s.da1 * gauss_factor(h);
+    const T ph = gauss_factor(h) * cdf(fma(kq, s.is, -s.rs * h));
+    const T pk = gauss_factor(kq) * cdf(fma(h, s.is, -s.rs * kq));
     return fma(s.da1, ph, s.da2 * pk);
 }
 
@@ -182,11 +185,11 @@ __device__ __forceinline__ T overlap(const DevProblem& P, const DesignState<T, D
     return acc;
 }
 
-// 1 - Phi_2(...) for design s and draw k; with dv, also its derivative in
-// alpha_1 (dalpha_term; the design's init_dalpha constants).
+// The bivariate normal's arguments h = z1 - mu1, k = z2 - mu2 of design s and
+// draw k.
 template <typename T, int D, int NMAX, typename Src>
-__device__ __forceinline__ T summand(const DevProblem& P, const DesignState<T, D, NMAX>& s, const Src& src,
-                                     int64_t k, const T* __restrict__ A, int K, T* dv = nullptr) {
+__device__ __forceinline__ void arguments(const DevProblem& P, const DesignState<T, D, NMAX>& s, const Src& src,
+                                          int64_t k, const T* __restrict__ A, int K, T* h, T* kq) {
     const T mu1 = src.mu1(k);
     T mu2;
     if (P.effect == BMD_EFFECT_STEP) {
@@ -205,12 +208,31 @@ __device__ __forceinline__ T summand(const DevProblem& P, const DesignState<T, D
     } else {
         mu2 = s.c0 + s.c1 * src.e1(k) + s.c2 * src.e2(k);
     }
-    const T h = s.z1 - mu1, kq = s.z2 - mu2;
-    if (dv) *dv = dalpha_term<T, D, NMAX>(P, s, h, kq);
-    if (P.zinf == 0) return bvn_sf<NMAX>(h, kq, s.bc, s.w, s.n);
-    if (P.zinf == 1) return T(1) - norm_cdf(kq);
-    if (P.zinf == 2) return T(1) - norm_cdf(h);
-    return T(0);
+    *h = s.z1 - mu1;
+    *kq = s.z2 - mu2;
+}
+
+// 1 - Phi_2(h_r, k_r) for R draws of design s (plain arguments); a critical
+// value at +infinity (zinf) leaves the other test's 1 - Phi.
+template <int R, typename T, int D, int NMAX>
+__device__ __forceinline__ void summands(const DevProblem& P, const DesignState<T, D, NMAX>& s, const T (&h)[R],
+                                         const T (&k)[R], const NormCdf<T>& cdf, T (&v)[R]) {
+    if (P.zinf == 0) {
+        if constexpr (sizeof(T) == 4) {
+            T hp[R], kp[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                hp[r] = h[r] * kPhiScale;
+                kp[r] = k[r] * kPhiScale;
+            }
+            bvn_sf_many<NMAX, R>(hp, kp, s.bc, s.w, s.n, cdf, v);
+        } else {
+            bvn_sf_many<NMAX, R>(h, k, s.bc, s.w, s.n, cdf, v);
+        }
+        return;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = P.zinf == 1 ? T(1) - cdf(k[r]) : P.zinf == 2 ? T(1) - cdf(h[r]) : T(0);
 }
 
 }  // namespace bmd

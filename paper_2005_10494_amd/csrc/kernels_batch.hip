@@ -50,6 +50,7 @@ constexpr int batch_waves() {
 template <typename T, int D, int NMAX, bool MF, int W>
 __global__ __launch_bounds__(kEvalBlock, (sizeof(T) == 4 ? batch_waves<D, MF, W>() : 1)) void k_batch(BatchPhase ph, const BatchRecord<T>* __restrict__ recs) {
     extern __shared__ __align__(16) char lds[];
+    __shared__ CdfCell cells[kCdfTableSize<T>];
     if (threadIdx.x == 0) atomicMin(ph.t_start, static_cast<unsigned long long>(wall_clock64()));
     const int4 it = ph.items[blockIdx.x];
     const int rec = __builtin_amdgcn_readfirstlane(it.x);
@@ -57,9 +58,9 @@ __global__ __launch_bounds__(kEvalBlock, (sizeof(T) == 4 ? batch_waves<D, MF, W>
     const int slice = __builtin_amdgcn_readfirstlane(it.z);
     const BatchRecord<T>& R = recs[rec];
     if constexpr (MF)
-        mfma_tile_body<T, D, NMAX, kSums>(R.a, R.geo, tile, slice, lds);
+        mfma_tile_body<T, D, NMAX, kSums>(R.a, R.geo, tile, slice, lds, cells);
     else
-        direct_body<T, D, NMAX, kSums>(R.a, tile, slice);
+        direct_body<T, D, NMAX, kSums>(R.a, tile, slice, cells);
     __syncthreads();   // every thread's partial sums are written
     if (threadIdx.x == 0) {
         __threadfence();
@@ -152,6 +153,8 @@ size_t batch_phase_lds(const bmd_problem* p, int prec, int chunk) {
     return prec == BMD_FP64 ? mfma_lds_bytes<double>(ch, p->P.d, p->tab[prec].K)
                             : mfma_lds_bytes<float>(ch, p->P.d, p->tab[prec].K);
 }
+
+size_t batch_static_lds(int prec) { return prec == BMD_FP64 ? sizeof(CdfCell) * kCdfCells : 0; }
 
 int batch_phase_blocks_per_cu(const bmd_problem* p, int prec, size_t lds, int variant) {
     int nb = 0;

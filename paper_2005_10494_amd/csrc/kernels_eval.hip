@@ -14,7 +14,8 @@ namespace {
 // VAR: also the per-design sums of squares (only when a variance is asked for).
 template <typename T, int D, int NMAX, bool VAR>
 __global__ __launch_bounds__(kEvalBlock) void k_eval_direct(EvalArgs<T> a) {
-    direct_body<T, D, NMAX, VAR ? kSquares : kSums>(a, blockIdx.x, blockIdx.y);
+    __shared__ CdfCell cells[kCdfTableSize<T>];
+    direct_body<T, D, NMAX, VAR ? kSquares : kSums>(a, blockIdx.x, blockIdx.y, cells);
 }
 
 // Tile of workgroup (x, y): the tiles of one draw slice lie along x, so every
@@ -30,18 +31,21 @@ __device__ __forceinline__ unsigned sweep_tile() { return (blockIdx.x + blockIdx
 template <typename T, int D, int NMAX, bool VAR>
 __global__ __launch_bounds__(kEvalBlock, sizeof(T) == 4 && D <= 3 ? 5 : 1) void k_eval_mfma(EvalArgs<T> a, MfmaGeom geo) {
     extern __shared__ __align__(16) char lds[];
-    mfma_tile_body<T, D, NMAX, VAR ? kSquares : kSums>(a, geo, sweep_tile(), blockIdx.y, lds);
+    __shared__ CdfCell cells[kCdfTableSize<T>];
+    mfma_tile_body<T, D, NMAX, VAR ? kSquares : kSums>(a, geo, sweep_tile(), blockIdx.y, lds, cells);
 }
 
 // The same sweeps with the summands' derivatives in alpha_1 as second sums.
 template <typename T, int D, int NMAX>
 __global__ __launch_bounds__(kEvalBlock) void k_eval_direct_da(EvalArgs<T> a) {
-    direct_body<T, D, NMAX, kDAlpha>(a, blockIdx.x, blockIdx.y);
+    __shared__ CdfCell cells[kCdfTableSize<T>];
+    direct_body<T, D, NMAX, kDAlpha>(a, blockIdx.x, blockIdx.y, cells);
 }
 template <typename T, int D, int NMAX>
 __global__ __launch_bounds__(kEvalBlock) void k_eval_mfma_da(EvalArgs<T> a, MfmaGeom geo) {
     extern __shared__ __align__(16) char lds[];
-    mfma_tile_body<T, D, NMAX, kDAlpha>(a, geo, sweep_tile(), blockIdx.y, lds);
+    __shared__ CdfCell cells[kCdfTableSize<T>];
+    mfma_tile_body<T, D, NMAX, kDAlpha>(a, geo, sweep_tile(), blockIdx.y, lds, cells);
 }
 
 // mean = sums / M in slice order; second: nothing (mode 0), the sample
@@ -84,9 +88,9 @@ MfmaGeom mfma_geometry(const bmd_problem* p, int prec) {
     // wavefronts; of 4 in FP64) within the LDS share of the resident
     // workgroups: five per compute unit for FP32 with up to three biomarkers
     // (32 KB each of 160 KB), else four (40 KB); FP64 holds two (its
-    // registers allow no more), 64 KB each.
+    // registers allow no more), 64 KB each with the table of Phi.
     const int step = prec == BMD_FP64 ? 4 : 8;
-    const size_t cap = prec == BMD_FP64 ? 64 * 1024 : d <= 3 ? 32 * 1024 : 40 * 1024;
+    const size_t cap = prec == BMD_FP64 ? 64 * 1024 - sizeof(CdfCell) * kCdfCells : d <= 3 ? 32 * 1024 : 40 * 1024;
     int ch = 32;
     while (ch > step && (prec == BMD_FP64 ? mfma_lds_bytes<double>(ch, d, K) : mfma_lds_bytes<float>(ch, d, K)) > cap)
         ch -= step;

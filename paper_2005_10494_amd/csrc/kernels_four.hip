@@ -86,6 +86,14 @@ struct FourArgs {
 template <typename T, bool VAR>
 __global__ __launch_bounds__(kEvalBlock) void k_eval_four(FourArgs<T> a) {
     constexpr int NB = sizeof(T) == 8 ? kBvnMax64 : kBvnMax32;
+    __shared__ CdfCell cells[kCdfTableSize<T>];
+    __shared__ PanelPoint pts[kNodes];
+    if constexpr (sizeof(T) == 8) {
+        cdf_table_fill(cells);
+        panel_points_fill(pts, a.gl);
+        __syncthreads();
+    }
+    const NormCdf<T> cdf(cells);
     const int64_t idx = static_cast<int64_t>(blockIdx.x) * kEvalBlock + threadIdx.x;
     const bool valid = idx < a.G;
     // idle lanes shadow the last design of the order
@@ -118,14 +126,14 @@ __global__ __launch_bounds__(kEvalBlock) void k_eval_four(FourArgs<T> a) {
         const T h2 = z2 - fma(m[4], e2, fma(m[3], e1, m[2]));
         const T h3 = z3 - fma(m[8], e3, fma(m[7], e2, fma(m[6], e1, m[5])));
         const T h4 = z4 - fma(m[13], e4, fma(m[12], e3, fma(m[11], e2, fma(m[10], e1, m[9]))));
-        const double v = static_cast<double>(T(1) - qvn(h1, h2, h3, h4, c));
+        const double v = static_cast<double>(T(1) - qvn(h1, h2, h3, h4, c, cdf, pts));
         s1 += v;
         if constexpr (VAR) s2 = fma(v, v, s2);
     }
     if (valid) {
         double* out = a.partials + static_cast<int64_t>(slice) * 2 * a.G;
-        out[g] = s1;
-        if constexpr (VAR) out[a.G + g] = s2;
+        out[g] = z4d == z4d ? s1 : z4d;   // a design without a last level among the wavefront's others
+        if constexpr (VAR) out[a.G + g] = z4d == z4d ? s2 : z4d;
     }
 }
 

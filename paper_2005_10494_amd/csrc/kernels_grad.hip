@@ -142,13 +142,18 @@ __global__ __launch_bounds__(128) void k_grad_points(DevProblem P, const double*
 }
 
 // Logistic 1/(1 + e^-x); FP32 with the hardware exp2 and reciprocal.
-__device__ __forceinline__ double lgst(double x) { return 1.0 / (1.0 + exp(-x)); }
+__device__ __forceinline__ double lgst(double x) { return 1.0 / (1.0 + exp2_fast(-1.4426950408889634074 * x)); }
 __device__ __forceinline__ float lgst(float x) {
     return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634074f * x));
 }
 // e^x; FP32 with the hardware exp2.
-__device__ __forceinline__ double expT(double x) { return exp(x); }
+__device__ __forceinline__ double expT(double x) { return exp2_fast(1.4426950408889634074 * x); }
 __device__ __forceinline__ float expT(float x) { return __builtin_amdgcn_exp2f(1.4426950408889634074f * x); }
+
+__device__ __forceinline__ double norm_pdf_fast(double x) {
+    return 0.39894228040143267794 * exp2_fast(x * x * -0.72134752044448170368);
+}
+__device__ __forceinline__ float norm_pdf_fast(float x) { return norm_pdf(x); }
 
 struct GradArgs {
     DevProblem P;
@@ -214,6 +219,9 @@ __device__ void stage_chunk(const DrawArrays<T>& G, int K, const ChunkView<T>& c
 template <typename T, int D, int NMAX, int R, bool SPLIT>
 __global__ __launch_bounds__(kGradBlock) void k_grad(GradArgs a, DrawArrays<T> Dr) {
     extern __shared__ __align__(16) char lds[];
+    __shared__ CdfCell cells[kCdfTableSize<T>];
+    if constexpr (sizeof(T) == 8) cdf_table_fill(cells);   // visible after the first chunk's barrier
+    const NormCdf<T> cdf(cells);
     const ChunkView<T> ch = carve_chunk<T>(lds, a.chunk, a.K);
     const DevProblem& P = a.P;
     const int K = a.K;
@@ -235,7 +243,8 @@ __global__ __launch_bounds__(kGradBlock) void k_grad(GradArgs a, DrawArrays<T> D
     n = __builtin_amdgcn_readfirstlane(n);
     BvnConst<T, NMAX> bc;
     bc.init(rho, n, a.gl);
-    const T* wgl = static_cast<const T*>(a.glw) + gl_offset(n) + n;
+    BvnWeights<T, NMAX, false> wgl;
+    wgl.load(static_cast<const T*>(a.glw) + gl_offset(n) + n, n);
 
     const T sI = static_cast<T>(P.sqrtI);
     const T srI = static_cast<T>(sqrt(r * P.info));
@@ -348,15 +357,15 @@ __global__ __launch_bounds__(kGradBlock) void k_grad(GradArgs a, DrawArrays<T> D
                 const T h = z1 - mu1, kq = z2 - mu2;
                 T p, ph, pk, pr;
                 if (P.zinf == 0) {
-                    p = bvn_cdf<NMAX>(h, kq, bc, wgl, n);
-                    ph = norm_pdf(h) * norm_cdf((kq - rhoT * h) * isig);
-                    pk = norm_pdf(kq) * norm_cdf((h - rhoT * kq) * isig);
+                    p = bvn_cdf<NMAX>(h, kq, bc, wgl, n, cdf);
+                    ph = norm_pdf_fast(h) * cdf((kq - rhoT * h) * isig);
+                    pk = norm_pdf_fast(kq) * cdf((h - rhoT * kq) * isig);
                     const T e = (h * h - T(2) * rhoT * h * kq + kq * kq) * isig * isig;
                     pr = expT(-T(0.5) * e) * isig * T(0.15915494309189533577);
                 } else if (P.zinf == 2) {
-                    p = norm_cdf(h); ph = norm_pdf(h); pk = T(0); pr = T(0);
+                    p = cdf(h); ph = norm_pdf_fast(h); pk = T(0); pr = T(0);
                 } else if (P.zinf == 1) {
-                    p = norm_cdf(kq); ph = T(0); pk = norm_pdf(kq); pr = T(0);
+                    p = cdf(kq); ph = T(0); pk = norm_pdf_fast(kq); pr = T(0);
                 } else {
                     p = T(1); ph = T(0); pk = T(0); pr = T(0);
                 }

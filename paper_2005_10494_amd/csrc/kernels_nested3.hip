@@ -110,6 +110,12 @@ struct Nested3Args {
 // start first, so the last workgroups to run are the cheapest.
 template <typename T, bool VAR>
 __global__ __launch_bounds__(kEvalBlock) void k_eval_nested3(Nested3Args<T> a) {
+    __shared__ CdfCell cells[kCdfTableSize<T>];
+    if constexpr (sizeof(T) == 8) {
+        cdf_table_fill(cells);
+        __syncthreads();
+    }
+    const NormCdf<T> cdf(cells);
     const int64_t G = a.P.G;
     const int64_t idx = static_cast<int64_t>(blockIdx.y) * kEvalBlock + threadIdx.x;
     const bool valid = idx < G;
@@ -148,7 +154,7 @@ __global__ __launch_bounds__(kEvalBlock) void k_eval_nested3(Nested3Args<T> a) {
         const T h1 = z - s1 * (b0 + b1 * (T(1) - tau));
         const T h2 = z - s2 * (b0 + b1 * (T(1) - fmax(tq1, tau)) * ir2);
         const T h3 = z - s3 * (b0 + b1 * (T(1) - fmax(tq2, tau)) * ir3);
-        const double v = static_cast<double>(T(1) - tvn(h1, h2, h3, c));
+        const double v = static_cast<double>(T(1) - tvn(h1, h2, h3, c, cdf));
         sum1 += v;
         if constexpr (VAR) sum2 = fma(v, v, sum2);
     }

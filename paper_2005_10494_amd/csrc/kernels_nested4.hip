@@ -119,6 +119,14 @@ struct Nested4Args {
 // whose designs all do not exist write NaN sums and leave.
 template <typename T, int NB, bool VAR>
 __global__ __launch_bounds__(kEvalBlock) void k_eval_nested4(Nested4Args<T> a) {
+    __shared__ CdfCell cells[kCdfTableSize<T>];
+    __shared__ PanelPoint pts[kNodes];
+    if constexpr (sizeof(T) == 8) {
+        cdf_table_fill(cells);
+        panel_points_fill(pts, a.gl);
+        __syncthreads();
+    }
+    const NormCdf<T> cdf(cells);
     const int64_t G = a.P.G;
     const int64_t idx = static_cast<int64_t>(blockIdx.y) * kEvalBlock + threadIdx.x;
     const bool valid = idx < G;
@@ -161,7 +169,7 @@ __global__ __launch_bounds__(kEvalBlock) void k_eval_nested4(Nested4Args<T> a) {
         const T h2 = z - s2 * (b0 + b1 * (T(1) - fmax(tq1, tau)) * ir2);
         const T h3 = z - s3 * (b0 + b1 * (T(1) - fmax(tq2, tau)) * ir3);
         const T h4 = z - s4 * (b0 + b1 * (T(1) - fmax(tq3, tau)) * ir4);
-        const double v = static_cast<double>(T(1) - qvn(h1, h2, h3, h4, c));
+        const double v = static_cast<double>(T(1) - qvn(h1, h2, h3, h4, c, cdf, pts));
         sum1 += v;
         if constexpr (VAR) sum2 = fma(v, v, sum2);
     }

@@ -28,10 +28,11 @@ __global__ __launch_bounds__(64) void k_three_precompute(DevProblem P, const dou
     const double z1 = -norm_quantile(grid_coord(P.q_lo, P.q_hi, i0, P.m[0]));
     const double z2 = -norm_quantile(grid_coord(P.q_lo, P.q_hi, i1, P.m[1]));
     constexpr int n = 24;
-    const double* w = gl + gl_offset(n) + n;
+    BvnWeights<double, n> w;
+    w.load(gl + gl_offset(n) + n, n);
     BvnConst<double, n> b12;
     b12.init(sqrt(P.r_lo), n, gl);
-    const double a12 = 1.0 - bvn_cdf<n>(z1, z2, b12, w, n);
+    const double a12 = 1.0 - bvn_cdf<n>(z1, z2, b12, w, n, LibraryCdf{});
     double z3 = NAN;
     if (a12 < P.alpha0) {
         TvnConst<double> c;
@@ -76,6 +77,12 @@ struct ThreeArgs {
 // wavefronts that write NaN sums and leave without touching the draws.
 template <typename T, bool VAR>
 __global__ __launch_bounds__(kEvalBlock) void k_eval_three(ThreeArgs<T> a) {
+    __shared__ CdfCell cells[kCdfTableSize<T>];
+    if constexpr (sizeof(T) == 8) {
+        cdf_table_fill(cells);
+        __syncthreads();
+    }
+    const NormCdf<T> cdf(cells);
     const int64_t idx = static_cast<int64_t>(blockIdx.x) * kEvalBlock + threadIdx.x;
     const bool valid = idx < a.G;
     // idle lanes shadow the last design of the order
@@ -104,14 +111,14 @@ __global__ __launch_bounds__(kEvalBlock) void k_eval_three(ThreeArgs<T> a) {
         const T h1 = z1 - fma(m[1], e1, m[0]);
         const T h2 = z2 - fma(m[4], e2, fma(m[3], e1, m[2]));
         const T h3 = z3 - fma(m[8], e3, fma(m[7], e2, fma(m[6], e1, m[5])));
-        const double v = static_cast<double>(T(1) - tvn(h1, h2, h3, c));
+        const double v = static_cast<double>(T(1) - tvn(h1, h2, h3, c, cdf));
         s1 += v;
         if constexpr (VAR) s2 = fma(v, v, s2);
     }
     if (valid) {
         double* out = a.partials + static_cast<int64_t>(slice) * 2 * a.G;
-        out[g] = s1;
-        if constexpr (VAR) out[a.G + g] = s2;
+        out[g] = z3d == z3d ? s1 : z3d;   // a design without a last level among the wavefront's others
+        if constexpr (VAR) out[a.G + g] = z3d == z3d ? s2 : z3d;
     }
 }
 

@@ -50,8 +50,10 @@ __device__ __forceinline__ int tvn_panels(double r2, double r3) {
     return max(lo, min(hi, static_cast<int>(ceil(c / l))));
 }
 
-// exp(-x^2 / 2); FP32 through exp2.
-__device__ __forceinline__ double half_gauss(double x) { return exp(-0.5 * x * x); }
+// exp(-x^2 / 2) as a power of two.
+__device__ __forceinline__ double half_gauss(double x) {
+    return exp2_fast(x * x * -0.72134752044448170368);   // log2(e) / 2
+}
 __device__ __forceinline__ float half_gauss(float x) {
     return __builtin_amdgcn_exp2f(x * x * -0.72134752044448170368f);   // log2(e) / 2
 }
@@ -121,7 +123,8 @@ struct TvnConst {
 // conditional argument, one for the Gaussian's exponent with the weight, an
 // exp2, the two CDFs and two to accumulate.
 template <bool UNI>
-__device__ __forceinline__ float tvn(float h1, float h2, float h3, const TvnConst<float, UNI>& c) {
+__device__ __forceinline__ float tvn(float h1, float h2, float h3, const TvnConst<float, UNI>& c,
+                                     const NormCdf<float>&) {
     const float k = kPhiScale;
     const float lo = -c.tail * k;
     const float hi = k * fminf(fminf(h2, c.tail), fminf((h1 + c.c1) * c.ir12, (h3 + c.c3) * c.ir23));
@@ -145,8 +148,10 @@ __device__ __forceinline__ float tvn(float h1, float h2, float h3, const TvnCons
 // Phi_3(h1, h2, h3) over c.np panels (wave-uniform).  Every lane runs the
 // same node count: an empty range (U <= -L) becomes a zero panel width, and
 // NaN inputs give NaN.
-template <typename T, bool UNI>
-__device__ __forceinline__ T tvn(T h1, T h2, T h3, const TvnConst<T, UNI>& c) {
+template <bool UNI>
+__device__ __forceinline__ double tvn(double h1, double h2, double h3, const TvnConst<double, UNI>& c,
+                                      const NormCdf<double>& cdf) {
+    using T = double;
     const T lo = -c.tail;
     const T hi = fmin(fmin(h2, c.tail), fmin((h1 + c.c1) * c.ir12, (h3 + c.c3) * c.ir23));
     const T width = fmax(hi - lo, T(0)) / static_cast<T>(c.np);
@@ -158,7 +163,7 @@ __device__ __forceinline__ T tvn(T h1, T h2, T h3, const TvnConst<T, UNI>& c) {
             const T y = fma(width, c.px[i], a);
             const T u = (h1 - c.r12 * y) * c.is12;
             const T v = (h3 - c.r23 * y) * c.is23;
-            acc = fma(c.pw[i] * half_gauss(y), norm_cdf(u) * norm_cdf(v), acc);
+            acc = fma(c.pw[i] * half_gauss(y), cdf(u) * cdf(v), acc);
         }
     }
     return acc * width;
@@ -268,7 +273,7 @@ struct QvnConst {
     T px[kNodes], pw[kNodes];
     int np;              // panels
     BvnConst<T, NMAX> bc;   // Phi_2 at the partial correlation of (Y3, Y4) given Y2
-    T bw[NMAX];          // its node weights
+    BvnWeights<T, NMAX> bw; // its node weights
     int nb;              // its node count (a rule of the packed table)
     // FP32 in y' as for Phi_3: slopes r1j / s1j, scales k / s1j, log2 weights
     T g1, g3, g4, k1, k3, k4;
@@ -326,8 +331,9 @@ struct QvnConst {
         bc.init(qvn_partial_rho(r2, r3, r4), bvn_n, gl);
         const double* bwx = gl + gl_offset(bvn_n) + bvn_n;
 #pragma unroll
+        for (int i = 0; i < NMAX / 2; ++i) bw.w[i] = uniform(static_cast<T>(2 * i < bvn_n ? bwx[i] : 0.0));
+#pragma unroll
         for (int i = 0; i < NMAX; ++i) {
-            bw[i] = uniform(static_cast<T>(i < bvn_n ? bwx[i] : 0.0));
             bc.a[i] = U(bc.a[i]);
             bc.b[i] = U(bc.b[i]);
         }
@@ -335,23 +341,24 @@ struct QvnConst {
     }
 };
 
-// Univariate and bivariate CDFs at the arguments QvnConst prepares: FP32
-// prescaled, FP64 as they are.
-__device__ __forceinline__ float qvn_cdf1(float x) { return norm_cdf_scaled(x); }
-__device__ __forceinline__ double qvn_cdf1(double x) { return norm_cdf(x); }
-template <int NMAX, bool UNI>
-__device__ __forceinline__ float qvn_cdf2(float a, float b, const QvnConst<float, NMAX, UNI>& c) {
-    return bvn_cdf_scaled<NMAX>(a, b, c.bc, c.bw, c.nb);
-}
-template <int NMAX, bool UNI>
-__device__ __forceinline__ double qvn_cdf2(double a, double b, const QvnConst<double, NMAX, UNI>& c) {
-    return bvn_cdf<NMAX>(a, b, c.bc, c.bw, c.nb);
+// The panel rule's points on [0, 1] and weights (phi's 1/sqrt(2 pi) folded in)
+// in LDS for the rolled FP64 loop below; the caller synchronises.
+struct alignas(16) PanelPoint {
+    double x, w;
+};
+__device__ __forceinline__ void panel_points_fill(PanelPoint* pts, const double* __restrict__ gl) {
+    const double* x = gl + gl_offset(kNodes);
+    if (threadIdx.x < kNodes) {
+        pts[threadIdx.x].x = 0.5 * (1.0 + x[threadIdx.x]);
+        pts[threadIdx.x].w = 0.5 * x[kNodes + threadIdx.x] * 0.39894228040143267794;
+    }
 }
 
 // FP32 Phi_4 in y' (see TvnConst): the three conditional arguments are one
 // FMA each and arrive prescaled at the univariate and bivariate CDFs.
 template <int NMAX, bool UNI>
-__device__ __forceinline__ float qvn(float h1, float h2, float h3, float h4, const QvnConst<float, NMAX, UNI>& c) {
+__device__ __forceinline__ float qvn(float h1, float h2, float h3, float h4, const QvnConst<float, NMAX, UNI>& c,
+                                     const NormCdf<float>& cdf, const PanelPoint*) {
     const float k = kPhiScale;
     const float lo = -c.tail * k;
     const float hi = k * fminf(fminf(fminf(h2, c.tail), (h1 + c.c1) * c.ir12),
@@ -368,31 +375,38 @@ __device__ __forceinline__ float qvn(float h1, float h2, float h3, float h4, con
             const float u3 = fmaf(-c.g3, y, H3);
             const float u4 = fmaf(-c.g4, y, H4);
             const float e = __builtin_amdgcn_exp2f(fmaf(-y, y, c.lw[i]));
-            acc = fmaf(e * norm_cdf_scaled(u1), bvn_cdf_scaled<NMAX>(u3, u4, c.bc, c.bw, c.nb), acc);
+            acc = fmaf(e * norm_cdf_scaled(u1), bvn_cdf_scaled<NMAX>(u3, u4, c.bc, c.bw, c.nb, cdf), acc);
         }
     }
     return acc * width;
 }
 
 // Phi_4(h1, h2, h3, h4) over c.np panels (wave-uniform); an empty range gives
-// zero, NaN inputs NaN.
-template <typename T, int NMAX, bool UNI>
-__device__ __forceinline__ T qvn(T h1, T h2, T h3, T h4, const QvnConst<T, NMAX, UNI>& c) {
-    const T lo = -c.tail;
-    const T hi = fmin(fmin(fmin(h2, c.tail), (h1 + c.c1) * c.ir12),
-                      fmin((h3 + c.c3) * c.ir23, (h4 + c.c4) * c.ir24));
-    const T width = fmax(hi - lo, T(0)) / static_cast<T>(c.np);
-    T acc = T(0);
+// zero.  The points go in a rolled loop (their constants read from LDS):
+// unrolled, eight copies of the bivariate node sum took the kernel to 474
+// registers, one wavefront per SIMD and coefficients moved in and out of the
+// accumulation registers.
+template <int NMAX, bool UNI>
+__device__ __forceinline__ double qvn(double h1, double h2, double h3, double h4,
+                                      const QvnConst<double, NMAX, UNI>& c, const NormCdf<double>& cdf,
+                                      const PanelPoint* pts) {
+    const double lo = -c.tail;
+    const double hi = fmin(fmin(fmin(h2, c.tail), (h1 + c.c1) * c.ir12),
+                           fmin((h3 + c.c3) * c.ir23, (h4 + c.c4) * c.ir24));
+    const double width = fmax(hi - lo, 0.0) / static_cast<double>(c.np);
+    const double H1 = h1 * c.is12, H3 = h3 * c.is23, H4 = h4 * c.is24;
+    double acc = 0.0, a = lo;
     for (int p = 0; p < c.np; ++p) {
-        const T a = fma(width, static_cast<T>(p), lo);
-#pragma unroll
+#pragma unroll 1
         for (int i = 0; i < kNodes; ++i) {
-            const T y = fma(width, c.px[i], a);
-            const T u1 = (h1 - c.r12 * y) * c.is12;
-            const T u3 = (h3 - c.r23 * y) * c.is23;
-            const T u4 = (h4 - c.r24 * y) * c.is24;
-            acc = fma(c.pw[i] * half_gauss(y) * qvn_cdf1(u1), qvn_cdf2(u3, u4, c), acc);
+            const PanelPoint pt = pts[i];
+            const double y = fma(width, pt.x, a);
+            const double u1 = fma(-c.g1, y, H1);
+            const double u3 = fma(-c.g3, y, H3);
+            const double u4 = fma(-c.g4, y, H4);
+            acc = fma(pt.w * half_gauss(y) * cdf(u1), bvn_cdf<NMAX>(u3, u4, c.bc, c.bw, c.nb, cdf), acc);
         }
+        a = fma(width, static_cast<double>(p + 1), lo);
     }
     return acc * width;
 }
@@ -411,7 +425,7 @@ __device__ __forceinline__ double qvn_wave(double h1, double h2, double h3, doub
         const double u1 = (h1 - c.r12 * y) * c.is12;
         const double u3 = (h3 - c.r23 * y) * c.is23;
         const double u4 = (h4 - c.r24 * y) * c.is24;
-        acc = fma(nd.pw * half_gauss(y) * qvn_cdf1(u1), qvn_cdf2(u3, u4, c), acc);
+        acc = fma(nd.pw * half_gauss(y) * norm_cdf(u1), bvn_cdf<NMAX>(u3, u4, c.bc, c.bw, c.nb, LibraryCdf{}), acc);
     }
     return wave_total(acc) * width;
 }

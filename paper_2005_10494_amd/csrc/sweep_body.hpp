@@ -31,9 +31,15 @@ struct EvalArgs {
 };
 
 // Direct sweep, one workgroup's work: designs bx * 256 + thread (one per
-// thread), draws of slice `slice`.  MODE: see kSums.
+// thread), draws of slice `slice`.  cells: the workgroup's LDS for the FP64
+// integrand's table of Phi (kCdfTableSize<T> cells), filled here.  MODE: see kSums.
 template <typename T, int D, int NMAX, int MODE>
-__device__ __forceinline__ void direct_body(const EvalArgs<T>& a, int64_t bx, int slice) {
+__device__ __forceinline__ void direct_body(const EvalArgs<T>& a, int64_t bx, int slice, CdfCell* cells) {
+    if constexpr (sizeof(T) == 8) {
+        cdf_table_fill(cells);
+        __syncthreads();
+    }
+    const NormCdf<T> cdf(cells);
     const int64_t G = a.P.G;
     const int64_t g = bx * kEvalBlock + threadIdx.x;
     const bool valid = g < G;
@@ -45,18 +51,27 @@ __device__ __forceinline__ void direct_body(const EvalArgs<T>& a, int64_t bx, in
     const int64_t M = a.D.M;
     const int64_t kb = static_cast<int64_t>(slice) * a.slice_len;
     const int64_t ke = min(M, kb + a.slice_len);
+    // R draws at a time: their scalar loads are in flight together and the
+    // node sums share the exit tests
+    constexpr int R = 2;
     double s1 = 0.0, s2 = 0.0;
-    for (int64_t k = kb; k < ke; ++k) {
-        if constexpr (MODE == kDAlpha) {
-            T dv;
-            s1 += static_cast<double>(summand<T, D, NMAX>(a.P, s, src, k, a.A, a.D.K, &dv));
-            s2 += static_cast<double>(dv);
-        } else {
-            const double v = static_cast<double>(summand<T, D, NMAX>(a.P, s, src, k, a.A, a.D.K));
-            s1 += v;
-            if constexpr (MODE == kSquares) s2 = fma(v, v, s2);
+    auto add = [&](auto count, int64_t k0) {
+        constexpr int N = decltype(count)::value;
+        T h[N], kq[N], v[N];
+#pragma unroll
+        for (int r = 0; r < N; ++r) arguments<T, D, NMAX>(a.P, s, src, k0 + r, a.A, a.D.K, &h[r], &kq[r]);
+        summands<N>(a.P, s, h, kq, cdf, v);
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            const double vd = static_cast<double>(v[r]);
+            s1 += vd;
+            if constexpr (MODE == kSquares) s2 = fma(vd, vd, s2);
+            if constexpr (MODE == kDAlpha) s2 += static_cast<double>(dalpha_term<T, D, NMAX>(a.P, s, h[r], kq[r], cdf));
         }
-    }
+    };
+    int64_t k = kb;
+    for (; k + R <= ke; k += R) add(std::integral_constant<int, R>{}, k);
+    for (; k < ke; ++k) add(std::integral_constant<int, 1>{}, k);
     if (valid) {
         double* out = a.partials + static_cast<int64_t>(slice) * 2 * G;
         out[g] = s1;
@@ -132,13 +147,16 @@ struct MfmaGeom {
 // designs at once; each wavefront takes every fourth draw.
 // Phase B (vector units): one design per thread, the bivariate normal part.
 // One workgroup's work: tile `tile`, draws of slice `slice`; lds holds
-// mfma_lds_bytes<T>(geo.chunk, D, K) bytes.  The body's first LDS copies are
+// mfma_lds_bytes<T>(geo.chunk, D, K) bytes, cells the FP64 integrand's table of
+// Phi (filled here, visible after the first barrier).  The body's first LDS copies are
 // issued before its first barrier and its last phase B reads LDS after its
 // last one, so a caller that runs another item on the same LDS must
 // synchronise the workgroup in between.  MODE: see kSums.
 template <typename T, int D, int NMAX, int MODE>
 __device__ __forceinline__ void mfma_tile_body(const EvalArgs<T>& a, const MfmaGeom& geo, int64_t tile, int slice,
-                                               char* lds) {
+                                               char* lds, CdfCell* cells) {
+    if constexpr (sizeof(T) == 8) cdf_table_fill(cells);
+    const NormCdf<T> cdf(cells);
     using acc_t = typename std::conditional<sizeof(T) == 8, mf_d4, mf_f4>::type;
     const int K = a.D.K;   // a multiple of 4 (node steps of four)
     const int CH = geo.chunk;
@@ -192,17 +210,6 @@ __device__ __forceinline__ void mfma_tile_body(const EvalArgs<T>& a, const MfmaG
         for (int j = 0; j < D; ++j)
             aH[s][j] = (s < S && m < K) ? a.A[(static_cast<int64_t>(j) * K + m) * mmax + iA[j]] : T(0);
     }
-    // Gauss-Legendre weights of this wavefront's rule: scalar registers in FP32
-    const auto wts = [&]() {
-        if constexpr (sizeof(T) == 4) {
-            BvnWeights<NMAX> w;
-            w.load(st.w, st.n);
-            return w;
-        } else {
-            return st.w;
-        }
-    }();
-
     const int64_t kb = static_cast<int64_t>(slice) * a.slice_len;
     const int64_t ke = min(M, kb + a.slice_len);
     // Stage draws [k0, k0 + nk): their B tables, thresholds and (b0, b1, mu1)
@@ -286,72 +293,71 @@ __device__ __forceinline__ void mfma_tile_body(const EvalArgs<T>& a, const MfmaG
         // The next chunk's copies overlap phase B: sB and sthr are no longer
         // read, and its quads go to the other buffer.
         if (k0 + CH < ke) stage(k0 + CH, static_cast<int>(min<int64_t>(CH, ke - k0 - CH)), sq0 + (buf ^ 1) * CH);
-        // phase B: bivariate normal part for this thread's design; with
-        // kDAlpha also the summand's derivative in alpha_1 (dalpha_term)
-        struct Val {
-            T v, dv;
-        };
-        const auto summand = [&](int i) -> Val {
-            const T O = sO[static_cast<size_t>(i) * kEvalBlock + tid];
-            const Quad<T> dq = sq[i];
-            if constexpr (sizeof(T) == 4) {
-                // arguments times sqrt(log2(e)/2):  h = z1 - mu1,
-                // k = z2 - sqrt(r I) (b0 + b1 O / r)
-                const float h = fmaf(dq.z, -kPhiScale, st.z1s);
-                const float kq2 = fmaf(-st.a1s, dq.y * O, fmaf(-st.a0s, dq.x, st.z2s));
-                float dv = 0.0f;
-                if constexpr (MODE == kDAlpha) {
-                    // phi(x) = 2^(-x'^2) / sqrt(2 pi) at the prescaled x'
-                    const float eh = __builtin_amdgcn_exp2f(-h * h);
-                    if (a.P.zinf & 2) {
-                        dv = st.da1 * eh;
+        // phase B: bivariate normal part for this thread's design, R draws at a
+        // time (their node sums share the exit tests and interleave); with
+        // kDAlpha also the summands' derivatives in alpha_1 (dalpha_term)
+        auto phase_b = [&](auto count, int i0) {
+            constexpr int R = decltype(count)::value;
+            T h[R], kk[R], v[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const T O = sO[static_cast<size_t>(i0 + r) * kEvalBlock + tid];
+                const Quad<T> dq = sq[i0 + r];
+                if constexpr (sizeof(T) == 4) {
+                    // arguments times sqrt(log2(e)/2):  h = z1 - mu1,
+                    // k = z2 - sqrt(r I) (b0 + b1 O / r)
+                    h[r] = fmaf(dq.z, -kPhiScale, st.z1s);
+                    kk[r] = fmaf(-st.a1s, dq.y * O, fmaf(-st.a0s, dq.x, st.z2s));
+                } else {
+                    h[r] = st.z1 - dq.z;
+                    kk[r] = st.z2 - st.srI * (dq.x + dq.y * O * st.invr);
+                }
+            }
+            // 1 - P(both statistics below their critical values)
+            if (a.P.zinf == 0) {
+                bvn_sf_many<NMAX, R>(h, kk, st.bc, st.w, st.n, cdf, v);
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    v[r] = a.P.zinf == 1 ? T(1) - cdf.scaled(kk[r]) : a.P.zinf == 2 ? T(1) - cdf.scaled(h[r]) : T(0);
+            }
+            if constexpr (sizeof(T) == 4 && MODE == kSums && R % 2 == 0) {
+#pragma unroll
+                for (int r = 0; r < R; r += 2) s1 += static_cast<double>(v[r] + v[r + 1]);   // pairs of draws in FP32
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const double vd = static_cast<double>(v[r]);
+                    s1 += vd;
+                    if constexpr (MODE == kSquares) s2 = fma(vd, vd, s2);
+                }
+            }
+            if constexpr (MODE == kDAlpha) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    T dv;
+                    if constexpr (sizeof(T) == 4) {
+                        // phi(x) = 2^(-x'^2) / sqrt(2 pi) at the prescaled x'
+                        const float eh = __builtin_amdgcn_exp2f(-h[r] * h[r]);
+                        if (a.P.zinf & 2) {
+                            dv = st.da1 * eh;
+                        } else {
+                            const float ek = __builtin_amdgcn_exp2f(-kk[r] * kk[r]);
+                            const float ph = eh * norm_cdf_scaled(fmaf(kk[r], st.is, -st.rs * h[r]));
+                            const float pk = ek * norm_cdf_scaled(fmaf(h[r], st.is, -st.rs * kk[r]));
+                            dv = fmaf(st.da1, ph, st.da2 * pk);
+                        }
                     } else {
-                        const float ek = __builtin_amdgcn_exp2f(-kq2 * kq2);
-                        const float ph = eh * norm_cdf_scaled(fmaf(kq2, st.is, -st.rs * h));
-                        const float pk = ek * norm_cdf_scaled(fmaf(h, st.is, -st.rs * kq2));
-                        dv = fmaf(st.da1, ph, st.da2 * pk);
+                        dv = dalpha_term<T, D, NMAX>(a.P, st, h[r], kk[r], cdf);
                     }
+                    s2 += static_cast<double>(dv);
                 }
-                if (a.P.zinf == 0) return {bvn_sf_scaled<NMAX>(h, kq2, st.bc, wts, st.n), dv};
-                if (a.P.zinf == 1) return {1.0f - norm_cdf_scaled(kq2), dv};
-                if (a.P.zinf == 2) return {1.0f - norm_cdf_scaled(h), dv};
-                return {0.0f, dv};
-            } else {
-                const T mu2 = st.srI * (dq.x + dq.y * O * st.invr);
-                const T h = st.z1 - dq.z, kq2 = st.z2 - mu2;
-                T dv = T(0);
-                if constexpr (MODE == kDAlpha) dv = dalpha_term<T, D, NMAX>(a.P, st, h, kq2);
-                // 1 - P(both statistics below their critical values)
-                if (a.P.zinf == 0) return {bvn_sf<NMAX>(h, kq2, st.bc, wts, st.n), dv};
-                if (a.P.zinf == 1) return {T(1) - norm_cdf(kq2), dv};
-                if (a.P.zinf == 2) return {T(1) - norm_cdf(h), dv};
-                return {T(0), dv};
             }
         };
+        constexpr int kDraws = 2;
         int i = 0;
-        for (; i + 1 < nk; i += 2) {
-            const Val v0 = summand(i), v1 = summand(i + 1);
-            if constexpr (sizeof(T) == 4 && MODE == kSums) {
-                s1 += static_cast<double>(v0.v + v1.v);   // pairs of draws summed in FP32 first
-            } else {
-                s1 += static_cast<double>(v0.v);
-                s1 += static_cast<double>(v1.v);
-                if constexpr (MODE == kSquares) {
-                    s2 = fma(static_cast<double>(v0.v), static_cast<double>(v0.v), s2);
-                    s2 = fma(static_cast<double>(v1.v), static_cast<double>(v1.v), s2);
-                } else if constexpr (MODE == kDAlpha) {
-                    s2 += static_cast<double>(v0.dv);
-                    s2 += static_cast<double>(v1.dv);
-                }
-            }
-        }
-        if (i < nk) {
-            const Val w = summand(i);
-            const double v = static_cast<double>(w.v);
-            s1 += v;
-            if constexpr (MODE == kSquares) s2 = fma(v, v, s2);
-            if constexpr (MODE == kDAlpha) s2 += static_cast<double>(w.dv);
-        }
+        for (; i + kDraws <= nk; i += kDraws) phase_b(std::integral_constant<int, kDraws>{}, i);
+        for (; i < nk; ++i) phase_b(std::integral_constant<int, 1>{}, i);
     }
     if (validB) {
         double* out = a.partials + static_cast<int64_t>(slice) * 2 * G;
