@@ -76,7 +76,7 @@ struct DrawJob {
     DevProblem P;
     const double* gh;       // FP64 Gauss-Hermite rule x[K], w[K]
     int K;
-    int64_t first;          // first flattened draw index of this job
+    int64_t first;          // first draw tile of this job in the launch
     DrawArrays<T> D;        // D.M = this job's draws
 };
 
@@ -261,7 +261,9 @@ hipError_t launch_grad(const bmd_problem* p, int prec, const double* d_q, int64_
 // one sweep launch per (precision, d, kernel kind), one workgroup per item.
 DrawArrays<double> draws_fp64_at(const bmd_problem* p, int64_t M, void* ws);
 DrawArrays<float> draws_fp32_at(const bmd_problem* p, int64_t M, void* ws);
-hipError_t launch_draws_batch(int prec, const void* jobs, int n_jobs, int64_t total, hipStream_t s);
+// tiles: draw tiles of all jobs (draw_tiles of each).
+int64_t draw_tiles(const bmd_problem* p, int prec, int64_t M);
+hipError_t launch_draws_batch(int prec, const void* jobs, int n_jobs, int64_t tiles, hipStream_t s);
 // chunk: draws per LDS chunk of the matrix-core items (0 = the one-problem
 // sweep's); variant: launch-bound variant (batch_variants of them, see
 // batch_variant_waves: waves per SIMD the bound keeps, 0 = none).
@@ -280,7 +282,7 @@ hipError_t launch_batch_phase(const bmd_problem* p, int prec, const BatchPhase& 
 hipError_t launch_batch_reset(int* left, unsigned long long* t_done, const int* items, int first, int n,
                               unsigned long long* t_start, hipStream_t s);
 size_t draw_job_bytes(int prec);
-void fill_draw_job(int prec, void* dst, const bmd_problem* p, void* draws_ws, int64_t M, int64_t first);
+void fill_draw_job(int prec, void* dst, const bmd_problem* p, void* draws_ws, int64_t M, int64_t first_tile);
 hipError_t launch_batch_finalize(const BatchFinal* jobs, int n_jobs, int64_t total, hipStream_t s);
 hipError_t launch_inspect_draws(const bmd_problem* p, uint64_t k0, int64_t n, double* u,
                                 double* fields, hipStream_t s);

@@ -1,5 +1,6 @@
 // Per-design and per-draw setup kernels: grid coordinates, subgroup fractions,
 // critical values (Formula 2), axis tables, and the prior draws of Formula 5.
+#include <algorithm>
 #include <cstring>
 
 #include "bmd_internal.hpp"
@@ -354,84 +355,136 @@ __device__ __forceinline__ int32_t count_le(const DevProblem& P, int j, double t
     return lo;
 }
 
-// Prior draw k (Formula 5's Delta^(k)) into slot kk of the per-draw arrays.
-template <typename T>
-__device__ __forceinline__ void draw_one(const DevProblem& P, const double* __restrict__ gh, int K, uint64_t k,
-                                         int64_t kk, int64_t M, const DrawArrays<T>& D) {
-    double u[8];
-    draw_uniforms<8>(k, P.scenario, P.key0, P.key1, P.n_uniform, u);
-    if (P.effect == BMD_EFFECT_STEP) {
-        const double b0 = P.mu_b0 + P.sd_b0 * norm_quantile(u[0]);
-        const double b1 = P.mu_b1 + P.sd_b1 * norm_quantile(u[1]);
-        double t[kMaxDim];
-        // two cutoffs on one biomarker: one true cutoff per draw
-        const int nbio = (P.design_space == BMD_DESIGN_NESTED3 || P.design_space == BMD_DESIGN_NESTED4) ? 1 : P.d;
-        for (int j = 0; j < nbio; ++j) {
-            const double tau = affine_uniform(P.tau_lo, P.tau_hi, u[2 + j]);
-            t[j] = norm_quantile(tau);
-            D.tau[j * M + kk] = tau;
-            if (P.G > 0) D.thr[kk * P.d + j] = count_le(P, j, tau);
-        }
-        double PR;
-        if (nbio == 1) {
-            PR = 1.0 - D.tau[kk];
-        } else {
-            PR = 0.0;
-            T* B = D.B + static_cast<int64_t>(kk) * P.d * K;
-            for (int m = 0; m < K; ++m) {
-                double prod = gh[K + m];
-                const double s = P.sr * gh[m];
-                for (int j = 0; j < P.d; ++j) {
-                    const double v = norm_cdf((s - t[j]) / P.sq);
-                    B[m * P.d + j] = static_cast<T>(j == 0 ? gh[K + m] * v : v);
-                    prod *= v;
-                }
-                PR += prod;
+// Prior draws (Formula 5's Delta^(k)) of one tile: draws k0 + kk0 + i into slots
+// kk0 + i of the per-draw arrays, i < n <= kDrawTile, by a workgroup of
+// kDrawThreads threads.  Three steps through LDS: one (draw, uniform) pair per
+// thread for the Philox words, quantiles, true cutoffs and grid thresholds;
+// one node-table entry per thread and turn, so that consecutive threads write
+// consecutive words; one draw per thread for P(R) (the products over the
+// biomarkers summed in node order) and the scalar fields.  One thread per draw
+// for all of it (seven quantiles and 160 CDFs in turn at five biomarkers, 256
+// registers, each lane writing its own kilobyte of node table) took 395 us for
+// 200,000 draws in FP64, 16.4 us for 10,000 of one biomarker; tiles take 336 and
+// 8.8 us.  (A loop over tiles in the kernel
+// hoists the library's constants out of it: 512 registers, and slower.)
+// TABLE: kNodeMajor B[kk][m][j] (the sweeps), or kDrawMinor B[m][j][M] (the
+// gradient kernel, whose lanes are draws).
+constexpr int kDrawTile = 32, kDrawThreads = 256;
+enum { kNodeMajor = 0, kDrawMinor = 1 };
+
+// Draws of a tile: at most kDrawTile, and few enough that their node values
+// fit 40 KB of LDS.
+__host__ __device__ inline int draw_tile_size(int d, int K) {
+    int n = kDrawTile;
+    while (n > 1 && static_cast<size_t>(n) * d * K * sizeof(double) > 40 * 1024) n /= 2;
+    return n;
+}
+
+template <typename T, int TABLE>
+__device__ __forceinline__ void draw_tile(const DevProblem& P, const double* __restrict__ gh, int K, uint64_t k0,
+                                          int64_t kk0, int n, const DrawArrays<T>& D, double (*val)[8],
+                                          double* node) {
+    const int tid = threadIdx.x;
+    // two cutoffs on one biomarker: one true cutoff per draw
+    const bool step = P.effect == BMD_EFFECT_STEP;
+    const int nbio = (P.design_space == BMD_DESIGN_NESTED3 || P.design_space == BMD_DESIGN_NESTED4) ? 1 : P.d;
+    {
+        const int i = tid % kDrawTile, ui = tid / kDrawTile;   // 8 uniforms a draw at most
+        if (i < n && ui < P.n_uniform) {
+            const uint64_t k = k0 + static_cast<uint64_t>(kk0 + i);
+            const uint4 o = philox4x32_10(make_uint4(static_cast<uint32_t>(k), static_cast<uint32_t>(k >> 32),
+                                                     P.scenario, static_cast<uint32_t>(ui / 2)),
+                                          P.key0, P.key1);
+            double u = (ui & 1) ? uniform52(o.z, o.w) : uniform52(o.x, o.y);
+            if (step && ui >= 2) {
+                const int j = ui - 2;
+                u = affine_uniform(P.tau_lo, P.tau_hi, u);   // the true cutoff quantile
+                D.tau[j * D.M + kk0 + i] = u;
+                if (j == 0) D.tauT[kk0 + i] = static_cast<T>(u);
+                if (TABLE == kNodeMajor && P.G > 0) D.thr[(kk0 + i) * P.d + j] = count_le(P, j, u);
+                if (nbio == 1) val[i][7] = u;
             }
+            val[i][ui] = norm_quantile(u);
         }
+    }
+    __syncthreads();
+    if (step && nbio > 1) {
+        const int per = P.d * K;
+        for (int e = tid; e < n * per; e += kDrawThreads) {
+            const int i = TABLE == kNodeMajor ? e / per : e % n;
+            const int mj = TABLE == kNodeMajor ? e % per : e / n;
+            const int m = mj / P.d, j = mj - m * P.d;
+            const double v = norm_cdf((P.sr * gh[m] - val[i][2 + j]) / P.sq);
+            const T b = static_cast<T>(j == 0 ? gh[K + m] * v : v);
+            if constexpr (TABLE == kNodeMajor) D.B[(kk0 + i) * per + mj] = b;
+            else D.B[static_cast<int64_t>(mj) * D.M + kk0 + i] = b;
+            node[i * per + mj] = v;
+        }
+        __syncthreads();
+        for (int e = tid; e < n * K; e += kDrawThreads) {
+            const int i = e / K, m = e - i * K;
+            double prod = gh[K + m];
+            for (int j = 0; j < P.d; ++j) prod *= node[i * per + m * P.d + j];
+            node[i * per + m * P.d] = prod;   // this thread's own entries
+        }
+        __syncthreads();
+    }
+    if (tid >= n) return;
+    const int64_t kk = kk0 + tid;
+    if (step) {
+        const double b0 = P.mu_b0 + P.sd_b0 * val[tid][0];
+        const double b1 = P.mu_b1 + P.sd_b1 * val[tid][1];
+        double PR = 0.0;
+        if (nbio == 1) PR = 1.0 - val[tid][7];
+        else
+            for (int m = 0; m < K; ++m) PR += node[(tid * K + m) * P.d];
         D.b0[kk] = static_cast<T>(b0);
         D.b1[kk] = static_cast<T>(b1);
         D.PR[kk] = static_cast<T>(PR);
         D.mu1[kk] = static_cast<T>(P.sqrtI * (b0 + b1 * PR));
-        D.tauT[kk] = static_cast<T>(D.tau[kk]);
-        D.q4[4 * kk + 0] = D.b0[kk];
-        D.q4[4 * kk + 1] = D.b1[kk];
-        D.q4[4 * kk + 2] = D.mu1[kk];
-        D.q4[4 * kk + 3] = T(0);
+        if constexpr (TABLE == kNodeMajor) {
+            D.q4[4 * kk + 0] = D.b0[kk];
+            D.q4[4 * kk + 1] = D.b1[kk];
+            D.q4[4 * kk + 2] = D.mu1[kk];
+            D.q4[4 * kk + 3] = T(0);
+        }
     } else {
-        const double e1 = norm_quantile(u[0]);
-        const double e2 = norm_quantile(u[1]);
-        D.e1[kk] = static_cast<T>(e1);
-        D.e2[kk] = static_cast<T>(e2);
-        if (P.n_uniform >= 3) D.e3[kk] = static_cast<T>(norm_quantile(u[2]));
-        if (P.n_uniform >= 4) D.e4[kk] = static_cast<T>(norm_quantile(u[3]));
-        D.mu1[kk] = static_cast<T>(P.sqrtI * (P.th1 + P.sg1 * e1));
+        D.e1[kk] = static_cast<T>(val[tid][0]);
+        D.e2[kk] = static_cast<T>(val[tid][1]);
+        if (P.n_uniform >= 3) D.e3[kk] = static_cast<T>(val[tid][2]);
+        if (P.n_uniform >= 4) D.e4[kk] = static_cast<T>(val[tid][3]);
+        D.mu1[kk] = static_cast<T>(P.sqrtI * (P.th1 + P.sg1 * val[tid][0]));
     }
 }
 
-// One prior draw per thread.
-template <typename T>
-__global__ __launch_bounds__(128) void k_draws(DevProblem P, const double* __restrict__ gh, int K, uint64_t k0, int64_t M,
-                        DrawArrays<T> D) {
-    const int64_t kk = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (kk >= M) return;
-    draw_one<T>(P, gh, K, k0 + static_cast<uint64_t>(kk), kk, M, D);
+// Tile blockIdx.x of the draws from slot base on.
+template <typename T, int TABLE>
+__global__ __launch_bounds__(kDrawThreads) void k_draws(DevProblem P, const double* __restrict__ gh, int K,
+                                                        uint64_t k0, int64_t base, int64_t M, DrawArrays<T> D) {
+    extern __shared__ double node[];
+    __shared__ double val[kDrawTile][8];
+    const int size = draw_tile_size(P.d, K);
+    const int64_t kk0 = base + static_cast<int64_t>(blockIdx.x) * size;
+    draw_tile<T, TABLE>(P, gh, K, k0, kk0, static_cast<int>(min<int64_t>(size, M - kk0)), D, val, node);
 }
 
-// Draws of many problems in one launch: thread t takes draw t - first[s] of the
+// Draws of many problems in one launch: tile t is tile t - first[s] of the
 // last job s with first[s] <= t (jobs in increasing order of first).
 template <typename T>
-__global__ __launch_bounds__(128) void k_draws_batch(const DrawJob<T>* __restrict__ jobs, int n_jobs, int64_t total) {
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t >= total) return;
+__global__ __launch_bounds__(kDrawThreads) void k_draws_batch(const DrawJob<T>* __restrict__ jobs, int n_jobs,
+                                                              int64_t base) {
+    extern __shared__ double node[];
+    __shared__ double val[kDrawTile][8];
+    const int64_t t = base + blockIdx.x;
     int lo = 0, hi = n_jobs - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (jobs[mid].first <= t) lo = mid; else hi = mid - 1;
     }
     const DrawJob<T>& j = jobs[lo];
-    const int64_t kk = t - j.first;
-    draw_one<T>(j.P, j.gh, j.K, static_cast<uint64_t>(kk), kk, j.D.M, j.D);
+    const int size = draw_tile_size(j.P.d, j.K);
+    const int64_t kk0 = (t - j.first) * size;
+    draw_tile<T, kNodeMajor>(j.P, j.gh, j.K, 0, kk0, static_cast<int>(min<int64_t>(size, j.D.M - kk0)), j.D, val, node);
 }
 
 __global__ __launch_bounds__(128) void k_inspect_draws(DevProblem P, const double* __restrict__ gh, int K, uint64_t k0,
@@ -647,14 +700,30 @@ DrawArrays<float> draws_fp32(const bmd_problem* p, int64_t M, const void* ws) {
     return carve<float>(p, BMD_FP32_COMP, M, const_cast<void*>(ws));
 }
 
-hipError_t launch_draws(const bmd_problem* p, int prec, uint64_t k0, int64_t M, void* ws, hipStream_t s) {
+// A launch holds at most kDrawGrid tiles (the grid's thread count stays below
+// 2^32); more draws go in several launches.
+constexpr int64_t kDrawGrid = 1 << 23;
+static size_t draw_lds(int d, int K) { return sizeof(double) * draw_tile_size(d, K) * static_cast<size_t>(d) * K; }
+
+template <typename T, int TABLE>
+static void launch_draws_typed(const bmd_problem* p, int prec, uint64_t k0, int64_t M, void* ws, hipStream_t s) {
     const PrecTables& t = p->tab[prec];
-    if (prec == BMD_FP64)
-        hipLaunchKernelGGL(k_draws<double>, dim3(blocks_for(M, 128)), dim3(128), 0, s, p->P, t.gh, t.K, k0, M,
-                           carve<double>(p, prec, M, ws));
-    else
-        hipLaunchKernelGGL(k_draws<float>, dim3(blocks_for(M, 128)), dim3(128), 0, s, p->P, t.gh, t.K, k0, M,
-                           carve<float>(p, prec, M, ws));
+    const int d = p->P.d;
+    const int64_t tiles = draw_tiles(p, prec, M);
+    for (int64_t t0 = 0; t0 < tiles; t0 += kDrawGrid)
+        hipLaunchKernelGGL((k_draws<T, TABLE>), dim3(static_cast<unsigned>(std::min(tiles - t0, kDrawGrid))),
+                           dim3(kDrawThreads), draw_lds(d, t.K), s, p->P, t.gh, t.K, k0, t0 * draw_tile_size(d, t.K),
+                           M, carve<T>(p, prec, M, ws));
+}
+
+int64_t draw_tiles(const bmd_problem* p, int prec, int64_t M) {
+    const int n = draw_tile_size(p->P.d, p->tab[prec].K);
+    return (M + n - 1) / n;
+}
+
+hipError_t launch_draws(const bmd_problem* p, int prec, uint64_t k0, int64_t M, void* ws, hipStream_t s) {
+    if (prec == BMD_FP64) launch_draws_typed<double, kNodeMajor>(p, prec, k0, M, ws, s);
+    else launch_draws_typed<float, kNodeMajor>(p, prec, k0, M, ws, s);
     return hipGetLastError();
 }
 
@@ -676,14 +745,17 @@ void fill_draw_job(int prec, void* dst, const bmd_problem* p, void* draws_ws, in
     }
 }
 
-hipError_t launch_draws_batch(int prec, const void* jobs, int n_jobs, int64_t total, hipStream_t s) {
-    if (total <= 0) return hipSuccess;
-    if (prec == BMD_FP64)
-        hipLaunchKernelGGL(k_draws_batch<double>, dim3(blocks_for(total, 128)), dim3(128), 0, s,
-                           static_cast<const DrawJob<double>*>(jobs), n_jobs, total);
-    else
-        hipLaunchKernelGGL(k_draws_batch<float>, dim3(blocks_for(total, 128)), dim3(128), 0, s,
-                           static_cast<const DrawJob<float>*>(jobs), n_jobs, total);
+hipError_t launch_draws_batch(int prec, const void* jobs, int n_jobs, int64_t tiles, hipStream_t s) {
+    const size_t lds = 40 * 1024;   // the most a tile takes
+    for (int64_t t0 = 0; t0 < tiles; t0 += kDrawGrid) {
+        const dim3 grid(static_cast<unsigned>(std::min(tiles - t0, kDrawGrid)));
+        if (prec == BMD_FP64)
+            hipLaunchKernelGGL(k_draws_batch<double>, grid, dim3(kDrawThreads), lds, s,
+                               static_cast<const DrawJob<double>*>(jobs), n_jobs, t0);
+        else
+            hipLaunchKernelGGL(k_draws_batch<float>, grid, dim3(kDrawThreads), lds, s,
+                               static_cast<const DrawJob<float>*>(jobs), n_jobs, t0);
+    }
     return hipGetLastError();
 }
 
