@@ -994,6 +994,21 @@ bmd_status bmd_argmax(bmd_problem* p, const double* d_surface, int64_t* h_index,
     return BMD_OK;
 }
 
+// The launches of a gradient call; draws_ready as launch_grad's.
+static bmd_status grad_design(bmd_problem* p, const double* d_q, int64_t B, int64_t M, int32_t prec, bool draws_ready,
+                              double* d_obj, double* d_grad_q, double* d_grad_mu, hipStream_t s) {
+    int n_slices = 0;
+    int64_t slice_len = 0;
+    grad_slices(p, prec, B, M, &n_slices, &slice_len);
+    const size_t need = grad_workspace_bytes(p, prec, B, n_slices, M, slice_len);
+    draws_ready = draws_ready && p->d_ws && p->ws_cap >= need;   // a new workspace holds no draws
+    bmd_status st = ensure(&p->d_ws, &p->ws_cap, need);
+    if (st != BMD_OK) return st;
+    HIP_TRY(launch_grad(p, prec, d_q, B, M, p->d_ws, n_slices, slice_len, draws_ready, d_obj, d_grad_q, d_grad_mu, s),
+            "gradient kernels");
+    return BMD_OK;
+}
+
 bmd_status bmd_grad_design(bmd_problem* p, const double* d_q, int64_t B, uint64_t n_draws, int32_t prec,
                            double* d_obj, double* d_grad_q, double* d_grad_mu, void* stream) {
     g_err.clear();
@@ -1006,25 +1021,7 @@ bmd_status bmd_grad_design(bmd_problem* p, const double* d_q, int64_t B, uint64_
         return fail(BMD_ENOTSUP, "grad_design needs the step prior and cutoff designs");
     DeviceGuard guard(p->device);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t M = static_cast<int64_t>(n_draws);
-    const int chunk = grad_chunk(prec, p->P.d, p->tab[prec].K);
-    // Draw slices: about kSweepRounds rounds of resident workgroups.
-    const int lanes = grad_lanes(B);
-    const int64_t bx = (B * lanes + 127) / 128;   // 128 threads per workgroup, `lanes` per point
-    const int64_t resident = static_cast<int64_t>(p->n_cu) * grad_blocks_per_cu(p, prec);
-    int64_t n_slices = (kSweepRounds * resident + bx - 1) / bx;
-    n_slices = std::max<int64_t>(1, std::min<int64_t>({n_slices, (M + chunk - 1) / chunk, 65535}));
-    // at least 16 draws per thread of a slice, so the per-point setup is amortised
-    int64_t slice_len = std::max<int64_t>((M + n_slices - 1) / n_slices, std::min<int64_t>(M, 16 * lanes));
-    slice_len = (slice_len + chunk - 1) / chunk * chunk;
-    n_slices = (M + slice_len - 1) / slice_len;
-    bmd_status st =
-        ensure(&p->d_ws, &p->ws_cap, grad_workspace_bytes(p, prec, B, static_cast<int>(n_slices), M, slice_len));
-    if (st != BMD_OK) return st;
-    HIP_TRY(launch_grad(p, prec, d_q, B, M, p->d_ws, static_cast<int>(n_slices), slice_len, d_obj, d_grad_q,
-                        d_grad_mu, s),
-            "gradient kernels");
-    return BMD_OK;
+    return grad_design(p, d_q, B, static_cast<int64_t>(n_draws), prec, false, d_obj, d_grad_q, d_grad_mu, s);
 }
 
 namespace {
@@ -1441,6 +1438,7 @@ bmd_status bmd_refine_design(bmd_problem* p, const double* h_q0, uint64_t n_draw
     if (max_iter < 0 || max_iter > 10000 || !(tol >= 0.0)) return fail(BMD_ERANGE, "max_iter or tol out of range");
     if (p->P.effect != BMD_EFFECT_STEP || p->P.design_space != BMD_DESIGN_CUTOFFS)
         return fail(BMD_ENOTSUP, "refinement needs the step prior and cutoff designs");
+    if (n_draws == 0 || n_draws > (1ull << 40)) return fail(BMD_ERANGE, "n_draws must be in [1, 2^40]");
     constexpr int kTrials = 8;
     constexpr double kFirstStep = 0.05, kMaxStep = 0.1, kArmijo = 1e-4;
     const int d = p->P.d;
@@ -1460,11 +1458,15 @@ bmd_status bmd_refine_design(bmd_problem* p, const double* h_q0, uint64_t n_draw
     double* d_f = d_g + kTrials * d;
     std::vector<double> q(d), g(d), tq(kTrials * d), tg(kTrials * d), tf(kTrials);
     for (int j = 0; j < d; ++j) q[j] = std::min(hi, std::max(lo, h_q0[j]));
+    bool drawn = false;
     // objective and gradient at the n points of tq (host) -> tf, tg
     auto evaluate = [&](int n) -> bmd_status {
         HIP_TRY(hipMemcpyAsync(d_q, tq.data(), sizeof(double) * n * d, hipMemcpyHostToDevice, s), "refine upload");
-        const bmd_status st = bmd_grad_design(p, d_q, n, n_draws, prec, d_f, d_g, nullptr, s);
+        // every evaluation uses the same draws: generated by the first, found by the others where
+        // one pass holds them all
+        const bmd_status st = grad_design(p, d_q, n, static_cast<int64_t>(n_draws), prec, drawn, d_f, d_g, nullptr, s);
         if (st != BMD_OK) return st;
+        drawn = true;
         HIP_TRY(hipMemcpyAsync(tf.data(), d_f, sizeof(double) * n, hipMemcpyDeviceToHost, s), "refine download");
         HIP_TRY(hipMemcpyAsync(tg.data(), d_g, sizeof(double) * n * d, hipMemcpyDeviceToHost, s), "refine download");
         HIP_TRY(hipStreamSynchronize(s), "refine sync");

@@ -66,6 +66,7 @@ struct DrawArrays {
     T* q4;      // [M][4] (b0, b1, mu1, 0): one 4-vector per draw for the matrix-core sweep
     double* tau;    // [d][M]
     T* B;       // [M][K][d] Phi((sqrt(rho) x_m - t_j)/sqrt(1-rho)), GH weight folded into j = 0
+                // (gradient calls: [K][d][M])
     int64_t M;
     int K;
 };
@@ -250,11 +251,15 @@ size_t smooth_local_bytes();
 hipError_t launch_smooth_local(const bmd_problem* p, const double* in, const double* q, const double* lo,
                                const double* hi, double* ws, double* out, hipStream_t s);
 size_t grad_workspace_bytes(const bmd_problem* p, int prec, int64_t B, int n_slices, int64_t M, int64_t slice_len);
-int grad_chunk(int prec, int d, int K);
-int grad_blocks_per_cu(const bmd_problem* p, int prec);   // resident gradient workgroups per CU
-int grad_lanes(int64_t B);   // threads per point of the gradient kernel (few points share their draws)
+int64_t grad_pass_draws(const bmd_problem* p, int prec, int64_t M, int64_t slice_len);
+void grad_slices(bmd_problem* p, int prec, int64_t B, int64_t M, int* n_slices, int64_t* slice_len);
+// draws_ready: the workspace still holds this problem's draws 0..M-1 in precision
+// prec from an earlier call on the same M (used when one pass holds them all).
 hipError_t launch_grad(const bmd_problem* p, int prec, const double* d_q, int64_t B, int64_t M, void* ws,
-                       int n_slices, int64_t slice_len, double* obj, double* gq, double* gmu, hipStream_t s);
+                       int n_slices, int64_t slice_len, bool draws_ready, double* obj, double* gq, double* gmu,
+                       hipStream_t s);
+// Draws with the node table draw-minor, B[m][j][M], for the gradient kernel.
+hipError_t launch_grad_draws(const bmd_problem* p, int prec, uint64_t k0, int64_t M, void* ws, hipStream_t s);
 // Batched form.  Sweep records are filled on the host (batch_record_bytes, the
 // record size and the stride the kernel indexes them with, each written by
 // batch_fill_record for scenario `scenario` of the batch);

@@ -83,6 +83,15 @@ __device__ __forceinline__ double affine_uniform(double lo, double hi, double u)
     return lo + x;
 }
 
+// Sum over L consecutive lanes (the wavefront by default) by a butterfly; each
+// returns the first lane's total.
+template <int L = 64>
+__device__ __forceinline__ double wave_total(double v) {
+#pragma unroll
+    for (int off = L / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    return __shfl(v, 0, L);
+}
+
 // ---------------------------------------------------------------------------
 // Univariate normal
 // ---------------------------------------------------------------------------
@@ -278,13 +287,20 @@ struct BvnConst {
     }
 };
 
+// The same constants of one design kept in memory (wave-uniform addresses, so
+// they arrive in scalar registers).
+template <typename T>
+struct BvnView {
+    const T* a;
+    const T* b;
+    T scale;
+};
+
 // The pair weights of a wavefront's rule, read once per design: FP64 in scalar
 // registers (an FP64 operation costs the same with a scalar operand), FP32 in
 // vector registers (an FP32 multiply-add takes 2.5 SIMD cycles a wavefront
 // from vector registers or a literal, 4.4 with a scalar register operand).
-// VEC = false keeps FP32 weights scalar too, for a kernel without vector
-// registers to spare.
-template <typename T, int NMAX, bool VEC = sizeof(T) == 4>
+template <typename T, int NMAX>
 struct BvnWeights {
     T w[NMAX / 2];
     __device__ __forceinline__ void load(const T* __restrict__ src, int n) {
@@ -294,10 +310,8 @@ struct BvnWeights {
             if constexpr (sizeof(T) == 8) {
                 v = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
                                      __builtin_amdgcn_readfirstlane(__double2loint(v)));
-            } else if constexpr (VEC) {
-                asm volatile("" : "+v"(v));   // a vector register
             } else {
-                v = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+                asm volatile("" : "+v"(v));   // a vector register
             }
             w[i] = v;
         }
@@ -316,9 +330,10 @@ struct BvnWeights {
 __device__ __forceinline__ double node_exp(double x) { return exp2_fast(x); }
 __device__ __forceinline__ float node_exp(float x) { return __builtin_amdgcn_exp2f(x); }
 
-template <int I, int R, typename T, int NMAX, typename W>
-__device__ __forceinline__ void bvn_node_pairs(int n, const T (&hk)[R], const T (&hs)[R], const BvnConst<T, NMAX>& c,
-                                               const W& w, T (&acc)[R]) {
+// c: BvnConst<T, NMAX>, or a BvnView of constants in memory; w: the pair weights.
+template <int I, int NMAX, int R, typename T, typename C, typename W>
+__device__ __forceinline__ void bvn_node_pairs(int n, const T (&hk)[R], const T (&hs)[R], const C& c, const W& w,
+                                               T (&acc)[R]) {
     // smallest rule: 4 nodes (FP32 table) or 6 (FP64 table); those need no test
     constexpr int kMinRule = sizeof(T) == 4 ? 4 : 6;
     if constexpr (I < NMAX) {
@@ -329,7 +344,7 @@ __device__ __forceinline__ void bvn_node_pairs(int n, const T (&hk)[R], const T 
             const T e1 = node_exp(fma(c.b[I + 1], hk[r], -(c.a[I + 1] * hs[r])));
             acc[r] = I == 0 ? w[0] * (e0 + e1) : fma(w[I / 2], e0 + e1, acc[r]);
         }
-        bvn_node_pairs<I + 2, R>(n, hk, hs, c, w, acc);
+        bvn_node_pairs<I + 2, NMAX, R>(n, hk, hs, c, w, acc);
     }
 }
 
@@ -346,23 +361,23 @@ __device__ __forceinline__ void bvn_sf_many(const T (&h)[R], const T (&k)[R], co
         hs[r] = fma(h[r], h[r], k[r] * k[r]);
         acc[r] = T(0);
     }
-    bvn_node_pairs<0, R>(n, hk, hs, c, w, acc);
+    bvn_node_pairs<0, NMAX, R>(n, hk, hs, c, w, acc);
 #pragma unroll
     for (int r = 0; r < R; ++r)
         sf[r] = fma(-cdf.scaled(h[r]), cdf.scaled(k[r]), fma(-c.scale, acc[r], T(1)));
 }
 
 // Phi_2(h, k; rho), arguments as above.
-template <int NMAX, typename T, typename W, typename Cdf>
-__device__ __forceinline__ T bvn_cdf_scaled(T h, T k, const BvnConst<T, NMAX>& c, const W& w, int n, const Cdf& cdf) {
+template <int NMAX, typename T, typename C, typename W, typename Cdf>
+__device__ __forceinline__ T bvn_cdf_scaled(T h, T k, const C& c, const W& w, int n, const Cdf& cdf) {
     const T hk[1] = {h * k}, hs[1] = {fma(h, h, k * k)};
     T acc[1] = {T(0)};
-    bvn_node_pairs<0, 1>(n, hk, hs, c, w, acc);
+    bvn_node_pairs<0, NMAX, 1>(n, hk, hs, c, w, acc);
     return fma(cdf.scaled(h), cdf.scaled(k), c.scale * acc[0]);
 }
 // Plain arguments in both precisions.
-template <int NMAX, typename T, typename W, typename Cdf>
-__device__ __forceinline__ T bvn_cdf(T h, T k, const BvnConst<T, NMAX>& c, const W& w, int n, const Cdf& cdf) {
+template <int NMAX, typename T, typename C, typename W, typename Cdf>
+__device__ __forceinline__ T bvn_cdf(T h, T k, const C& c, const W& w, int n, const Cdf& cdf) {
     if constexpr (sizeof(T) == 4)
         return bvn_cdf_scaled<NMAX>(h * kPhiScale, k * kPhiScale, c, w, n, cdf);
     else

@@ -1,7 +1,6 @@
 // Objective and gradient at continuous design points (the differentiation
 // form): d obj / d q_j and d obj / d (mu_b0, mu_b1), averaged over the prior
-// draws, which the draw kernel writes to HBM in passes and the gradient kernel
-// stages chunk by chunk in LDS.
+// draws, which the draw kernel writes to HBM in passes.
 //
 // Per (point, draw) the summand is f = 1 - Phi_2(h, k; rho) with
 //   h = z1 - sqrt(I) (b0 + b1 P(R)),  k = z2 - sqrt(r I) (b0 + b1 O / r),  rho = sqrt(r),
@@ -16,55 +15,53 @@
 
 #include "bmd_internal.hpp"
 #include "device_math.hpp"
-#include "draw_chunk.hpp"
 
 namespace bmd {
 namespace {
 
-constexpr int kGradBlock = 128;   // points per workgroup
-constexpr int kPointFields = 32;
+constexpr int kGradThreads = 256;   // four wavefronts, over points and draws
 
-// Per-point record (FP64):
-//  0 r, 1 z1, 2 z2, 3 dz/drho, 4 valid, 5..10 dr/dq_j, 11..16 q_j, 17..22 c_j
+// What the gradient kernel reads of a point.  FP64: validity, cutoffs, rule
+// size.  T: the constants below, then the bivariate rule's a[NMAX], b[NMAX].
+constexpr int kInfoFields = 9;      // 0 valid, 1..6 q_j, 7 Gauss-Legendre nodes, 8 rho
+enum { kZ1, kZ2, kSrI, kInvR, kRho, kISig, kVV, kScale, kDA, kDZ = kDA + kMaxDim, kUU = kDZ + kMaxDim,
+       kWW = kUU + kMaxDim, kRecHead = kWW + kMaxDim };
+template <typename T>
+constexpr int kGradNmax = sizeof(T) == 8 ? 24 : 12;
+template <typename T>
+constexpr int kGradNodeBlock = 2;   // nodes loaded ahead together
+template <typename T>
+constexpr int kRecSize = kRecHead + 2 * kGradNmax<T>;
 
-__device__ double orthant_factor_gh(const DevProblem& P, const double* c, const double* __restrict__ gh,
-                                    int K, int deriv_axis) {
-    const double* x = gh;
-    const double* w = gh + K;
-    double acc = 0.0;
-    for (int m = 0; m < K; ++m) {
-        const double t = P.sr * x[m];
-        double prod = w[m];
-        for (int j = 0; j < P.d; ++j) {
-            const double a = (t - c[j]) / P.sq;
-            prod *= (j == deriv_axis) ? norm_pdf(a) : norm_cdf(a);
-        }
-        acc += prod;
-    }
-    return acc;
-}
-
-__device__ double bvn_setup24(double h, double k, double rho, const double* __restrict__ gl) {
-    const int n = 24;
+// Common critical value with family-wise error alpha0 at null correlation rho
+// (Formula 2 for two tests), as the design precompute: F(z) = 2 Phi(-z) -
+// Phi_2(-z, -z; rho) - alpha0 falls in z; safeguarded Newton inside [z(alpha0),
+// z(alpha0 / 2)].  Phi_2 by the largest rule, its 24 nodes on the point's L
+// lanes (node constants formed once); every value the same on all of them.
+template <int L>
+__device__ double zstar_lanes(double rho, double alpha0, const double* __restrict__ gl, int lane) {
+    constexpr int n = 24, N = (n + L - 1) / L;
     const double* x = gl + gl_offset(n);
-    const double* w = x + n;
     const double th = asin(rho);
-    const double hk = h * k, hs = 0.5 * (h * h + k * k);
-    double acc = 0.0;
-    for (int i = 0; i < n; ++i) {
-        const double s = sin(0.5 * th * (1.0 + x[i]));
-        const double a = 1.0 / ((1.0 - s) * (1.0 + s));
-        acc += w[i] * exp(a * (s * hk - hs));
+    double e[N], w[N];   // the lane's nodes: w exp(e z^2), e = -1 / (1 + s)
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int at = lane + i * L;
+        e[i] = w[i] = 0.0;
+        if (at < n) {
+            e[i] = -1.0 / (1.0 + sin(0.5 * th * (1.0 + x[at])));
+            w[i] = x[n + at] * (th * 0.079577471545947667884);
+        }
     }
-    return norm_cdf(h) * norm_cdf(k) + th * 0.079577471545947667884 * acc;
-}
-
-__device__ double zstar_pt(double rho, double alpha0, const double* __restrict__ gl) {
     double lo = -norm_quantile(alpha0), hi = -norm_quantile(0.5 * alpha0);
     double z = 0.5 * (lo + hi);
     const double c = sqrt((1.0 - rho) / (1.0 + rho));
     for (int it = 0; it < 60; ++it) {
-        const double F = 2.0 * norm_cdf(-z) - bvn_setup24(-z, -z, rho, gl) - alpha0;
+        const double t = norm_cdf(-z);
+        double nodes = 0.0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) nodes += w[i] * exp(e[i] * (z * z));
+        const double F = 2.0 * t - (t * t + wave_total<L>(nodes)) - alpha0;
         if (F > 0.0) lo = z; else hi = z;
         const double dF = -2.0 * norm_pdf(z) * norm_cdf(z * c);
         double zn = z - F / dF;
@@ -76,67 +73,167 @@ __device__ double zstar_pt(double rho, double alpha0, const double* __restrict__
     return z;
 }
 
-// One thread per point: design quantities, their q-derivatives, and the
-// per-node tables A_j[m] = Phi(a_jm), dA_j[m] = d A_j[m] / d q_j
-// (a_jm = (sqrt(rho_b) x_m - c_j)/sqrt(1 - rho_b); weights folded into j = 0).
+// Node i's constants of the n-point bivariate rule at correlation rho, in
+// BvnConst's pair order (0 past the rule's end).
 template <typename T>
-__global__ __launch_bounds__(128) void k_grad_points(DevProblem P, const double* __restrict__ q_in, int64_t B,
-                              const double* __restrict__ ghp, int Kp, const double* __restrict__ gh, int K,
-                              const double* __restrict__ gl, double* __restrict__ info, T* __restrict__ A,
-                              T* __restrict__ dA) {
-    const int64_t b = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    double* f = info + b * kPointFields;
+__device__ __forceinline__ void rule_constants(double rho, int n, int i, const double* __restrict__ gl, T* a, T* b) {
+    *a = *b = T(0);
+    if (i >= n) return;
+    const int node = i % 2 == 0 ? i / 2 : n - 1 - i / 2;
+    const double s = sin(0.5 * asin(rho) * (1.0 + gl[gl_offset(n) + node]));
+    const double ai = 1.0 / ((1.0 - s) * (1.0 + s));
+    constexpr double l2e = 1.4426950408889634074;
+    *a = static_cast<T>(sizeof(T) == 4 ? ai : 0.5 * l2e * ai);
+    *b = static_cast<T>(sizeof(T) == 4 ? 2.0 * s * ai : l2e * s * ai);
+}
+
+// FP32 only, one thread per point and node (blockIdx.y): `share` consecutive
+// points (a power of two up to a wavefront) take the largest of their node
+// counts.  A count at the upper end of its range of rho is 1e-8 off, which the
+// FP32 values show; a neighbour's larger count takes that away (7e-10 of the
+// objective over 512 points).
+__global__ __launch_bounds__(256) void k_grad_rule(int64_t b0, int64_t B, int share, const double* __restrict__ gl,
+                                                   double* __restrict__ info, float* __restrict__ rec) {
+    const int64_t bw = b0 + static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int64_t b = bw < B ? bw : B - 1;
+    const int i = blockIdx.y;
+    const double rho = info[b * kInfoFields + 8];
+    int n = bvn_nodes_fp32(rho);
+    for (int off = share / 2; off > 0; off >>= 1) n = max(n, __shfl_xor(n, off));
+    if (bw >= B) return;
+    if (i == 0) info[b * kInfoFields + 7] = n;
+    float* f = rec + b * kRecSize<float> + kRecHead + i;
+    rule_constants<float>(rho, n, i, gl, f, f + kGradNmax<float>);
+}
+
+// L lanes per point: subgroup fraction r and its q-derivatives (the lanes
+// share the Gauss-Hermite nodes), critical values (the lanes share the bivariate
+// rule), the constants of the gradient kernel, and the node table
+// AD[b][m][j] = (A_jm, d A_jm / d q_j), A_jm = Phi(a_jm), a_jm = (sqrt(rho_b)
+// x_m - c_j)/sqrt(1 - rho_b), weights folded into j = 0.  (One thread per
+// point walked 128 nodes of up to six CDFs seven times over and the node
+// tables in turn: 1.7 ms however few the points; a wavefront each takes 50 us
+// for 8, 104 for 2,048.)  L = 64 keeps the latency of few points low; beyond
+// kGradWidePoints points, where throughput counts, 16 lanes waste less on the
+// values that all of them form alike (9,000 points, five biomarkers: 305 -> 267 us
+// a call of 100 draws).
+constexpr int64_t kGradWidePoints = 2048;
+template <typename T, int L>
+__global__ __launch_bounds__(256) void k_grad_points(DevProblem P, const double* __restrict__ q_in, int64_t b0, int64_t B,
+                                                     const double* __restrict__ ghp, int Kp,
+                                                     const double* __restrict__ gh, int K,
+                                                     const double* __restrict__ gl, double* __restrict__ info,
+                                                     T* __restrict__ rec, T* __restrict__ AD) {
+    const int64_t bw = b0 + (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) / L;
+    const bool inside = bw < B;
+    const int64_t b = inside ? bw : B - 1;   // lanes past the end shadow the last point (and store nothing)
+    const int lane = threadIdx.x & (L - 1);
     const int d = P.d;
-    double q[kMaxDim], c[kMaxDim];
+    double q[kMaxDim], c[kMaxDim], dens[kMaxDim];
     bool valid = true;
-    for (int j = 0; j < d; ++j) {
-        q[j] = q_in[b * d + j];
+#pragma unroll
+    for (int j = 0; j < kMaxDim; ++j) {
+        q[j] = j < d ? q_in[b * d + j] : 0.5;
         // grid endpoints may round a few ulp past q_lo / q_hi
-        valid = valid && (q[j] >= P.q_lo - 1e-12 && q[j] <= P.q_hi + 1e-12);
+        valid = valid && (j >= d || (q[j] >= P.q_lo - 1e-12 && q[j] <= P.q_hi + 1e-12));
         if (!valid) q[j] = P.q_lo;
-        c[j] = norm_quantile(q[j]);
     }
-    double r, dr[kMaxDim];
+    double mine = q[0];
+#pragma unroll
+    for (int j = 1; j < kMaxDim; ++j) mine = lane == j ? q[j] : mine;
+    const double cl = norm_quantile(mine), dl = norm_pdf(cl);   // lane j: axis j
+#pragma unroll
+    for (int j = 0; j < kMaxDim; ++j) {
+        c[j] = __shfl(cl, j, L);
+        dens[j] = __shfl(dl, j, L);
+    }
+    double r = 0.0, dr[kMaxDim];
+#pragma unroll
+    for (int j = 0; j < kMaxDim; ++j) dr[j] = 0.0;
     if (d == 1) {
         r = 1.0 - q[0];
         dr[0] = -1.0;
     } else {
-        r = orthant_factor_gh(P, c, ghp, Kp, -1);
-        for (int j = 0; j < d; ++j)
-            dr[j] = -orthant_factor_gh(P, c, ghp, Kp, j) / P.sq / norm_pdf(c[j]);
+        for (int m = lane; m < Kp; m += L) {
+            const double t = P.sr * ghp[m];
+            double cd[kMaxDim], pd[kMaxDim], pre[kMaxDim + 1];
+            pre[0] = ghp[Kp + m];
+#pragma unroll
+            for (int j = 0; j < kMaxDim; ++j) {
+                const double a = (t - c[j]) / P.sq;
+                cd[j] = j < d ? norm_cdf(a) : 1.0;
+                pd[j] = j < d ? norm_pdf(a) : 0.0;
+                pre[j + 1] = pre[j] * cd[j];
+            }
+            r += pre[kMaxDim];
+            double suf = 1.0;
+#pragma unroll
+            for (int j = kMaxDim - 1; j >= 0; --j) {
+                dr[j] += pd[j] * (pre[j] * suf);
+                suf *= cd[j];
+            }
+        }
+        r = wave_total<L>(r);
+#pragma unroll
+        for (int j = 0; j < kMaxDim; ++j)
+            if (j < d) dr[j] = -wave_total<L>(dr[j]) / P.sq / dens[j];
     }
     const double rho = sqrt(r);
     double z1, z2, dzdrho = 0.0;
     if (P.alpha_rule == BMD_ALPHA_FWER_EQUAL) {
-        z1 = z2 = zstar_pt(rho, P.alpha0, gl);
+        z1 = z2 = zstar_lanes<L>(rho, P.alpha0, gl, lane);
         // Formula 2 held fixed: dz*/drho = -phi_2(z,z;rho) / (2 phi(z) Phi(z sqrt((1-rho)/(1+rho))))
         const double om = (1.0 - rho) * (1.0 + rho);
-        const double dens = exp(-z1 * z1 / (1.0 + rho)) / (2.0 * M_PI * sqrt(om));
-        dzdrho = -dens / (2.0 * norm_pdf(z1) * norm_cdf(z1 * sqrt((1.0 - rho) / (1.0 + rho))));
+        const double pd2 = exp(-z1 * z1 / (1.0 + rho)) / (2.0 * M_PI * sqrt(om));
+        dzdrho = -pd2 / (2.0 * norm_pdf(z1) * norm_cdf(z1 * sqrt((1.0 - rho) / (1.0 + rho))));
     } else {
         z1 = P.zf1;
         z2 = P.zf2;
     }
-    f[0] = r;
-    f[1] = z1;
-    f[2] = z2;
-    f[3] = dzdrho;
-    f[4] = valid ? 1.0 : 0.0;
-    for (int j = 0; j < kMaxDim; ++j) {
-        f[5 + j] = j < d ? dr[j] : 0.0;
-        f[11 + j] = j < d ? q[j] : 0.0;
-        f[17 + j] = j < d ? c[j] : 0.0;
+    const int n = bvn_nodes_fp64(rho);
+    T* f = rec + b * kRecSize<T>;
+    if (lane == 0 && inside) {
+        double* in = info + b * kInfoFields;
+        in[0] = valid ? 1.0 : 0.0;
+        if constexpr (sizeof(T) == 8) in[7] = n;
+        in[8] = rho;
+        f[kZ1] = static_cast<T>(z1);
+        f[kZ2] = static_cast<T>(z2);
+        f[kSrI] = static_cast<T>(sqrt(r * P.info));
+        f[kInvR] = static_cast<T>(1.0 / r);
+        f[kRho] = static_cast<T>(rho);
+        f[kISig] = static_cast<T>(1.0 / sqrt((1.0 - rho) * (1.0 + rho)));
+        f[kVV] = static_cast<T>(P.sqrtI / rho);
+        f[kScale] = static_cast<T>(asin(rho) * 0.079577471545947667884);   // BvnConst's 1/(4 pi)
+#pragma unroll
+        for (int j = 0; j < kMaxDim; ++j) {
+            const double drho = dr[j] / (2.0 * rho);
+            in[1 + j] = q[j];
+            f[kDA + j] = static_cast<T>(drho);
+            f[kDZ + j] = static_cast<T>(dzdrho * drho);
+            f[kUU + j] = static_cast<T>(P.sqrtI * dr[j] / (2.0 * rho));
+            f[kWW + j] = static_cast<T>(P.sqrtI * dr[j] / (2.0 * r * rho));
+        }
     }
-    if (d >= 2) {
-        for (int j = 0; j < d; ++j) {
-            const double dcdq = 1.0 / norm_pdf(c[j]);
-            for (int m = 0; m < K; ++m) {
-                const double a = (P.sr * gh[m] - c[j]) / P.sq;
-                const double wf = j == 0 ? gh[K + m] : 1.0;
-                A[(static_cast<int64_t>(j) * K + m) * B + b] = static_cast<T>(wf * norm_cdf(a));
-                dA[(static_cast<int64_t>(j) * K + m) * B + b] = static_cast<T>(-wf * norm_pdf(a) / P.sq * dcdq);
+    if constexpr (sizeof(T) == 8)   // FP32: k_grad_rule
+        for (int i = lane; i < kGradNmax<T>; i += L) {
+            T ca, cb;
+            rule_constants<T>(rho, n, i, gl, &ca, &cb);
+            if (inside) {
+                f[kRecHead + i] = ca;
+                f[kRecHead + kGradNmax<T> + i] = cb;
             }
+        }
+    if (d >= 2) {
+        for (int e0 = 0; e0 < d * K; e0 += L) {   // every lane stays for the shuffles
+            const int e = e0 + lane, m = min(e / d, K - 1), j = e % d;
+            const double cj = __shfl(cl, j, L), dj = __shfl(dl, j, L);
+            if (e >= d * K || !inside) continue;
+            const double a = (P.sr * gh[m] - cj) / P.sq;
+            const double wf = j == 0 ? gh[K + m] : 1.0;
+            T* o = AD + (b * K * d + e) * 2;
+            o[0] = static_cast<T>(wf * norm_cdf(a));
+            o[1] = static_cast<T>(-wf * norm_pdf(a) / P.sq / dj);
         }
     }
 }
@@ -149,252 +246,236 @@ __device__ __forceinline__ float lgst(float x) {
 // e^x; FP32 with the hardware exp2.
 __device__ __forceinline__ double expT(double x) { return exp2_fast(1.4426950408889634074 * x); }
 __device__ __forceinline__ float expT(float x) { return __builtin_amdgcn_exp2f(1.4426950408889634074f * x); }
-
 __device__ __forceinline__ double norm_pdf_fast(double x) {
     return 0.39894228040143267794 * exp2_fast(x * x * -0.72134752044448170368);
 }
 __device__ __forceinline__ float norm_pdf_fast(float x) { return norm_pdf(x); }
 
+template <typename T>
 struct GradArgs {
     DevProblem P;
     int64_t B;
     int64_t M;
     int K;
-    int chunk;             // draws staged per chunk
-    const double* info;
-    const void* A;
-    const void* dA;
-    const double* gl;
-    const void* glw;
     int64_t slice_len;
-    int slice0;            // first draw slice of this launch (a pass over draws)
+    int64_t slice0;        // first draw slice of this launch (a pass over draws)
+    int64_t slices;        // slices of this launch
+    int64_t group0, groups;   // workgroup rows of points (pw * PP points each) of this launch
+    int pw;                // wavefronts of a workgroup along the points (1, 2 or 4); the others along the draws
+    bool by_xcd;           // workgroup numbering: see k_grad
     int64_t draw_k0;       // first draw held by the draw arrays of this pass
     double* partials;      // [n_slices][d+3][B]
-    int lanes;             // threads per point (a power of two <= 64): each takes every lanes-th draw pass
 };
 
-// Copy draws k0 .. k0+nk-1 of a pass (local indices) from the draw arrays into
-// the LDS chunk; every thread of the block calls it.  Ends with the chunk
-// visible to the whole block.
-template <typename T, int D>
-__device__ void stage_chunk(const DrawArrays<T>& G, int K, const ChunkView<T>& c, int64_t k0, int nk) {
-    __syncthreads();   // previous chunk fully consumed
-    for (int e = threadIdx.x; e < nk; e += blockDim.x) {
-        c.b0[e] = G.b0[k0 + e];
-        c.b1[e] = G.b1[k0 + e];
-        c.PR[e] = G.PR[k0 + e];
-        c.mu1[e] = G.mu1[k0 + e];
-#pragma unroll
-        for (int j = 0; j < D; ++j) c.tau[e * kMaxDim + j] = G.tau[j * G.M + k0 + e];
-    }
-    if constexpr (D >= 2) {
-        const T* src = G.B + k0 * D * K;   // B rows of consecutive draws are contiguous
-        if constexpr (sizeof(T) == 8) {
-            // FP64: eight loads in flight before their LDS writes, then the
-            // tail one by one (the FP64 refinement's gradient call 5.2 -> 4.1
-            // ms; the FP32 kernel, short of registers, was slower with it)
-            const int total = nk * D * K, bd = blockDim.x;
-            int e = threadIdx.x;
-            for (; e + 7 * bd < total; e += 8 * bd) {
-                T v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = src[e + u * bd];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) c.Bt[e + u * bd] = v[u];
-            }
-            for (; e < total; e += bd) c.Bt[e] = src[e];
-        } else {
-            for (int e = threadIdx.x; e < nk * D * K; e += blockDim.x) c.Bt[e] = src[e];
-        }
-    }
-    __syncthreads();
-}
-
-// R draws per pass over the point's node tables.  SPLIT (few points): `lanes`
-// consecutive threads share a point; thread `sub` of a point takes the draw
-// passes sub, sub + lanes, ... of every chunk, and the point's sums are added
-// across those lanes (a fixed butterfly order) before they are written.  (A
-// separate instantiation: the runtime stride costs the one-lane kernel 17
-// VGPRs and a wavefront per SIMD.)
-template <typename T, int D, int NMAX, int R, bool SPLIT>
-__global__ __launch_bounds__(kGradBlock) void k_grad(GradArgs a, DrawArrays<T> Dr) {
-    extern __shared__ __align__(16) char lds[];
+// One draw per lane, PP points at a time: the lanes of a wavefront hold 64
+// consecutive draws, whose node tables (draw index fastest) load coalesced,
+// and a point's constants and node table are wave-uniform scalar loads.  Per
+// (node m, point), with mix_j = b_j + s_j (a_j - b_j) and L_j the product of the
+// other axes' mixes,
+//   O += prod_j mix_j,  U_j += (a_j - b_j) L_j,  V_j += a'_j L_j,
+// and d O / d q_j = s'_j U_j + s_j V_j after the nodes: 6 D operations a node.
+// FP32 adds (s'_j (a_j - b_j) + s_j a'_j) L_j node by node, 7 D operations: the
+// rounding of V_j is the same for every draw whose other axes have s = 1, so it
+// does not average out over the draws (4e-9 of the gradient).
+// A workgroup takes one slice of draws and one row of points: its wavefronts
+// hold different points and the same draws, so that the node tables come from
+// the L1 for all but the first (from the L2 for every pair of points they
+// limited the kernel at 9.4 TB/s); with fewer points than that the
+// wavefronts split the draws.  A wavefront's sums go through its lanes by a
+// butterfly, draw wavefronts are added in order through LDS.
+// Workgroups reach the XCDs round-robin; with `by_xcd` the rows of one slice
+// get consecutive numbers on one XCD, so that its L2 reads the slice's node
+// tables once.
+// Bound: vector issue (scalar operands of FP32 operations cost 4.4 cycles in
+// place of 2.5, on 2 of the 6).  With one point per lane and the draws staged
+// through LDS, as before, every (node, axis) cost an LDS broadcast a draw and
+// two table loads a pass, and few points left the staging exposed.
+// Measured, d = 5: 2,048 points x 500,000 draws FP32 a call of 35.1 -> 27.4 ms; 8 points x
+// 200,000 draws FP64 1,056 -> 260 us.
+// FP64 is held to 168 registers, three wavefronts per SIMD (a refinement call 2.00 ->
+// 1.90 ms against two).
+template <typename T, int D, int PP>
+__global__ __launch_bounds__(kGradThreads, sizeof(T) == 8 ? 3 : 1) void k_grad(GradArgs<T> a, const double* __restrict__ info,
+                                                       const T* __restrict__ rec, const T* __restrict__ AD,
+                                                       const T* __restrict__ glw, DrawArrays<T> Dr) {
+    constexpr int NMAX = kGradNmax<T>;
+    constexpr int NS = D + 3;   // sums per point: objective, d q_j, d mu_b0, d mu_b1
+    constexpr bool kSplit = sizeof(T) == 8;
     __shared__ CdfCell cells[kCdfTableSize<T>];
-    if constexpr (sizeof(T) == 8) cdf_table_fill(cells);   // visible after the first chunk's barrier
+    __shared__ double red[kGradThreads / 64][PP * NS];
+    int64_t slice, group;
+    if (a.by_xcd) {
+        const uint32_t i = blockIdx.x >> 3, gr = static_cast<uint32_t>(a.groups);
+        slice = static_cast<int64_t>(i / gr) * 8 + (blockIdx.x & 7);
+        group = i % gr;
+        if (slice >= a.slices) return;   // the whole workgroup
+    } else {
+        slice = blockIdx.y;
+        group = blockIdx.x;
+    }
+    group += a.group0;
+    if constexpr (sizeof(T) == 8) {
+        cdf_table_fill(cells);
+        __syncthreads();
+    }
     const NormCdf<T> cdf(cells);
-    const ChunkView<T> ch = carve_chunk<T>(lds, a.chunk, a.K);
     const DevProblem& P = a.P;
     const int K = a.K;
-    const int64_t Bn = a.B;
-    const int L = SPLIT ? a.lanes : 1;
-    const int sub = static_cast<int>(threadIdx.x) & (L - 1);
-    const int64_t b = (static_cast<int64_t>(blockIdx.x) * kGradBlock + threadIdx.x) / L;
-    const bool active = b < Bn;
-    const int64_t bb = active ? b : Bn - 1;
-    const double* f = a.info + bb * kPointFields;
-    const T* A = static_cast<const T*>(a.A);
-    const T* dA = static_cast<const T*>(a.dA);
-
-    const double r = f[0];
-    const double rho = sqrt(r);
-    int n = sizeof(T) == 8 ? bvn_nodes_fp64(rho) : bvn_nodes_fp32(rho);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) n = max(n, __shfl_xor(n, off));
-    n = __builtin_amdgcn_readfirstlane(n);
-    BvnConst<T, NMAX> bc;
-    bc.init(rho, n, a.gl);
-    BvnWeights<T, NMAX, false> wgl;
-    wgl.load(static_cast<const T*>(a.glw) + gl_offset(n) + n, n);
-
     const T sI = static_cast<T>(P.sqrtI);
-    const T srI = static_cast<T>(sqrt(r * P.info));
-    const T invr = static_cast<T>(1.0 / r);
-    const T rhoT = static_cast<T>(rho);
-    const T isig = static_cast<T>(1.0 / sqrt((1.0 - rho) * (1.0 + rho)));
-    const T z1 = static_cast<T>(f[1]), z2 = static_cast<T>(f[2]);
-    const double sqr = sqrt(r);
-    T da[D], dz[D], uu[D], ww[D];
-    double qd[D];
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        const double drj = f[5 + j];
-        const double drho = drj / (2.0 * rho);
-        da[j] = static_cast<T>(drho);
-        dz[j] = static_cast<T>(f[3] * drho);
-        uu[j] = static_cast<T>(P.sqrtI * drj / (2.0 * sqr));
-        ww[j] = static_cast<T>(P.sqrtI * drj / (2.0 * r * sqr));
-        qd[j] = f[11 + j];
-    }
-    const T vv = static_cast<T>(P.sqrtI / sqr);
     const bool logistic = P.width > 0.0;
     const double iw64 = logistic ? 1.0 / P.width : 0.0;
     const T iw = static_cast<T>(iw64);
-
-    double s_obj = 0.0, s_mu0 = 0.0, s_mu1 = 0.0, s_q[D];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int dw = kGradThreads / 64 / a.pw;
+    const int64_t first = (group * a.pw + wave % a.pw) * PP;   // this wavefront's points
+    int64_t b[PP];
 #pragma unroll
-    for (int j = 0; j < D; ++j) s_q[j] = 0.0;
+    for (int p = 0; p < PP; ++p) b[p] = min(first + p, a.B - 1);   // past the end: the last point again
 
-    const int slice = a.slice0 + static_cast<int>(blockIdx.y);
-    const int64_t kb = static_cast<int64_t>(slice) * a.slice_len;
+    double sum[PP][NS];
+#pragma unroll
+    for (int p = 0; p < PP; ++p)
+#pragma unroll
+        for (int i = 0; i < NS; ++i) sum[p][i] = 0.0;
+
+    const int64_t kb = (a.slice0 + slice) * a.slice_len;
     const int64_t ke = min(a.M, kb + a.slice_len);
-    for (int64_t k0 = kb; k0 < ke; k0 += a.chunk) {
-        const int nk = static_cast<int>(min<int64_t>(a.chunk, ke - k0));
-        stage_chunk<T, D>(Dr, K, ch, k0 - a.draw_k0, nk);
-        for (int i0 = sub * R; i0 < nk; i0 += R * L) {
-            T O[R], dO[R][D], s[R][D], sp[R][D];
+    for (int64_t k = kb + 64 * (wave / a.pw) + lane; k < ke; k += 64 * dw) {
+        const int64_t kk = k - a.draw_k0;
+        T O[PP], U[PP][D], V[PP][D], s[PP][D];   // kSplit: the sums; else U is d O / d q_j, V is s'_j
 #pragma unroll
-            for (int rr = 0; rr < R; ++rr) {
-                const int i = min(i0 + rr, nk - 1);
-                O[rr] = T(0);
+        for (int j = 0; j < D; ++j) {
+            const double tau = Dr.tau[j * Dr.M + kk];
 #pragma unroll
-                for (int j = 0; j < D; ++j) {
-                    const double dq = qd[j] - ch.tau[i * kMaxDim + j];
-                    if (logistic) {
-                        s[rr][j] = lgst(static_cast<T>(dq * iw64));
-                        sp[rr][j] = s[rr][j] * (T(1) - s[rr][j]) * iw;
-                    } else {
-                        s[rr][j] = dq > 0.0 ? T(1) : T(0);
-                        sp[rr][j] = T(0);
-                    }
-                    dO[rr][j] = T(0);
-                }
+            for (int p = 0; p < PP; ++p) {
+                const double dq = info[b[p] * kInfoFields + 1 + j] - tau;
+                s[p][j] = logistic ? lgst(static_cast<T>(dq * iw64)) : dq > 0.0 ? T(1) : T(0);
+                U[p][j] = T(0);
+                V[p][j] = kSplit || !logistic ? T(0) : s[p][j] * (T(1) - s[p][j]) * iw;
             }
-            if constexpr (D == 1) {
+        }
 #pragma unroll
-                for (int rr = 0; rr < R; ++rr) {
-                    const int i = min(i0 + rr, nk - 1);
-                    const T tau = static_cast<T>(ch.tau[i * kMaxDim]);
-                    const T q0 = static_cast<T>(qd[0]);
-                    if (logistic) {
-                        O[rr] = T(1) - (s[rr][0] * q0 + (T(1) - s[rr][0]) * tau);
-                        dO[rr][0] = -(s[rr][0] + sp[rr][0] * static_cast<T>(qd[0] - ch.tau[i * kMaxDim]));
-                    } else {
-                        O[rr] = s[rr][0] > T(0) ? T(1) - q0 : T(1) - tau;
-                        dO[rr][0] = s[rr][0] > T(0) ? T(-1) : T(0);
-                    }
-                }
-            } else {
-                for (int m = 0; m < K; ++m) {
-                    T av[D], dav[D];
+        for (int p = 0; p < PP; ++p) O[p] = T(0);
+        if constexpr (D == 1) {
+            const double tau64 = Dr.tau[kk];
+            const T tau = static_cast<T>(tau64);
 #pragma unroll
-                    for (int j = 0; j < D; ++j) {
-                        const int64_t o = (static_cast<int64_t>(j) * K + m) * Bn + bb;
-                        av[j] = A[o];
-                        dav[j] = dA[o];
-                    }
+            for (int p = 0; p < PP; ++p) {   // O and its derivative in closed form
+                const double q64 = info[b[p] * kInfoFields + 1];
+                const T q0 = static_cast<T>(q64);
+                O[p] = logistic ? T(1) - fma(s[p][0], q0, (T(1) - s[p][0]) * tau) : s[p][0] > T(0) ? T(1) - q0 : T(1) - tau;
+                const T du = -static_cast<T>(q64 - tau64);
+                U[p][0] = kSplit ? du : fma(V[p][0], du, -s[p][0]);
+                if constexpr (kSplit) V[p][0] = T(-1);
+            }
+        } else {
+            // node rows by a uniform base and the lane's byte offset (grad_pass_draws keeps it
+            // below 2^32); the next block of nodes is in flight while one is used
+            constexpr int NB = kGradNodeBlock<T>;
+            const uint32_t off = static_cast<uint32_t>(kk) * static_cast<uint32_t>(sizeof(T));
+            const auto load = [&](int m0, T (&to)[NB][D]) {
 #pragma unroll
-                    for (int rr = 0; rr < R; ++rr) {
-                        const int i = min(i0 + rr, nk - 1);
-                        const T* Bi = ch.Bt + (static_cast<size_t>(i) * K + m) * D;
-                        // mix_j = s_j a_j + (1 - s_j) b_j = b_j + s_j (a_j - b_j);
-                        // d mix_j / d q_j = s'_j (a_j - b_j) + s_j a'_j
-                        T dif[D], mix[D], pre[D + 1];
-                        pre[0] = T(1);
+                for (int i = 0; i < NB; ++i)
+#pragma unroll
+                    for (int j = 0; j < D; ++j)
+                        to[i][j] = *reinterpret_cast<const T*>(
+                            reinterpret_cast<const char*>(Dr.B + (static_cast<int64_t>(m0 + i) * D + j) * Dr.M) + off);
+            };
+            T cur[NB][D], nxt[NB][D];
+            load(0, nxt);
+            for (int m0 = 0; m0 < K; m0 += NB) {   // K is a multiple of 4
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+#pragma unroll
+                    for (int j = 0; j < D; ++j) cur[i][j] = nxt[i][j];
+                load(min(m0 + NB, K - NB), nxt);
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+#pragma unroll
+                    for (int p = 0; p < PP; ++p) {
+                        const T* ad = AD + (b[p] * K + m0 + i) * (2 * D);
+                        T dif[D], mix[D], pre[D];
 #pragma unroll
                         for (int j = 0; j < D; ++j) {
-                            const T bv = Bi[j];
-                            dif[j] = av[j] - bv;
-                            mix[j] = fma(s[rr][j], dif[j], bv);
-                            pre[j + 1] = pre[j] * mix[j];
+                            dif[j] = ad[2 * j] - cur[i][j];
+                            mix[j] = fma(s[p][j], dif[j], cur[i][j]);
                         }
-                        O[rr] += pre[D];
+                        pre[0] = T(1);
+#pragma unroll
+                        for (int j = 1; j < D; ++j) pre[j] = j == 1 ? mix[0] : pre[j - 1] * mix[j - 1];
+                        O[p] = fma(pre[D - 1], mix[D - 1], O[p]);
                         T suf = T(1);
 #pragma unroll
                         for (int j = D - 1; j >= 0; --j) {
-                            const T dmix = fma(sp[rr][j], dif[j], s[rr][j] * dav[j]);
-                            dO[rr][j] = fma(dmix, pre[j] * suf, dO[rr][j]);
-                            suf *= mix[j];
+                            const T L = j == D - 1 ? pre[j] : j == 0 ? suf : pre[j] * suf;
+                            if constexpr (kSplit) {
+                                U[p][j] = fma(dif[j], L, U[p][j]);
+                                V[p][j] = fma(ad[2 * j + 1], L, V[p][j]);
+                            } else {
+                                U[p][j] = fma(fma(V[p][j], dif[j], s[p][j] * ad[2 * j + 1]), L, U[p][j]);
+                            }
+                            suf = j == D - 1 ? mix[j] : suf * mix[j];
                         }
                     }
-                }
-            }
-#pragma unroll
-            for (int rr = 0; rr < R; ++rr) {
-                if (i0 + rr >= nk) break;
-                const int i = i0 + rr;
-                const T b0 = ch.b0[i], b1 = ch.b1[i], PR = ch.PR[i], mu1 = ch.mu1[i];
-                const T mu2 = srI * (b0 + b1 * O[rr] * invr);
-                const T h = z1 - mu1, kq = z2 - mu2;
-                T p, ph, pk, pr;
-                if (P.zinf == 0) {
-                    p = bvn_cdf<NMAX>(h, kq, bc, wgl, n, cdf);
-                    ph = norm_pdf_fast(h) * cdf((kq - rhoT * h) * isig);
-                    pk = norm_pdf_fast(kq) * cdf((h - rhoT * kq) * isig);
-                    const T e = (h * h - T(2) * rhoT * h * kq + kq * kq) * isig * isig;
-                    pr = expT(-T(0.5) * e) * isig * T(0.15915494309189533577);
-                } else if (P.zinf == 2) {
-                    p = cdf(h); ph = norm_pdf_fast(h); pk = T(0); pr = T(0);
-                } else if (P.zinf == 1) {
-                    p = cdf(kq); ph = T(0); pk = norm_pdf_fast(kq); pr = T(0);
-                } else {
-                    p = T(1); ph = T(0); pk = T(0); pr = T(0);
-                }
-                s_obj += static_cast<double>(T(1) - p);
-                s_mu0 += static_cast<double>(ph * sI + pk * srI);
-                s_mu1 += static_cast<double>(ph * sI * PR + pk * srI * O[rr] * invr);
-#pragma unroll
-                for (int j = 0; j < D; ++j) {
-                    const T dmu2 = b0 * uu[j] + b1 * (vv * dO[rr][j] - O[rr] * ww[j]);
-                    const T dp = (ph + pk) * dz[j] - pk * dmu2 + pr * da[j];
-                    s_q[j] -= static_cast<double>(dp);
-                }
             }
         }
-    }
-    for (int off = 1; off < L; off <<= 1) {   // the point's lanes are consecutive within one wavefront
-        s_obj += __shfl_xor(s_obj, off);
-        s_mu0 += __shfl_xor(s_mu0, off);
-        s_mu1 += __shfl_xor(s_mu1, off);
+        const T b0 = Dr.b0[kk], b1 = Dr.b1[kk], PR = Dr.PR[kk], mu1 = Dr.mu1[kk];
 #pragma unroll
-        for (int j = 0; j < D; ++j) s_q[j] += __shfl_xor(s_q[j], off);
-    }
-    if (active && sub == 0) {
-        double* out = a.partials + static_cast<int64_t>(slice) * (D + 3) * Bn;
-        out[b] = s_obj;
+        for (int p = 0; p < PP; ++p) {
+            const T* f = rec + b[p] * kRecSize<T>;
+            const int n = __builtin_amdgcn_readfirstlane(static_cast<int>(info[b[p] * kInfoFields + 7]));
+            const T* w = glw + gl_offset(n) + n;
+            const T srI = f[kSrI], invr = f[kInvR], rhoT = f[kRho], isig = f[kISig], vv = f[kVV];
+            const T mu2 = srI * (b0 + b1 * O[p] * invr);
+            const T h = f[kZ1] - mu1, kq = f[kZ2] - mu2;
+            T pc, ph, pk, pr;
+            if (P.zinf == 0) {
+                const BvnView<T> bc{f + kRecHead, f + kRecHead + NMAX, f[kScale]};
+                pc = bvn_cdf<NMAX>(h, kq, bc, w, n, cdf);
+                ph = norm_pdf_fast(h) * cdf((kq - rhoT * h) * isig);
+                pk = norm_pdf_fast(kq) * cdf((h - rhoT * kq) * isig);
+                const T e = (h * h - T(2) * rhoT * h * kq + kq * kq) * isig * isig;
+                pr = expT(-T(0.5) * e) * isig * T(0.15915494309189533577);
+            } else if (P.zinf == 2) {
+                pc = cdf(h); ph = norm_pdf_fast(h); pk = T(0); pr = T(0);
+            } else if (P.zinf == 1) {
+                pc = cdf(kq); ph = T(0); pk = norm_pdf_fast(kq); pr = T(0);
+            } else {
+                pc = T(1); ph = T(0); pk = T(0); pr = T(0);
+            }
+            sum[p][0] += static_cast<double>(T(1) - pc);
 #pragma unroll
-        for (int j = 0; j < D; ++j) out[(1 + j) * Bn + b] = s_q[j];
-        out[(1 + D) * Bn + b] = s_mu0;
-        out[(2 + D) * Bn + b] = s_mu1;
+            for (int j = 0; j < D; ++j) {
+                T dO = U[p][j];
+                if constexpr (kSplit) {
+                    const T sp = logistic ? s[p][j] * (T(1) - s[p][j]) * iw : T(0);
+                    dO = fma(sp, U[p][j], s[p][j] * V[p][j]);
+                }
+                const T dmu2 = b0 * f[kUU + j] + b1 * (vv * dO - O[p] * f[kWW + j]);
+                const T dp = (ph + pk) * f[kDZ + j] - pk * dmu2 + pr * f[kDA + j];
+                sum[p][1 + j] -= static_cast<double>(dp);
+            }
+            sum[p][1 + D] += static_cast<double>(ph * sI + pk * srI);
+            sum[p][2 + D] += static_cast<double>(ph * sI * PR + pk * srI * O[p] * invr);
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < PP; ++p)
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            double v = sum[p][i];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+            if (lane == 0) red[wave][p * NS + i] = v;
+        }
+    __syncthreads();
+    if (threadIdx.x < a.pw * PP * NS) {   // the draw wavefronts' sums in order
+        const int w0 = threadIdx.x / (PP * NS), c = threadIdx.x % (PP * NS), p = c / NS, i = c % NS;
+        const int64_t bp = (group * a.pw + w0) * PP + p;
+        double v = red[w0][c];
+        for (int w = w0 + a.pw; w < kGradThreads / 64; w += a.pw) v += red[w][c];
+        if (bp < a.B) a.partials[((a.slice0 + slice) * NS + i) * a.B + bp] = v;
     }
 }
 
@@ -403,7 +484,7 @@ __global__ void k_grad_finalize(int d, int64_t B, int64_t M, int n_slices, const
                                 double* __restrict__ gq, double* __restrict__ gmu) {
     const int64_t b = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (b >= B) return;
-    const bool valid = info[b * kPointFields + 4] != 0.0;
+    const bool valid = info[b * kInfoFields] != 0.0;
     const double Md = static_cast<double>(M);
     for (int c = 0; c < d + 3; ++c) {
         double s = 0.0;
@@ -434,33 +515,93 @@ __global__ __launch_bounds__(256) void k_grad_finalize_wide(int d, int64_t B, in
         __syncthreads();
     }
     if (threadIdx.x != 0) return;
-    const bool valid = info[b * kPointFields + 4] != 0.0;
+    const bool valid = info[b * kInfoFields] != 0.0;
     const double v = valid ? red[0] / static_cast<double>(M) : NAN;
     if (c == 0) obj[b] = v;
     else if (c <= d) { if (gq) gq[b * d + (c - 1)] = v; }
     else if (gmu) gmu[b * 2 + (c - 1 - d)] = v;
 }
 
-template <typename T, int NMAX, int R, bool SPLIT>
+template <typename T, int PP>
 const void* grad_kernel(int d) {
     switch (d) {
-        case 1: return reinterpret_cast<const void*>(k_grad<T, 1, NMAX, 1, SPLIT>);
-        case 2: return reinterpret_cast<const void*>(k_grad<T, 2, NMAX, R, SPLIT>);
-        case 3: return reinterpret_cast<const void*>(k_grad<T, 3, NMAX, R, SPLIT>);
-        case 4: return reinterpret_cast<const void*>(k_grad<T, 4, NMAX, R, SPLIT>);
-        case 5: return reinterpret_cast<const void*>(k_grad<T, 5, NMAX, R, SPLIT>);
-        default: return reinterpret_cast<const void*>(k_grad<T, 6, NMAX, R, SPLIT>);
+        case 1: return reinterpret_cast<const void*>(k_grad<T, 1, PP>);
+        case 2: return reinterpret_cast<const void*>(k_grad<T, 2, PP>);
+        case 3: return reinterpret_cast<const void*>(k_grad<T, 3, PP>);
+        case 4: return reinterpret_cast<const void*>(k_grad<T, 4, PP>);
+        case 5: return reinterpret_cast<const void*>(k_grad<T, 5, PP>);
+        default: return reinterpret_cast<const void*>(k_grad<T, 6, PP>);
     }
 }
 
-template <typename T, int NMAX, int R>
-hipError_t launch_grad_typed(const GradArgs& ga, const DrawArrays<T>& Dr, int d, int n_slices, hipStream_t s) {
-    const dim3 grid(static_cast<unsigned>((ga.B * ga.lanes + kGradBlock - 1) / kGradBlock),
-                    static_cast<unsigned>(n_slices));
-    const size_t lds = chunk_bytes<T>(ga.chunk, d, ga.K);
-    const void* k = ga.lanes > 1 ? grad_kernel<T, NMAX, R, true>(d) : grad_kernel<T, NMAX, R, false>(d);
-    void* args[] = {const_cast<GradArgs*>(&ga), const_cast<DrawArrays<T>*>(&Dr)};
-    return hipLaunchKernel(k, grid, dim3(kGradBlock), args, lds, s);
+constexpr int kGradPoints = 2;   // points per wavefront
+
+// Wavefronts of a workgroup along the points (as many as they fill), and the
+// rows of points that gives.
+int grad_point_waves(int64_t B) { return B > 2 * kGradPoints ? 4 : B > kGradPoints ? 2 : 1; }
+int64_t grad_groups(int64_t B) {
+    const int64_t per = static_cast<int64_t>(grad_point_waves(B)) * kGradPoints;
+    return (B + per - 1) / per;
+}
+
+// Points go in launches of at most kGradGrid groups or wavefronts (the grid's
+// thread count stays below 2^32).
+constexpr int64_t kGradGrid = 1 << 22;
+
+template <typename T>
+hipError_t launch_grad_typed(GradArgs<T> ga, const double* info, const T* rec, const T* AD, const T* glw,
+                             const DrawArrays<T>& Dr, int d, hipStream_t s) {
+    const int64_t rounds = (ga.slices + 7) / 8, groups = grad_groups(ga.B);
+    ga.pw = grad_point_waves(ga.B);
+    for (ga.group0 = 0; ga.group0 < groups; ga.group0 += kGradGrid) {
+        ga.groups = std::min(groups - ga.group0, kGradGrid);
+        // the XCD numbering needs a slice for every XCD, and a workgroup count within the first dimension
+        ga.by_xcd = ga.slices >= 8 && ga.groups * rounds <= (int64_t(1) << 20);
+        const dim3 grid = ga.by_xcd ? dim3(static_cast<unsigned>(8 * rounds * ga.groups))
+                                    : dim3(static_cast<unsigned>(ga.groups), static_cast<unsigned>(ga.slices));
+        void* args[] = {&ga, &info, &rec, &AD, &glw, const_cast<DrawArrays<T>*>(&Dr)};
+        const hipError_t e = hipLaunchKernel(grad_kernel<T, kGradPoints>(d), grid, dim3(kGradThreads), args, 0, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+template <typename T>
+hipError_t run_grad(const bmd_problem* p, int prec, const double* d_q, int64_t B, int64_t M, char* ws, int n_slices,
+                    int64_t slice_len, bool draws_ready, double* info, double* part, T* rec, T* AD, hipStream_t s) {
+    const int d = p->P.d, K = p->tab[prec].K;
+    const int per = B > kGradWidePoints ? 16 : 4;   // points per workgroup of 256: 16 or 64 lanes each
+    for (int64_t b0 = 0; b0 < B; b0 += per * kGradGrid) {
+        const dim3 grid(static_cast<unsigned>(std::min((B - b0 + per - 1) / per, kGradGrid)));
+        if (per == 16)
+            hipLaunchKernelGGL((k_grad_points<T, 16>), grid, dim3(256), 0, s, p->P, d_q, b0, B, p->d_ghp, kPrecomputeGH,
+                               p->tab[prec].gh, K, p->d_gl, info, rec, AD);
+        else
+            hipLaunchKernelGGL((k_grad_points<T, 64>), grid, dim3(256), 0, s, p->P, d_q, b0, B, p->d_ghp, kPrecomputeGH,
+                               p->tab[prec].gh, K, p->d_gl, info, rec, AD);
+    }
+    if constexpr (sizeof(T) == 4) {
+        int share = 64;   // few points: fewer of them, as few as one for one or two
+        while (share > 1 && B * (64 / share) < 128) share /= 2;
+        for (int64_t b0 = 0; b0 < B; b0 += 256 * kGradGrid)
+            hipLaunchKernelGGL(k_grad_rule, dim3(static_cast<unsigned>(std::min((B - b0 + 255) / 256, kGradGrid)), kGradNmax<T>),
+                               dim3(256), 0, s, b0, B, share, p->d_gl, info, rec);
+    }
+    hipError_t e = hipGetLastError();
+    // Passes over the draws: generate a pass into HBM, then the slices it holds.
+    const int64_t pass = grad_pass_draws(p, prec, M, slice_len);
+    for (int64_t k0 = 0; k0 < M && e == hipSuccess; k0 += pass) {
+        const int64_t np = std::min<int64_t>(pass, M - k0);
+        if (!(draws_ready && pass >= M)) e = launch_grad_draws(p, prec, static_cast<uint64_t>(k0), np, ws, s);
+        if (e != hipSuccess) return e;
+        GradArgs<T> ga{p->P, B, M, K, slice_len, k0 / slice_len, (np + slice_len - 1) / slice_len,
+                       0, 0, 1, false, k0, part};
+        DrawArrays<T> D;
+        if constexpr (sizeof(T) == 8) D = draws_fp64_at(p, np, ws);
+        else D = draws_fp32_at(p, np, ws);
+        e = launch_grad_typed<T>(ga, info, rec, AD, static_cast<const T*>(p->tab[prec].glw), D, d, s);
+    }
+    return e;
 }
 
 }  // namespace
@@ -475,91 +616,78 @@ int64_t grad_pass_draws(const bmd_problem* p, int prec, int64_t M, int64_t slice
     }
     const double per = static_cast<double>(draw_workspace_bytes(p, prec, 1 << 20)) / (1 << 20);
     int64_t slices = static_cast<int64_t>(static_cast<double>(budget) / (per * slice_len));
-    slices = std::max<int64_t>(1, slices);
+    // the kernel addresses a pass's draws with 32-bit byte offsets
+    slices = std::max<int64_t>(1, std::min(slices, (int64_t(1) << 28) / slice_len));
     return std::min<int64_t>(M, slices * slice_len);
 }
 
+static size_t al256(size_t x) { return (x + 255) / 256 * 256; }
+static size_t rec_bytes(int prec, int64_t B) {
+    return prec == BMD_FP64 ? sizeof(double) * kRecSize<double> * B : sizeof(float) * kRecSize<float> * B;
+}
+
+// Layout: the draws of a pass first (so that a later call on the same draws
+// finds them whatever its point count), then the points' records and tables,
+// then the partial sums.
 size_t grad_workspace_bytes(const bmd_problem* p, int prec, int64_t B, int n_slices, int64_t M, int64_t slice_len) {
     const size_t T = prec == BMD_FP64 ? 8 : 4;
     const int d = p->P.d, K = p->tab[prec].K;
-    auto al = [](size_t x) { return (x + 255) / 256 * 256; };
-    return al(sizeof(double) * kPointFields * B) + 2 * al(T * d * K * B) +
-           al(sizeof(double) * (d + 3) * B * n_slices) +
-           al(draw_workspace_bytes(p, prec, grad_pass_draws(p, prec, M, slice_len)));
+    return al256(draw_workspace_bytes(p, prec, grad_pass_draws(p, prec, M, slice_len))) +
+           al256(sizeof(double) * kInfoFields * B) + al256(rec_bytes(prec, B)) + al256(2 * T * d * K * B) +
+           al256(sizeof(double) * (d + 3) * B * n_slices);
 }
 
-int grad_blocks_per_cu(const bmd_problem* p, int prec) {
-    const int d = p->P.d, K = p->tab[prec].K;
-    const int C = grad_chunk(prec, d, K);
-    const void* f = prec == BMD_FP64 ? grad_kernel<double, 24, 1, false>(d) : grad_kernel<float, 12, 2, false>(d);
-    const size_t lds = prec == BMD_FP64 ? chunk_bytes<double>(C, d, K) : chunk_bytes<float>(C, d, K);
+// Draw slices of a call: about kSweepRounds rounds of resident workgroups over
+// the point groups, whole workgroups of draws.
+void grad_slices(bmd_problem* p, int prec, int64_t B, int64_t M, int* n_slices_out, int64_t* slice_len_out) {
+    const void* f = prec == BMD_FP64 ? grad_kernel<double, kGradPoints>(p->P.d) : grad_kernel<float, kGradPoints>(p->P.d);
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kGradBlock, lds) != hipSuccess || nb < 1) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kGradThreads, 0) != hipSuccess || nb < 1) {
         (void)hipGetLastError();
         nb = 1;
     }
-    return nb;
-}
-
-// Threads per point: one when the points fill a workgroup, else the power of
-// two (at most a wavefront) that lets the few points fill one.
-int grad_lanes(int64_t B) {
-    int L = 1;
-    while (L < 64 && B * L < kGradBlock) L *= 2;
-    return L;
-}
-
-// Draws per LDS chunk: as many as fit in 48 KB, at most 32.
-int grad_chunk(int prec, int d, int K) {
-    int C = 32;
-    while (C > 1 && (prec == BMD_FP64 ? chunk_bytes<double>(C, d, K) : chunk_bytes<float>(C, d, K)) > 48 * 1024)
-        C /= 2;
-    return C;
+    const int64_t groups = grad_groups(B), draws = kGradThreads / grad_point_waves(B);   // draws in flight
+    int64_t n_slices = (static_cast<int64_t>(kSweepRounds) * p->n_cu * nb + groups - 1) / groups;
+    n_slices = std::max<int64_t>(1, std::min<int64_t>({n_slices, (M + draws - 1) / draws, 65528}));
+    if (n_slices >= 8) n_slices = (n_slices + 7) / 8 * 8;   // the XCDs take slices in turn
+    int64_t slice_len = (M + n_slices - 1) / n_slices;
+    slice_len = (slice_len + draws - 1) / draws * draws;
+    *n_slices_out = static_cast<int>((M + slice_len - 1) / slice_len);
+    *slice_len_out = slice_len;
 }
 
 hipError_t launch_grad(const bmd_problem* p, int prec, const double* d_q, int64_t B, int64_t M, void* ws,
-                       int n_slices, int64_t slice_len, double* obj, double* gq, double* gmu, hipStream_t s) {
-    const int d = p->P.d, K = p->tab[prec].K;
+                       int n_slices, int64_t slice_len, bool draws_ready, double* obj, double* gq, double* gmu,
+                       hipStream_t s) {
     const size_t T = prec == BMD_FP64 ? 8 : 4;
-    auto al = [](size_t x) { return (x + 255) / 256 * 256; };
-    char* c = static_cast<char*>(ws);
-    double* info = reinterpret_cast<double*>(c);
-    c += al(sizeof(double) * kPointFields * B);
-    void* A = c;
-    c += al(T * d * K * B);
-    void* dA = c;
-    c += al(T * d * K * B);
-    double* part = reinterpret_cast<double*>(c);
-    c += al(sizeof(double) * (d + 3) * B * n_slices);
-    void* dws = c;
-    const unsigned pb = static_cast<unsigned>((B + 127) / 128);
+    const int d = p->P.d, K = p->tab[prec].K;
+    char* base = static_cast<char*>(ws);
+    char* c = base + al256(draw_workspace_bytes(p, prec, grad_pass_draws(p, prec, M, slice_len)));
+    auto take = [&](size_t bytes) {
+        char* at = c;
+        c += al256(bytes);
+        return at;
+    };
+    double* info = reinterpret_cast<double*>(take(sizeof(double) * kInfoFields * B));
+    char* rec = take(rec_bytes(prec, B));
+    char* AD = take(2 * T * d * K * B);
+    double* part = reinterpret_cast<double*>(take(sizeof(double) * (d + 3) * B * n_slices));
+    hipError_t e;
     if (prec == BMD_FP64)
-        hipLaunchKernelGGL(k_grad_points<double>, dim3(pb), dim3(128), 0, s, p->P, d_q, B, p->d_ghp, kPrecomputeGH,
-                           p->tab[prec].gh, K, p->d_gl, info, static_cast<double*>(A), static_cast<double*>(dA));
+        e = run_grad<double>(p, prec, d_q, B, M, base, n_slices, slice_len, draws_ready, info, part,
+                             reinterpret_cast<double*>(rec), reinterpret_cast<double*>(AD), s);
     else
-        hipLaunchKernelGGL(k_grad_points<float>, dim3(pb), dim3(128), 0, s, p->P, d_q, B, p->d_ghp, kPrecomputeGH,
-                           p->tab[prec].gh, K, p->d_gl, info, static_cast<float*>(A), static_cast<float*>(dA));
-    hipError_t e = hipGetLastError();
+        e = run_grad<float>(p, prec, d_q, B, M, base, n_slices, slice_len, draws_ready, info, part,
+                            reinterpret_cast<float*>(rec), reinterpret_cast<float*>(AD), s);
     if (e != hipSuccess) return e;
-    // Passes over the draws: generate a pass into HBM, then the slices it holds.
-    const int64_t pass = grad_pass_draws(p, prec, M, slice_len);
-    for (int64_t k0 = 0; k0 < M; k0 += pass) {
-        const int64_t np = std::min<int64_t>(pass, M - k0);
-        e = launch_draws(p, prec, static_cast<uint64_t>(k0), np, dws, s);
-        if (e != hipSuccess) return e;
-        const int slice0 = static_cast<int>(k0 / slice_len);
-        const int ns = static_cast<int>((np + slice_len - 1) / slice_len);
-        GradArgs ga{p->P, B, M, K, grad_chunk(prec, d, K), info, A, dA, p->d_gl, p->tab[prec].glw,
-                    slice_len, slice0, k0, part, grad_lanes(B)};
-        e = prec == BMD_FP64 ? launch_grad_typed<double, 24, 1>(ga, draws_fp64_at(p, np, dws), d, ns, s)
-                             : launch_grad_typed<float, 12, 2>(ga, draws_fp32_at(p, np, dws), d, ns, s);
-        if (e != hipSuccess) return e;
-    }
-    if (n_slices > 256 && B * (d + 3) <= (int64_t(1) << 20))
+    // one thread per point walking the slices is a serial chain of loads: few
+    // points with more than a handful of slices take a workgroup per component
+    if (n_slices > 16 && B * (d + 3) <= (int64_t(1) << (n_slices > 256 ? 20 : 14)))
         hipLaunchKernelGGL(k_grad_finalize_wide, dim3(static_cast<unsigned>(B * (d + 3))), dim3(256), 0, s, d, B, M,
                            n_slices, part, info, obj, gq, gmu);
     else
-        hipLaunchKernelGGL(k_grad_finalize, dim3(pb), dim3(128), 0, s, d, B, M, n_slices, part, info, obj, gq, gmu);
+        hipLaunchKernelGGL(k_grad_finalize, dim3(static_cast<unsigned>((B + 127) / 128)), dim3(128), 0, s, d, B, M,
+                           n_slices, part, info, obj, gq, gmu);
     return hipGetLastError();
 }
 

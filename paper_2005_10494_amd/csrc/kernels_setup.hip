@@ -727,6 +727,12 @@ hipError_t launch_draws(const bmd_problem* p, int prec, uint64_t k0, int64_t M, 
     return hipGetLastError();
 }
 
+hipError_t launch_grad_draws(const bmd_problem* p, int prec, uint64_t k0, int64_t M, void* ws, hipStream_t s) {
+    if (prec == BMD_FP64) launch_draws_typed<double, kDrawMinor>(p, prec, k0, M, ws, s);
+    else launch_draws_typed<float, kDrawMinor>(p, prec, k0, M, ws, s);
+    return hipGetLastError();
+}
+
 DrawArrays<double> draws_fp64_at(const bmd_problem* p, int64_t M, void* ws) { return carve<double>(p, BMD_FP64, M, ws); }
 DrawArrays<float> draws_fp32_at(const bmd_problem* p, int64_t M, void* ws) {
     return carve<float>(p, BMD_FP32_COMP, M, ws);

@@ -192,12 +192,6 @@ __device__ __forceinline__ PanelNode panel_node(const double* __restrict__ gl, i
     return {0.5 * (1.0 + x[i]), 0.5 * x[kNodes + i] * 0.39894228040143267794, lane / kNodes};
 }
 
-__device__ __forceinline__ double wave_total(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return __shfl(v, 0);
-}
-
 // Phi_3(h1, h2, h3) by the wavefront, the rule of tvn().
 __device__ __forceinline__ double tvn_wave(double h1, double h2, double h3, const TvnConst<double>& c,
                                            const PanelNode& nd) {
