@@ -25,8 +25,9 @@ struct TpsFit {
 
 namespace {
 
-constexpr int kNB = 32;          // Cholesky and triangular-solve block
-constexpr int kUT = 64;          // trailing-update tile (kUT x kUT outputs per workgroup)
+constexpr int kNB = 64;          // Cholesky and triangular-solve block, and the update's output tile
+constexpr int kLS = kNB + 2;     // LDS row stride of a tile: a 16 x 4 operand read touches every bank twice
+constexpr int kIS = 18;          // LDS row stride of a 16 x 16 inverse
 
 // The radial function for D dimensions, fixed at compile time: with the
 // dimension chosen at run time inside one function, the gfx950 code of an
@@ -207,176 +208,236 @@ __global__ void k_tps_rank2(int64_t n, int np, int k, const double* __restrict__
     A[i * n + j] -= vi * wj + wi * vj;
 }
 
-// Panel slices are kPanelRows rows: thread t of a slice owns its row t.
-constexpr int kPanelRows = 128;
+// FP64 16x16x4 matrix instruction: lane l supplies A[l % 16][l / 16] and
+// B[l / 16][l % 16]; element v of its result is row l / 16 + 4 v, column
+// l % 16.  So a result's element v is also the B operand of the v-th slice of
+// four of a following product's 16 inner indices.
+typedef double tps_d4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ tps_d4 mfma64(double a, double b, tps_d4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
 
-// The bs x bs block at blk (row stride n) into L by NT threads: thread t
-// takes column t % kNB of rows t / kNB + (NT / kNB) i, all loads in flight
-// before the first LDS write.
-template <int NT>
-__device__ __forceinline__ void stage_block(const double* __restrict__ blk, int64_t n, int bs, double (*L)[kNB + 1]) {
-    constexpr int kStep = NT / kNB, kIt = kNB / kStep;
-    const int t = threadIdx.x, c = t % kNB, r = t / kNB;
+// 1/sqrt(x): the hardware's estimate (2^-24) and one third-order step.
+__device__ __forceinline__ double rsqrt64(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// The kNB columns [c0, c0 + kNB) of rows [r0, r0 + kNB) of the reduced system
+// (rows from `rows` on: 0) into X: consecutive lanes on consecutive columns,
+// all loads in flight before the first LDS write.
+__device__ __forceinline__ void stage_tile(const double* __restrict__ M, int64_t n, int64_t r0, int64_t rows, int64_t c0,
+                                           double (*X)[kLS]) {
+    constexpr int kIt = kNB * kNB / 256;
+    const int c = threadIdx.x % kNB, r = threadIdx.x / kNB;
     double v[kIt];
 #pragma unroll
-    for (int i = 0; i < kIt; ++i) v[i] = (r + kStep * i < bs && c < bs) ? blk[(r + kStep * i) * n + c] : 0.0;
+    for (int q = 0; q < kIt; ++q) v[q] = r0 + r + 4 * q < rows ? M[(r0 + r + 4 * q) * n + c0 + c] : 0.0;
 #pragma unroll
-    for (int i = 0; i < kIt; ++i) L[r + kStep * i][c] = v[i];
+    for (int q = 0; q < kIt; ++q) X[r + 4 * q][c] = v[q];
 }
 
-// Rows [0, nr) x columns [0, bs) of the slice at base (row stride n) into X:
-// thread t takes column t % kNB of rows t / kNB + 4 i, every load issued
-// before the first LDS write so the loads' latencies overlap.
-__device__ __forceinline__ void stage_rows(const double* __restrict__ base, int64_t n, int nr, int bs,
-                                           double (*X)[kNB + 1]) {
-    static_assert(kPanelRows == 4 * kNB, "four rows per pass");
-    const int t = threadIdx.x, c = t % kNB, r = t / kNB;
-    double v[kNB];
+// Cholesky factor of the kNB x kNB block in the lower triangle of S by four
+// wavefronts, in blocks of 16: afterwards the blocks of S below the diagonal
+// blocks hold -L, and Iv[j] the inverse of diagonal block j.  Each wavefront
+// factors the diagonal block in registers, its rows in lanes 0..15 and the
+// rows of the unit matrix in lanes 16..31 (the same steps turn those into the
+// inverse's transpose; a column's elements go to all lanes as scalars); the
+// rest are products on the matrix cores.  True if a pivot was not positive.
+__device__ __forceinline__ bool factor_block(double (*S)[kLS], double (*Iv)[16][kIS]) {
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63, r16 = lane & 15, kq = lane >> 4;
+    bool neg = false;
+    for (int j = 0; j < kNB / 16; ++j) {
+        const int j0 = 16 * j;
+        double row[16];
 #pragma unroll
-    for (int i = 0; i < kNB; ++i) v[i] = (r + 4 * i < nr && c < bs) ? base[(r + 4 * i) * n + c] : 0.0;
+        for (int c = 0; c < 16; ++c) {
+            const double v = S[j0 + r16][j0 + c];
+            row[c] = lane < 16 ? (c <= r16 ? v : 0.0) : lane < 32 && c == r16 ? 1.0 : 0.0;
+        }
 #pragma unroll
-    for (int i = 0; i < kNB; ++i) X[r + 4 * i][c] = v[i];
+        for (int c = 0; c < 16; ++c) {
+            const double pv = lane_value(row[c], c);
+            neg |= !(pv > 0.0);
+            row[c] *= pv > 0.0 ? rsqrt64(pv) : 1.0;
+#pragma unroll
+            for (int e = c + 1; e < 16; ++e) row[e] = fma(-row[c], lane_value(row[c], e), row[e]);
+        }
+        if (wave == 0 && kq == 1) {
+#pragma unroll
+            for (int c = 0; c < 16; ++c) Iv[j][c][r16] = row[c];
+        }
+        __syncthreads();
+        if (j0 + 16 == kNB) break;
+        const int i = j + 1 + wave;
+        if (i < kNB / 16) {   // block (i, j) of -L
+            tps_d4 x{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x = mfma64(S[16 * i + r16][j0 + 4 * k + kq], Iv[j][r16][4 * k + kq], x);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[16 * i + kq + 4 * v][j0 + r16] = -x[v];
+        }
+        __syncthreads();
+        for (int b = wave, bi = j + 1, bk = j + 1;; ++bk) {   // blocks (bi, bk), j < bk <= bi, every fourth
+            if (bk > bi) bk = j + 1, ++bi;
+            if (bi == kNB / 16) break;
+            if (b-- != 0) continue;
+            b = 3;
+            tps_d4 x{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x = mfma64(S[16 * bi + r16][j0 + 4 * k + kq], S[16 * bk + r16][j0 + 4 * k + kq], x);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[16 * bi + kq + 4 * v][16 * bk + r16] -= x[v];
+        }
+        __syncthreads();
+    }
+    return neg;
 }
 
-// One step of the blocked Cholesky M22 = L L^T at block column kb: the kNB x
-// kNB diagonal block, then the panel below it, L21 = A21 L11^-T.  Every
-// workgroup factors the diagonal block itself in its first wavefront (lane r
-// holds row r in registers; per column j every lane reads the pivot from lane
-// j, lanes below scale their element of column j and update their rows with
-// the other lanes' column-j elements, read from their lanes), so the step is
-// one launch; A's diagonal block is only read, and workgroup 0 stores the
-// factor in Ld (row stride kNB, zeros above the diagonal) for the triangular
-// solves.  The panel's row segments go through LDS with consecutive lanes on
-// consecutive columns (a thread walking its own row in memory would touch a
-// different cache line per lane on every load).  A pivot <= 0 raises *bad.
-__global__ __launch_bounds__(kPanelRows) void k_chol_step(int64_t n, int64_t o, int64_t kb, int bs, int64_t n2,
-                                                          double* __restrict__ A, double* __restrict__ Ld,
-                                                          int* __restrict__ bad) {
-    __shared__ double L[kNB][kNB + 1];
-    __shared__ double X[kPanelRows][kNB + 1];
-    const int t = threadIdx.x;
-    const int64_t r0 = kb + bs + static_cast<int64_t>(blockIdx.x) * kPanelRows;
-    const int nr = static_cast<int>(max<int64_t>(0, min<int64_t>(kPanelRows, n2 - r0)));
-    double* base = A + (o + r0) * n + o + kb;
-    if (nr > 0) stage_rows(base, n, nr, bs, X);
-    if (t < 64) {   // the first wavefront
-        double row[kNB];
+// Step kb of the blocked Cholesky M22 = L L^T, one launch: the trailing update
+// by the previous block column (A -= L21 L21^T) and, in the same launch, block
+// column kb's factor.  M is the reduced system, lower triangle, its row n2 the
+// right-hand side z2, which the steps turn into the forward solve L^-1 z2.
+//   Workgroups 0 .. panels: the block column.  Each updates the diagonal block
+//     for itself (it is only read: no workgroup sees another's results within
+//     a launch), factors it, then updates its own kNB rows below it and solves
+//     them, X L11^T = A21, sixteen rows a wavefront: held transposed, each
+//     16 x 16 block's result is the next product's operand as it stands.
+//     Workgroup 0 solves the unit matrix instead and stores Ld = L11^-T for
+//     the backward solve.
+//   The others: one tile of the update each, four wavefronts of 32 x 32.
+// The factor runs beside the update of the rest, which is bound by reading and
+// writing the trailing matrix (3.4 TB/s as separate launches of rank 32); with
+// few rows left, by the factor's serial chain of 64 pivots.  A launch for the
+// factor (22 us) and one for the update (26 us) per 32 columns, and two (9 us)
+// for the solves, took 12.0 ms for 5,800 centres; one per 64 columns, and one (5.5 us) for the
+// backward solve, take 4.5 ms.
+// A pivot <= 0 raises *bad.
+__global__ __launch_bounds__(256, 2) void k_chol_step(int64_t n, int64_t kb, int bs, int64_t n2, int panels,
+                                                      double* __restrict__ M, double* __restrict__ Ld,
+                                                      int* __restrict__ bad) {
+    __shared__ double Xi[kNB][kLS], Xk[kNB][kLS];
+    __shared__ double Iv[kNB / 16][16][kIS];
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63, r16 = lane & 15, kq = lane >> 4;
+    const int64_t rows = n2 + 1;
+    if (static_cast<int>(blockIdx.x) > panels) {
+        // workgroup b -> lower-triangle tile (ti, tk), tk <= ti, b = ti (ti + 1) / 2 + tk
+        const int64_t b = static_cast<int64_t>(blockIdx.x) - panels - 1;
+        int64_t ti = static_cast<int64_t>((sqrt(8.0 * static_cast<double>(b) + 1.0) - 1.0) * 0.5);
+        while (ti * (ti + 1) / 2 > b) --ti;
+        while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
+        const int64_t i0 = kb + kNB + ti * kNB, k0 = kb + kNB + (b - ti * (ti + 1) / 2) * kNB;
+        const int rb = (wave >> 1) * 32, cb = (wave & 1) * 32;
+        double old[2][2][4];   // in flight during the products
 #pragma unroll
-        for (int c = 0; c < kNB; ++c) row[c] = (t < bs && c <= t) ? A[(o + kb + t) * n + o + kb + c] : 0.0;
-        bool neg = false;
+        for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int j = 0; j < kNB; ++j) {
-            if (j < bs) {   // wave-uniform
-                const double pv = lane_value(row[j], j);
-                neg |= !(pv > 0.0);
-                const double dj = pv > 0.0 ? sqrt(pv) : 1.0;
-                const double lrj = (t > j) ? row[j] / dj : (t == j ? dj : row[j]);
-                row[j] = lrj;
+            for (int q = 0; q < 2; ++q)
 #pragma unroll
-                for (int c = j + 1; c < kNB; ++c) {
-                    const double lcj = lane_value(lrj, c);   // column j of row c
-                    if (t >= c) row[c] -= lrj * lcj;
+                for (int v = 0; v < 4; ++v) {
+                    const int64_t i = i0 + rb + 16 * p + kq + 4 * v, k = k0 + cb + 16 * q + r16;
+                    old[p][q][v] = i < rows && k <= i && k < n2 ? M[i * n + k] : 0.0;
                 }
+        stage_tile(M, n, i0, rows, kb - kNB, Xi);
+        stage_tile(M, n, k0, rows, kb - kNB, Xk);
+        __syncthreads();
+        tps_d4 acc[2][2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) acc[p][q] = tps_d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int c0 = 0; c0 < kNB; c0 += 4) {
+            const double x0 = Xi[rb + r16][c0 + kq], x1 = Xi[rb + 16 + r16][c0 + kq];
+            const double y0 = Xk[cb + r16][c0 + kq], y1 = Xk[cb + 16 + r16][c0 + kq];
+            acc[0][0] = mfma64(x0, y0, acc[0][0]);
+            acc[0][1] = mfma64(x0, y1, acc[0][1]);
+            acc[1][0] = mfma64(x1, y0, acc[1][0]);
+            acc[1][1] = mfma64(x1, y1, acc[1][1]);
+        }
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int64_t i = i0 + rb + 16 * p + kq + 4 * v, k = k0 + cb + 16 * q + r16;
+                    if (i < rows && k <= i && k < n2) M[i * n + k] = old[p][q][v] - acc[p][q][v];
+                }
+        return;
+    }
+    const bool unit = blockIdx.x == 0;
+    const int64_t r0 = kb + bs + (static_cast<int64_t>(blockIdx.x) - 1) * kNB;   // this workgroup's rows
+    // diag[q]: block 4 q + wave of the ten lower 16 x 16 blocks of the diagonal block (past the
+    // block column's end: the unit matrix); x[q]: columns 16 q .. of rows 16 wave .., transposed
+    tps_d4 diag[3], x[4];
+    int bi[3], bk[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int b = min(4 * q + wave, 9);
+        bi[q] = b < 1 ? 0 : b < 3 ? 1 : b < 6 ? 2 : 3;
+        bk[q] = b - bi[q] * (bi[q] + 1) / 2;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = 16 * bi[q] + kq + 4 * v, k = 16 * bk[q] + r16;
+            diag[q][v] = i < bs && k < bs ? (k <= i ? M[(kb + i) * n + kb + k] : 0.0) : i == k ? 1.0 : 0.0;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int k = 16 * q + kq + 4 * v, i = 16 * wave + r16;
+            x[q][v] = unit ? (i == k ? 1.0 : 0.0) : r0 + i < rows && k < bs ? M[(r0 + i) * n + kb + k] : 0.0;
+        }
+    if (kb > 0) {
+        if (!unit) stage_tile(M, n, r0, rows, kb - kNB, Xi);
+        stage_tile(M, n, kb, kb + bs, kb - kNB, Xk);
+        __syncthreads();
+#pragma unroll
+        for (int c0 = 0; c0 < kNB; c0 += 4)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) diag[q] = mfma64(-Xk[16 * bi[q] + r16][c0 + kq], Xk[16 * bk[q] + r16][c0 + kq], diag[q]);
+        if (!unit) {
+#pragma unroll
+            for (int c0 = 0; c0 < kNB; c0 += 4) {
+                const double y = Xi[16 * wave + r16][c0 + kq];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x[q] = mfma64(-Xk[16 * q + r16][c0 + kq], y, x[q]);
             }
         }
-        if (t < kNB) {
-#pragma unroll
-            for (int c = 0; c < kNB; ++c) L[t][c] = c <= t ? row[c] : 0.0;
-        }
-        if (blockIdx.x == 0 && t == 0 && neg) *bad = 1;
+        __syncthreads();   // Xk becomes the diagonal block
     }
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)   // the tenth block comes from waves 1..3 alike
+            Xk[16 * bi[q] + kq + 4 * v][16 * bk[q] + r16] = diag[q][v];
     __syncthreads();
-    if (blockIdx.x == 0) {
-        double* ld = Ld + kb * kNB;
-        for (int e = t; e < kNB * kNB; e += kPanelRows) ld[e] = L[e / kNB][e % kNB];
+    const bool neg = factor_block(Xk, Iv);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int e = 0; e < q; ++e)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x[q] = mfma64(Xk[16 * q + r16][16 * e + 4 * k + kq], x[e][k], x[q]);
+        tps_d4 y{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) y = mfma64(Iv[q][r16][4 * k + kq], x[q][k], y);
+        x[q] = y;
     }
-    if (nr == 0) return;   // workgroup-uniform
-    if (t < nr) {
-        double x[kNB];
+    const int i = 16 * wave + r16;
+    double* to = unit ? Ld + (kb + i) * kNB : M + (r0 + i) * n + kb;
+    if (unit || r0 + i < rows)
 #pragma unroll
-        for (int c = 0; c < kNB; ++c) {
-            if (c < bs) {
-                double s = X[t][c];
-#pragma unroll
-                for (int e = 0; e < kNB; ++e)
-                    if (e < c) s -= x[e] * L[c][e];
-                x[c] = s / L[c][c];
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < kNB; ++c)
-            if (c < bs) X[t][c] = x[c];
-    }
-    __syncthreads();
-    const int c = t % kNB, r = t / kNB;
-#pragma unroll
-    for (int i = 0; i < kNB; ++i)
-        if (r + 4 * i < nr && c < bs) base[(r + 4 * i) * n + c] = X[r + 4 * i][c];
-}
-
-// Trailing update A22 -= L21 L21^T on the lower triangle, kUT x kUT output
-// tiles on the matrix cores (FP64 16x16x4): four wavefronts, each a 32 x 32
-// quarter as 2 x 2 blocks of 16 x 16; the tile's rows of L21 (both factors)
-// staged in LDS; one workgroup per tile on or below the diagonal.  Operand layout of the
-// instruction: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]; its
-// result element v is row l / 16 + 4 v, column l % 16.
-typedef double tps_d4 __attribute__((ext_vector_type(4)));
-
-__global__ __launch_bounds__(256) void k_chol_update(int64_t n, int64_t o, int64_t kb, int bs, int64_t n2,
-                                                     double* __restrict__ A) {
-    const int64_t t0 = kb + bs;
-    // workgroup b -> lower-triangle tile (ti, tk), tk <= ti, b = ti (ti + 1) / 2 + tk
-    const int64_t b = blockIdx.x;
-    int64_t ti = static_cast<int64_t>((sqrt(8.0 * static_cast<double>(b) + 1.0) - 1.0) * 0.5);
-    while (ti * (ti + 1) / 2 > b) --ti;
-    while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
-    const int64_t tk = b - ti * (ti + 1) / 2;
-    __shared__ double Li[kUT][kNB + 1], Lk[kUT][kNB + 1];
-    const int t = threadIdx.x;
-    const int64_t i0 = t0 + ti * kUT, k0 = t0 + tk * kUT;
-    {   // thread t takes column t % kNB of rows t / kNB + 8 q; every load issued before the first LDS write
-        constexpr int kIt = kUT * kNB / 256;
-        const int c = t % kNB, r = t / kNB;
-        double vi[kIt], vk[kIt];
-#pragma unroll
-        for (int q = 0; q < kIt; ++q) {
-            const int rr = r + 8 * q;
-            vi[q] = (i0 + rr < n2 && c < bs) ? A[(o + i0 + rr) * n + o + kb + c] : 0.0;
-            vk[q] = (k0 + rr < n2 && c < bs) ? A[(o + k0 + rr) * n + o + kb + c] : 0.0;
-        }
-#pragma unroll
-        for (int q = 0; q < kIt; ++q) {
-            Li[r + 8 * q][c] = vi[q];
-            Lk[r + 8 * q][c] = vk[q];
-        }
-    }
-    __syncthreads();
-    const int wave = t >> 6, lane = t & 63;
-    const int r16 = lane & 15, kq = lane >> 4;
-    const int rb = (wave >> 1) * 32, cb = (wave & 1) * 32;
-    tps_d4 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = tps_d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int c0 = 0; c0 < kNB; c0 += 4) {
-        const double x0 = Li[rb + r16][c0 + kq], x1 = Li[rb + 16 + r16][c0 + kq];
-        const double y0 = Lk[cb + r16][c0 + kq], y1 = Lk[cb + 16 + r16][c0 + kq];
-        acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y0, acc[0][0], 0, 0, 0);
-        acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y1, acc[0][1], 0, 0, 0);
-        acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y0, acc[1][0], 0, 0, 0);
-        acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y1, acc[1][1], 0, 0, 0);
-    }
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int64_t i = i0 + rb + 16 * a + kq + 4 * v, k = k0 + cb + 16 * b + r16;
-                if (i < n2 && k <= i) A[(o + i) * n + o + k] -= acc[a][b][v];
+                const int k = 16 * q + kq + 4 * v;
+                if (unit || k < bs) to[k] = x[q][v];
             }
+    if (unit && t == 0 && neg) *bad = 1;
 }
 
 // z = Q^T y = H_d ... H_0 y (one workgroup).
@@ -395,67 +456,41 @@ __global__ __launch_bounds__(1024) void k_tps_qty(int64_t n, int np, const doubl
     }
 }
 
-// One block of kNB rows of M22 w = z2 with M22 = L L^T, forward (L t = z2)
-// or backward (L^T w = t): every workgroup solves the block's own rows in its
-// first wavefront from the factor in Ld (lane l holds element l; per row r
-// the solved value is read from lane r and subtracted from the lanes below
-// it, or above it for L^T), workgroup 0 stores them in out, and each
-// workgroup updates its slice of the remaining rows of in: forward the rows
-// below, b[r] -= L[r][kb..] x (row segments through LDS as in the Cholesky
-// step), backward the rows above, b[r] -= L[kb..][r]^T x (consecutive
-// threads on consecutive elements).  The block's own elements of in are only
-// read, so no workgroup sees another's results within a launch.
-__global__ __launch_bounds__(kPanelRows) void k_trsv_step(int64_t n, int64_t o, int64_t kb, int bs, int64_t n2,
-                                                          bool upper, const double* __restrict__ A,
-                                                          const double* __restrict__ Ld, double* __restrict__ in,
-                                                          double* __restrict__ out) {
-    __shared__ double Lb[kNB][kNB + 1];
-    __shared__ double X[kPanelRows][kNB + 1];
-    __shared__ double xb[kNB];
-    const int t = threadIdx.x;
-    stage_block<kPanelRows>(Ld + kb * kNB, kNB, bs, Lb);
-    int64_t r0 = 0;
-    int nr = 0;
-    if (!upper) {
-        r0 = kb + bs + static_cast<int64_t>(blockIdx.x) * kPanelRows;
-        nr = static_cast<int>(max<int64_t>(0, min<int64_t>(kPanelRows, n2 - r0)));
-        if (nr > 0) stage_rows(A + (o + r0) * n + o + kb, n, nr, bs, X);
-    }
-    __syncthreads();
-    if (t < 64) {   // the first wavefront
-        double x = t < bs ? in[kb + t] : 0.0;
-        if (!upper) {
-            for (int r = 0; r < bs; ++r) {
-                const double xr = lane_value(x, r) / Lb[r][r];
-                if (t == r) x = xr;
-                if (t > r && t < bs) x -= Lb[t][r] * xr;
-            }
-        } else {
-            for (int r = bs - 1; r >= 0; --r) {
-                const double xr = lane_value(x, r) / Lb[r][r];
-                if (t == r) x = xr;
-                if (t < r) x -= Lb[r][t] * xr;
-            }
-        }
-        if (t < bs) {
-            xb[t] = x;
-            if (blockIdx.x == 0) out[kb + t] = x;
-        }
-    }
-    __syncthreads();
+// One block of kNB rows of the backward solve L^T w = t: every workgroup forms
+// the block's w = L11^-T t from Ld (four threads a row), workgroup 0 stores
+// it, and each subtracts L[kb ..][r]^T w from kNB of the rows r above (sixteen
+// block rows a wavefront, loaded before w is formed).  The block's own
+// elements of t are only read.
+__global__ __launch_bounds__(256) void k_back_step(int64_t n, int64_t kb, int bs, const double* __restrict__ M,
+                                                   const double* __restrict__ Ld, double* __restrict__ tv,
+                                                   double* __restrict__ w) {
+    __shared__ double wb[kNB];
+    __shared__ double part[4][kNB];
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    const int64_t r = static_cast<int64_t>(blockIdx.x) * kNB + lane;
+    double l[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) l[c] = r < kb && 16 * wave + c < bs ? M[(kb + 16 * wave + c) * n + r] : 0.0;
+    const int row = t >> 2, q = t & 3;
     double s = 0.0;
-    if (!upper) {
-        if (t < nr) {
-            for (int c = 0; c < bs; ++c) s = fma(X[t][c], xb[c], s);
-            in[r0 + t] -= s;
-        }
-    } else {
-        const int64_t r = static_cast<int64_t>(blockIdx.x) * kPanelRows + t;
-        if (r < kb) {
-            for (int c = 0; c < bs; ++c) s = fma(A[(o + kb + c) * n + o + r], xb[c], s);
-            in[r] -= s;
-        }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {   // columns 4 j + q: the four threads of a row read one segment
+        const int c = 4 * j + q;
+        if (c < bs) s = fma(Ld[(kb + row) * kNB + c], tv[kb + c], s);
     }
+    s += __shfl_xor(s, 1);
+    s += __shfl_xor(s, 2);
+    if (q == 0) {
+        wb[row] = s;
+        if (blockIdx.x == 0 && row < bs) w[kb + row] = s;
+    }
+    __syncthreads();
+    double a = 0.0;
+#pragma unroll
+    for (int c = 0; c < 16; ++c) a = fma(l[c], wb[16 * wave + c], a);
+    part[wave][lane] = a;
+    __syncthreads();
+    if (wave == 0 && r < kb) tv[r] -= (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
 }
 
 // c = Q [0; w] = H_0 ... H_d [0; w] and R a = z1 - M12 w; writes c and a into
@@ -463,17 +498,18 @@ __global__ __launch_bounds__(kPanelRows) void k_trsv_step(int64_t n, int64_t o, 
 __global__ __launch_bounds__(1024) void k_tps_coeffs(int64_t n, int np, const double* __restrict__ A,
                                                      const double* __restrict__ V, const double* __restrict__ tau,
                                                      const double* __restrict__ R, const double* __restrict__ z,
-                                                     double* __restrict__ c, double* __restrict__ a) {
+                                                     const double* __restrict__ w, double* __restrict__ c,
+                                                     double* __restrict__ a) {
     __shared__ double red[16];
     __shared__ double rhs[kMaxDim + 1];
     const int t = threadIdx.x;
     for (int k = 0; k < np; ++k) {   // z1_k - sum_j M[k][np + j] w_j
         double s = 0.0;
-        for (int64_t j = np + t; j < n; j += blockDim.x) s = fma(A[k * n + j], z[j], s);
+        for (int64_t j = np + t; j < n; j += blockDim.x) s = fma(A[k * n + j], w[j - np], s);
         s = block_sum(s, red);
         if (t == 0) rhs[k] = z[k] - s;
     }
-    for (int64_t i = t; i < n; i += blockDim.x) c[i] = i < np ? 0.0 : z[i];
+    for (int64_t i = t; i < n; i += blockDim.x) c[i] = i < np ? 0.0 : w[i - np];
     __syncthreads();
     for (int k = np - 1; k >= 0; --k) {
         double s = 0.0;
@@ -602,17 +638,17 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
     const int d = P.d, np = d + 1;
     const int64_t G = P.G;
     TpsFitResult res{kTpsOk, 0, hipSuccess};
-    int64_t n = 0, n2 = 0, o = 0;
+    int64_t n = 0, n2 = 0;
     int bad = 0;
     char* small = nullptr;   // idx [G], n, bad flag; tau, R, kappa
-    double* big = nullptr;   // A [n n], V and P [n (d + 1)], y, z, p [n]
+    double* big = nullptr;   // A [n n], z [n] as its row n, V and P [n (d + 1)], y, p, w [n], Ld
     double* fitmem = nullptr;
     int64_t* d_idx = nullptr;
     int64_t* d_n = nullptr;
     int* d_bad = nullptr;
     double *d_tau = nullptr, *d_R = nullptr, *d_kappa = nullptr;
-    double *A = nullptr, *V = nullptr, *Pm = nullptr, *y = nullptr, *z = nullptr, *pv = nullptr;
-    double *Ld = nullptr, *T = nullptr;   // diagonal blocks of the factor; the forward solve's result
+    double *A = nullptr, *V = nullptr, *Pm = nullptr, *y = nullptr, *z = nullptr, *pv = nullptr, *M = nullptr;
+    double *Ld = nullptr, *w = nullptr;   // inverses of the factor's diagonal blocks; the reduced system's solution
     double *U = nullptr, *c = nullptr, *a = nullptr;
     const size_t small_bytes = sizeof(int64_t) * (G + 2) + 64 + sizeof(double) * (2 * np + np * np + 8);
     if (hipMalloc(&small, small_bytes) != hipSuccess) {
@@ -646,13 +682,13 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
             goto done;
         }
         A = big;
-        V = A + nn * nn;
+        z = A + nn * nn;
+        V = z + nn;
         Pm = V + nn * np;
         y = Pm + nn * np;
-        z = y + nn;
-        pv = z + nn;
-        Ld = pv + nn;
-        T = Ld + kNB * (nn + kNB);
+        pv = y + nn;
+        w = pv + nn;
+        Ld = w + nn;
         U = fitmem;
         c = U + nn * d;
         a = c + nn;
@@ -676,33 +712,24 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
                            dim3(256), 0, s, n, np, k, V, pv, d_kappa, A);
         TPS_TRY(hipGetLastError());
     }
-    o = np;
+    hipLaunchKernelGGL(k_tps_qty, dim3(1), dim3(1024), 0, s, n, np, V, d_tau, y, z);
+    TPS_TRY(hipGetLastError());
     n2 = n - np;
-    for (int64_t kb = 0; kb < n2; kb += kNB) {   // M22 = L L^T
+    M = A + np * n + np;   // the reduced system, row stride n; its row n2 is z2
+    for (int64_t kb = 0; kb < n2; kb += kNB) {   // M22 = L L^T, L t = z2
         const int bs = static_cast<int>(std::min<int64_t>(kNB, n2 - kb));
-        const int64_t rest = n2 - kb - bs;
-        hipLaunchKernelGGL(k_chol_step, dim3(static_cast<unsigned>(std::max<int64_t>(1, (rest + kPanelRows - 1) / kPanelRows))),
-                           dim3(kPanelRows), 0, s, n, o, kb, bs, n2, A, Ld, d_bad);
-        if (rest > 0) {
-            const int64_t tiles = (rest + kUT - 1) / kUT;
-            hipLaunchKernelGGL(k_chol_update, dim3(static_cast<unsigned>(tiles * (tiles + 1) / 2)), dim3(256), 0, s, n,
-                               o, kb, bs, n2, A);
-        }
+        const int64_t panels = (n2 + 1 - kb - bs + kNB - 1) / kNB;
+        const int64_t tiles = kb > 0 && kb + kNB < n2 ? (n2 + 1 - kb - kNB + kNB - 1) / kNB : 0;
+        hipLaunchKernelGGL(k_chol_step, dim3(static_cast<unsigned>(1 + panels + tiles * (tiles + 1) / 2)), dim3(256), 0,
+                           s, n, kb, bs, n2, static_cast<int>(panels), M, Ld, d_bad);
         TPS_TRY(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_tps_qty, dim3(1), dim3(1024), 0, s, n, np, V, d_tau, y, z);
-    for (int64_t kb = 0; kb < n2; kb += kNB) {   // L t = z2: z2 = z [o, n) in, t out
+    for (int64_t kb = ((n2 - 1) / kNB) * kNB; kb >= 0; kb -= kNB) {   // L^T w = t
         const int bs = static_cast<int>(std::min<int64_t>(kNB, n2 - kb));
-        const int64_t rest = n2 - kb - bs;
-        hipLaunchKernelGGL(k_trsv_step, dim3(static_cast<unsigned>(std::max<int64_t>(1, (rest + kPanelRows - 1) / kPanelRows))),
-                           dim3(kPanelRows), 0, s, n, o, kb, bs, n2, false, A, Ld, z + o, T);
+        hipLaunchKernelGGL(k_back_step, dim3(static_cast<unsigned>(std::max<int64_t>(1, kb / kNB))), dim3(256), 0, s, n,
+                           kb, bs, M, Ld, z + np, w);
     }
-    for (int64_t kb = ((n2 - 1) / kNB) * kNB; kb >= 0; kb -= kNB) {   // L^T w = t: t in, w out to z [o, n)
-        const int bs = static_cast<int>(std::min<int64_t>(kNB, n2 - kb));
-        hipLaunchKernelGGL(k_trsv_step, dim3(static_cast<unsigned>(std::max<int64_t>(1, (kb + kPanelRows - 1) / kPanelRows))),
-                           dim3(kPanelRows), 0, s, n, o, kb, bs, n2, true, A, Ld, T, z + o);
-    }
-    hipLaunchKernelGGL(k_tps_coeffs, dim3(1), dim3(1024), 0, s, n, np, A, V, d_tau, d_R, z, c, a);
+    hipLaunchKernelGGL(k_tps_coeffs, dim3(1), dim3(1024), 0, s, n, np, A, V, d_tau, d_R, z, w, c, a);
     TPS_TRY(hipGetLastError());
     TPS_TRY(hipMemcpyAsync(&bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, s));
     TPS_TRY(hipStreamSynchronize(s));
