@@ -113,9 +113,9 @@ __global__ void k_tps_points(DevProblem P, int64_t n, const int64_t* __restrict_
     y[i] = f[idx[i]];
 }
 
-// A = Phi + lam I (n x n, row-major).
+// A = Phi + lam I (n x n, row stride ld).
 template <int D>
-__global__ void k_tps_matrix(int64_t n, const double* __restrict__ U, double lam, double* __restrict__ A) {
+__global__ void k_tps_matrix(int64_t n, int64_t ld, const double* __restrict__ U, double lam, double* __restrict__ A) {
     const int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     const int64_t i = blockIdx.y;
     if (k >= n) return;
@@ -125,7 +125,7 @@ __global__ void k_tps_matrix(int64_t n, const double* __restrict__ U, double lam
         const double s = U[i * D + j] - U[k * D + j];
         r2 = fma(s, s, r2);
     }
-    A[i * n + k] = tps_phi<D>(sqrt(r2)) + (i == k ? lam : 0.0);
+    A[i * ld + k] = tps_phi<D>(sqrt(r2)) + (i == k ? lam : 0.0);
 }
 
 // Householder QR of P [n][d + 1] (one workgroup): reflector k is
@@ -174,13 +174,13 @@ __global__ __launch_bounds__(1024) void k_tps_qr(int64_t n, int d, double* __res
 }
 
 // p = tau_k A v_k, one workgroup per row.
-__global__ __launch_bounds__(256) void k_tps_gemv(int64_t n, int np, int k, const double* __restrict__ A,
+__global__ __launch_bounds__(256) void k_tps_gemv(int64_t n, int64_t ld, int np, int k, const double* __restrict__ A,
                                                   const double* __restrict__ V, const double* __restrict__ tau,
                                                   double* __restrict__ p) {
     __shared__ double red[4];
     const int64_t i = blockIdx.x;
     double s = 0.0;
-    for (int64_t j = threadIdx.x + k; j < n; j += blockDim.x) s = fma(A[i * n + j], V[j * np + k], s);
+    for (int64_t j = threadIdx.x + k; j < n; j += blockDim.x) s = fma(A[i * ld + j], V[j * np + k], s);
     s = block_sum(s, red);
     if (threadIdx.x == 0) p[i] = tau[k] * s;
 }
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(1024) void k_tps_kappa(int64_t n, int np, int k, co
 }
 
 // A <- H A H = A - v w^T - w v^T with w = p - K v.
-__global__ void k_tps_rank2(int64_t n, int np, int k, const double* __restrict__ V, const double* __restrict__ p,
+__global__ void k_tps_rank2(int64_t n, int64_t ld, int np, int k, const double* __restrict__ V, const double* __restrict__ p,
                             const double* __restrict__ kappa, double* __restrict__ A) {
     const int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     const int64_t i = blockIdx.y;
@@ -205,7 +205,7 @@ __global__ void k_tps_rank2(int64_t n, int np, int k, const double* __restrict__
     const double K = *kappa;
     const double vi = V[i * np + k], vj = V[j * np + k];
     const double wi = p[i] - K * vi, wj = p[j] - K * vj;
-    A[i * n + j] -= vi * wj + wi * vj;
+    A[i * ld + j] -= vi * wj + wi * vj;
 }
 
 // FP64 16x16x4 matrix instruction: lane l supplies A[l % 16][l / 16] and
@@ -217,37 +217,61 @@ __device__ __forceinline__ tps_d4 mfma64(double a, double b, tps_d4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// 1/sqrt(x): the hardware's estimate (2^-24) and one third-order step.
+// Orders a wavefront's LDS writes before its other lanes' reads.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// 1/sqrt(x) and 1/x: the hardware's estimates (2^-24) and one third-order step.
 __device__ __forceinline__ double rsqrt64(double x) {
     const double y = __builtin_amdgcn_rsq(x);
     const double e = fma(-(x * y), y, 1.0);
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
-
-// The kNB columns [c0, c0 + kNB) of rows [r0, r0 + kNB) of the reduced system
-// (rows from `rows` on: 0) into X: consecutive lanes on consecutive columns,
-// all loads in flight before the first LDS write.
-__device__ __forceinline__ void stage_tile(const double* __restrict__ M, int64_t n, int64_t r0, int64_t rows, int64_t c0,
-                                           double (*X)[kLS]) {
-    constexpr int kIt = kNB * kNB / 256;
-    const int c = threadIdx.x % kNB, r = threadIdx.x / kNB;
-    double v[kIt];
-#pragma unroll
-    for (int q = 0; q < kIt; ++q) v[q] = r0 + r + 4 * q < rows ? M[(r0 + r + 4 * q) * n + c0 + c] : 0.0;
-#pragma unroll
-    for (int q = 0; q < kIt; ++q) X[r + 4 * q][c] = v[q];
+__device__ __forceinline__ double rcp64(double x) {
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
 }
 
-// Cholesky factor of the kNB x kNB block in the lower triangle of S by four
-// wavefronts, in blocks of 16: afterwards the blocks of S below the diagonal
-// blocks hold -L, and Iv[j] the inverse of diagonal block j.  Each wavefront
-// factors the diagonal block in registers, its rows in lanes 0..15 and the
-// rows of the unit matrix in lanes 16..31 (the same steps turn those into the
-// inverse's transpose; a column's elements go to all lanes as scalars); the
-// rest are products on the matrix cores.  True if a pivot was not positive.
-__device__ __forceinline__ bool factor_block(double (*S)[kLS], double (*Iv)[16][kIS]) {
+// The kNB columns [c0, c0 + kNB) of rows [r0, r0 + kNB) of the reduced system
+// (rows from `rows` on: 0), consecutive lanes on consecutive columns, and
+// their place in LDS.
+constexpr int kTileIt = kNB * kNB / 256;
+__device__ __forceinline__ void load_tile(const double* __restrict__ M, int64_t ld, int64_t r0, int64_t rows, int64_t c0,
+                                          double (&v)[kTileIt]) {
+    const int c = threadIdx.x % kNB, r = threadIdx.x / kNB, left = static_cast<int>(min<int64_t>(rows - r0, kNB));
+    const uint32_t off = static_cast<uint32_t>(r * static_cast<int>(ld) + c);
+    if (left == kNB) {   // whole tiles without a branch per load
+#pragma unroll
+        for (int q = 0; q < kTileIt; ++q) v[q] = (M + (r0 + 4 * q) * ld + c0)[off];
+    } else {
+#pragma unroll
+        for (int q = 0; q < kTileIt; ++q) v[q] = r + 4 * q < left ? (M + (r0 + 4 * q) * ld + c0)[off] : 0.0;
+    }
+}
+__device__ __forceinline__ void store_tile(const double (&v)[kTileIt], double (*X)[kLS]) {
+    const int c = threadIdx.x % kNB, r = threadIdx.x / kNB;
+#pragma unroll
+    for (int q = 0; q < kTileIt; ++q) X[r + 4 * q][c] = v[q];
+}
+
+// Cholesky factor L of the kNB x kNB block in the lower triangle of S by four
+// wavefronts, in blocks of 16: N receives -L below its diagonal blocks, Iv[j]
+// the inverse of diagonal block j.  Each wavefront eliminates the diagonal
+// block by itself in registers, its rows in lanes 0..15 and the rows of the
+// unit matrix in lanes 16..31 (the same steps turn those into the inverse's
+// transpose; a column's elements go to all lanes as scalars).  Columns are
+// scaled by 1/sqrt(pivot) afterwards, and the next pivot is formed beside the
+// row updates, so a column's chain is a reciprocal and two operations.  All
+// wavefronts form the same inverse, so each goes on without waiting for the
+// others; a panel block is formed transposed, which is the operand of its
+// product either way.  True if a pivot was not positive.
+__device__ __forceinline__ bool factor_block(double (*S)[kLS], double (*N)[kLS], double (*Iv)[16][kIS], double (*T)[kIS]) {
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63, r16 = lane & 15, kq = lane >> 4;
     bool neg = false;
+#pragma unroll 1
     for (int j = 0; j < kNB / 16; ++j) {
         const int j0 = 16 * j;
         double row[16];
@@ -256,37 +280,56 @@ __device__ __forceinline__ bool factor_block(double (*S)[kLS], double (*Iv)[16][
             const double v = S[j0 + r16][j0 + c];
             row[c] = lane < 16 ? (c <= r16 ? v : 0.0) : lane < 32 && c == r16 ? 1.0 : 0.0;
         }
+        double pv = lane_value(row[0], 0), mine = 1.0;   // mine: pivot r16
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
-            const double pv = lane_value(row[c], c);
-            neg |= !(pv > 0.0);
-            row[c] *= pv > 0.0 ? rsqrt64(pv) : 1.0;
+            const bool ok = pv > 0.0;
+            neg |= !ok;
+            pv = ok ? pv : 1.0;
+            mine = r16 == c ? pv : mine;
+            const double inv = rcp64(pv);
+            if (c < 15) {
+                const double a = lane_value(row[c], c + 1);
+                pv = fma(-(a * inv), a, lane_value(row[c + 1], c + 1));
+            }
+            const double u = row[c] * inv;
 #pragma unroll
-            for (int e = c + 1; e < 16; ++e) row[e] = fma(-row[c], lane_value(row[c], e), row[e]);
+            for (int e = c + 1; e < 16; ++e) row[e] = fma(-u, lane_value(row[c], e), row[e]);
         }
-        if (wave == 0 && kq == 1) {
+        if (kq == 1) {
 #pragma unroll
-            for (int c = 0; c < 16; ++c) Iv[j][c][r16] = row[c];
+            for (int c = 0; c < 16; ++c) T[c][r16] = row[c];
         }
-        __syncthreads();
-        if (j0 + 16 == kNB) break;
-        const int i = j + 1 + wave;
-        if (i < kNB / 16) {   // block (i, j) of -L
+        wave_sync();
+        const double rs = rsqrt64(mine);
+        double inv[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            inv[k] = T[r16][4 * k + kq] * rs;
+            Iv[j][r16][4 * k + kq] = inv[k];
+        }
+        const auto panel = [&](int b) {   // element (4 v + kq, r16) of block (b, j)'s transpose
             tps_d4 x{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int k = 0; k < 4; ++k) x = mfma64(S[16 * i + r16][j0 + 4 * k + kq], Iv[j][r16][4 * k + kq], x);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) S[16 * i + kq + 4 * v][j0 + r16] = -x[v];
-        }
-        __syncthreads();
+            for (int k = 0; k < 4; ++k) x = mfma64(inv[k], S[16 * b + r16][j0 + 4 * k + kq], x);
+            return x;
+        };
+#pragma unroll 1
         for (int b = wave, bi = j + 1, bk = j + 1;; ++bk) {   // blocks (bi, bk), j < bk <= bi, every fourth
             if (bk > bi) bk = j + 1, ++bi;
             if (bi == kNB / 16) break;
             if (b-- != 0) continue;
             b = 3;
+            const tps_d4 y = panel(bk);
+            tps_d4 z = y;
+            if (bi != bk) z = panel(bi);
+            else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) N[16 * bk + r16][j0 + 4 * v + kq] = -y[v];
+            }
             tps_d4 x{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int k = 0; k < 4; ++k) x = mfma64(S[16 * bi + r16][j0 + 4 * k + kq], S[16 * bk + r16][j0 + 4 * k + kq], x);
+            for (int k = 0; k < 4; ++k) x = mfma64(z[k], y[k], x);
 #pragma unroll
             for (int v = 0; v < 4; ++v) S[16 * bi + kq + 4 * v][16 * bk + r16] -= x[v];
         }
@@ -295,8 +338,8 @@ __device__ __forceinline__ bool factor_block(double (*S)[kLS], double (*Iv)[16][
     return neg;
 }
 
-// Step kb of the blocked Cholesky M22 = L L^T, one launch: the trailing update
-// by the previous block column (A -= L21 L21^T) and, in the same launch, block
+// Step kb of the blocked Cholesky M22 = L L^T, one launch: the update by the
+// previous `depth` block columns (A -= L21 L21^T) and, in the same launch, block
 // column kb's factor.  M is the reduced system, lower triangle, its row n2 the
 // right-hand side z2, which the steps turn into the forward solve L^-1 z2.
 //   Workgroups 0 .. panels: the block column.  Each updates the diagonal block
@@ -306,65 +349,92 @@ __device__ __forceinline__ bool factor_block(double (*S)[kLS], double (*Iv)[16][
 //     16 x 16 block's result is the next product's operand as it stands.
 //     Workgroup 0 solves the unit matrix instead and stores Ld = L11^-T for
 //     the backward solve.
-//   The others: one tile of the update each, four wavefronts of 32 x 32.
-// The factor runs beside the update of the rest, which is bound by reading and
-// writing the trailing matrix (3.4 TB/s as separate launches of rank 32); with
-// few rows left, by the factor's serial chain of 64 pivots.  A launch for the
-// factor (22 us) and one for the update (26 us) per 32 columns, and two (9 us)
-// for the solves, took 12.0 ms for 5,800 centres; one per 64 columns, and one (5.5 us) for the
-// backward solve, take 4.5 ms.
+//   The others: one tile of the trailing update each, four wavefronts of 32 x 32.
+// The trailing matrix is updated at every second step, by two block columns at
+// once (the steps between update their own block column only): 118 us at 5,700
+// rows, where two updates by one take 88 each.  It costs as much in matrix
+// instructions (59 us) as in reading and writing that matrix (57 us), and the
+// two overlap little.  A step without it is the factor's serial chain (14 of
+// 25 us).  5,754 centres: a launch for the factor (22 us) and one for the
+// update (26 us) per 32 columns, and two (9 us) for the solves, took 12.0 ms;
+// a launch per 64 columns (a square root and a division in each column's chain)
+// and one (5.5 us) for the backward solve 4.5 ms; this 4.2 ms.  Giving each
+// XCD a compact part of the tiles changes nothing.
 // A pivot <= 0 raises *bad.
-__global__ __launch_bounds__(256, 2) void k_chol_step(int64_t n, int64_t kb, int bs, int64_t n2, int panels,
+__global__ __launch_bounds__(256, 2) void k_chol_step(int64_t ld, int64_t kb, int bs, int64_t n2, int panels, int depth,
                                                       double* __restrict__ M, double* __restrict__ Ld,
                                                       int* __restrict__ bad) {
     __shared__ double Xi[kNB][kLS], Xk[kNB][kLS];
-    __shared__ double Iv[kNB / 16][16][kIS];
+    __shared__ double Iv[kNB / 16][16][kIS], T[16][kIS];
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63, r16 = lane & 15, kq = lane >> 4;
     const int64_t rows = n2 + 1;
+    double vi[kTileIt], vk[kTileIt];   // the next block column's tiles, in flight during a product
     if (static_cast<int>(blockIdx.x) > panels) {
         // workgroup b -> lower-triangle tile (ti, tk), tk <= ti, b = ti (ti + 1) / 2 + tk
         const int64_t b = static_cast<int64_t>(blockIdx.x) - panels - 1;
-        int64_t ti = static_cast<int64_t>((sqrt(8.0 * static_cast<double>(b) + 1.0) - 1.0) * 0.5);
+        int ti = __builtin_amdgcn_readfirstlane(static_cast<int>((sqrt(8.0 * static_cast<double>(b) + 1.0) - 1.0) * 0.5));
         while (ti * (ti + 1) / 2 > b) --ti;
         while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
         const int64_t i0 = kb + kNB + ti * kNB, k0 = kb + kNB + (b - ti * (ti + 1) / 2) * kNB;
         const int rb = (wave >> 1) * 32, cb = (wave & 1) * 32;
-        double old[2][2][4];   // in flight during the products
+        // element v of block (p, q) of the wavefront's quarter: row 16 p + 4 v + rb + kq, column 16 q + cb + r16
+        double* tile = M + i0 * ld + k0;
+        const uint32_t off = static_cast<uint32_t>((rb + kq) * static_cast<int>(ld) + cb + r16);
+        const auto inside = [&](int p, int q, int v) {
+            const int i = rb + kq + 16 * p + 4 * v, k = cb + r16 + 16 * q;
+            return i0 + i < rows && k0 + k < n2 && k0 + k <= i0 + i;
+        };
+        load_tile(M, ld, i0, rows, kb - depth * kNB, vi);
+        load_tile(M, ld, k0, rows, kb - depth * kNB, vk);
+        const bool whole = i0 + kNB <= rows && k0 + kNB <= n2 && k0 < i0;
+        double old[2][2][4];
+        const auto load_old = [&](auto in) {
 #pragma unroll
-        for (int p = 0; p < 2; ++p)
+            for (int p = 0; p < 2; ++p)
 #pragma unroll
-            for (int q = 0; q < 2; ++q)
+                for (int q = 0; q < 2; ++q)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int64_t i = i0 + rb + 16 * p + kq + 4 * v, k = k0 + cb + 16 * q + r16;
-                    old[p][q][v] = i < rows && k <= i && k < n2 ? M[i * n + k] : 0.0;
-                }
-        stage_tile(M, n, i0, rows, kb - kNB, Xi);
-        stage_tile(M, n, k0, rows, kb - kNB, Xk);
-        __syncthreads();
+                    for (int v = 0; v < 4; ++v) old[p][q][v] = in(p, q, v) ? (tile + (16 * p + 4 * v) * ld + 16 * q)[off] : 0.0;
+        };
+        const auto all = [](int, int, int) { return true; };
+        if (whole) load_old(all);
+        else load_old(inside);
         tps_d4 acc[2][2];
 #pragma unroll
         for (int p = 0; p < 2; ++p)
 #pragma unroll
             for (int q = 0; q < 2; ++q) acc[p][q] = tps_d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+        for (int back = depth; back > 0; --back) {
+            if (back < depth) __syncthreads();
+            store_tile(vi, Xi);
+            store_tile(vk, Xk);
+            __syncthreads();
+            if (back > 1) {
+                load_tile(M, ld, i0, rows, kb - (back - 1) * kNB, vi);
+                load_tile(M, ld, k0, rows, kb - (back - 1) * kNB, vk);
+            }
 #pragma unroll
-        for (int c0 = 0; c0 < kNB; c0 += 4) {
-            const double x0 = Xi[rb + r16][c0 + kq], x1 = Xi[rb + 16 + r16][c0 + kq];
-            const double y0 = Xk[cb + r16][c0 + kq], y1 = Xk[cb + 16 + r16][c0 + kq];
-            acc[0][0] = mfma64(x0, y0, acc[0][0]);
-            acc[0][1] = mfma64(x0, y1, acc[0][1]);
-            acc[1][0] = mfma64(x1, y0, acc[1][0]);
-            acc[1][1] = mfma64(x1, y1, acc[1][1]);
+            for (int c0 = 0; c0 < kNB; c0 += 4) {
+                const double x0 = Xi[rb + r16][c0 + kq], x1 = Xi[rb + 16 + r16][c0 + kq];
+                const double y0 = Xk[cb + r16][c0 + kq], y1 = Xk[cb + 16 + r16][c0 + kq];
+                acc[0][0] = mfma64(x0, y0, acc[0][0]);
+                acc[0][1] = mfma64(x0, y1, acc[0][1]);
+                acc[1][0] = mfma64(x1, y0, acc[1][0]);
+                acc[1][1] = mfma64(x1, y1, acc[1][1]);
+            }
         }
+        const auto store = [&](auto in) {
 #pragma unroll
-        for (int p = 0; p < 2; ++p)
+            for (int p = 0; p < 2; ++p)
 #pragma unroll
-            for (int q = 0; q < 2; ++q)
+                for (int q = 0; q < 2; ++q)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int64_t i = i0 + rb + 16 * p + kq + 4 * v, k = k0 + cb + 16 * q + r16;
-                    if (i < rows && k <= i && k < n2) M[i * n + k] = old[p][q][v] - acc[p][q][v];
-                }
+                    for (int v = 0; v < 4; ++v)
+                        if (in(p, q, v)) (tile + (16 * p + 4 * v) * ld + 16 * q)[off] = old[p][q][v] - acc[p][q][v];
+        };
+        if (whole) store(all);
+        else store(inside);
         return;
     }
     const bool unit = blockIdx.x == 0;
@@ -378,36 +448,63 @@ __global__ __launch_bounds__(256, 2) void k_chol_step(int64_t n, int64_t kb, int
         const int b = min(4 * q + wave, 9);
         bi[q] = b < 1 ? 0 : b < 3 ? 1 : b < 6 ? 2 : 3;
         bk[q] = b - bi[q] * (bi[q] + 1) / 2;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int i = 16 * bi[q] + kq + 4 * v, k = 16 * bk[q] + r16;
-            diag[q][v] = i < bs && k < bs ? (k <= i ? M[(kb + i) * n + kb + k] : 0.0) : i == k ? 1.0 : 0.0;
-        }
     }
+    double own[16];
+    const auto load_block = [&](auto in, auto below) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = 16 * bi[q] + kq + 4 * v, k = 16 * bk[q] + r16;
+                diag[q][v] = in(i, k) ? M[(kb + i) * ld + kb + k] : i == k ? 1.0 : 0.0;
+            }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {   // the wavefront's rows, a row at a time
+            const int i = 16 * wave + r;
+            own[r] = below(i, lane) ? M[(r0 + i) * ld + kb + lane] : unit && i == lane ? 1.0 : 0.0;
+        }
+    };
+    const bool whole = bs == kNB && r0 + kNB <= rows && !unit;
+    const auto all = [](int, int) { return true; };
+    if (whole)   // with the diagonal blocks' upper elements, which factor_block leaves out
+        load_block(all, all);
+    else
+        load_block([&](int i, int k) { return i < bs && k < bs; },
+                   [&](int i, int k) { return !unit && r0 + i < rows && k < bs; });
+    if (depth > 0) {
+        if (!unit) load_tile(M, ld, r0, rows, kb - depth * kNB, vi);
+        load_tile(M, ld, kb, kb + bs, kb - depth * kNB, vk);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) Xi[16 * wave + r][lane] = own[r];
+    wave_sync();
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int k = 16 * q + kq + 4 * v, i = 16 * wave + r16;
-            x[q][v] = unit ? (i == k ? 1.0 : 0.0) : r0 + i < rows && k < bs ? M[(r0 + i) * n + kb + k] : 0.0;
+        for (int v = 0; v < 4; ++v) x[q][v] = Xi[16 * wave + r16][16 * q + kq + 4 * v];
+    __syncthreads();
+#pragma unroll 1
+    for (int back = depth; back > 0; --back) {
+        if (back < depth) {
+            if (!unit) load_tile(M, ld, r0, rows, kb - back * kNB, vi);
+            load_tile(M, ld, kb, kb + bs, kb - back * kNB, vk);
         }
-    if (kb > 0) {
-        if (!unit) stage_tile(M, n, r0, rows, kb - kNB, Xi);
-        stage_tile(M, n, kb, kb + bs, kb - kNB, Xk);
+        if (!unit) store_tile(vi, Xi);
+        store_tile(vk, Xk);
         __syncthreads();
-#pragma unroll
+#pragma unroll 4
         for (int c0 = 0; c0 < kNB; c0 += 4)
 #pragma unroll
             for (int q = 0; q < 3; ++q) diag[q] = mfma64(-Xk[16 * bi[q] + r16][c0 + kq], Xk[16 * bk[q] + r16][c0 + kq], diag[q]);
         if (!unit) {
-#pragma unroll
+#pragma unroll 4
             for (int c0 = 0; c0 < kNB; c0 += 4) {
                 const double y = Xi[16 * wave + r16][c0 + kq];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) x[q] = mfma64(-Xk[16 * q + r16][c0 + kq], y, x[q]);
             }
         }
-        __syncthreads();   // Xk becomes the diagonal block
+        __syncthreads();   // Xk takes the next block column, at the end the diagonal block
     }
 #pragma unroll
     for (int q = 0; q < 3; ++q)
@@ -415,28 +512,29 @@ __global__ __launch_bounds__(256, 2) void k_chol_step(int64_t n, int64_t kb, int
         for (int v = 0; v < 4; ++v)   // the tenth block comes from waves 1..3 alike
             Xk[16 * bi[q] + kq + 4 * v][16 * bk[q] + r16] = diag[q][v];
     __syncthreads();
-    const bool neg = factor_block(Xk, Iv);
+    const bool neg = factor_block(Xk, Xi, Iv, T);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
 #pragma unroll
         for (int e = 0; e < q; ++e)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) x[q] = mfma64(Xk[16 * q + r16][16 * e + 4 * k + kq], x[e][k], x[q]);
+            for (int k = 0; k < 4; ++k) x[q] = mfma64(Xi[16 * q + r16][16 * e + 4 * k + kq], x[e][k], x[q]);
         tps_d4 y{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int k = 0; k < 4; ++k) y = mfma64(Iv[q][r16][4 * k + kq], x[q][k], y);
         x[q] = y;
     }
-    const int i = 16 * wave + r16;
-    double* to = unit ? Ld + (kb + i) * kNB : M + (r0 + i) * n + kb;
-    if (unit || r0 + i < rows)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int k = 16 * q + kq + 4 * v;
-                if (unit || k < bs) to[k] = x[q][v];
-            }
+        for (int v = 0; v < 4; ++v) Xk[16 * wave + r16][16 * q + kq + 4 * v] = x[q][v];
+    wave_sync();
+    double* to = unit ? Ld + kb * kNB + lane : M + r0 * ld + kb + lane;
+    const int64_t stride = unit ? kNB : ld;
+    const int left = unit || whole ? kNB : static_cast<int>(min<int64_t>(rows - r0, kNB));
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        if (16 * wave + r < left && (unit || lane < bs)) to[(16 * wave + r) * stride] = Xk[16 * wave + r][lane];
     if (unit && t == 0 && neg) *bad = 1;
 }
 
@@ -461,7 +559,7 @@ __global__ __launch_bounds__(1024) void k_tps_qty(int64_t n, int np, const doubl
 // it, and each subtracts L[kb ..][r]^T w from kNB of the rows r above (sixteen
 // block rows a wavefront, loaded before w is formed).  The block's own
 // elements of t are only read.
-__global__ __launch_bounds__(256) void k_back_step(int64_t n, int64_t kb, int bs, const double* __restrict__ M,
+__global__ __launch_bounds__(256) void k_back_step(int64_t ld, int64_t kb, int bs, const double* __restrict__ M,
                                                    const double* __restrict__ Ld, double* __restrict__ tv,
                                                    double* __restrict__ w) {
     __shared__ double wb[kNB];
@@ -470,7 +568,7 @@ __global__ __launch_bounds__(256) void k_back_step(int64_t n, int64_t kb, int bs
     const int64_t r = static_cast<int64_t>(blockIdx.x) * kNB + lane;
     double l[16];
 #pragma unroll
-    for (int c = 0; c < 16; ++c) l[c] = r < kb && 16 * wave + c < bs ? M[(kb + 16 * wave + c) * n + r] : 0.0;
+    for (int c = 0; c < 16; ++c) l[c] = r < kb && 16 * wave + c < bs ? M[(kb + 16 * wave + c) * ld + r] : 0.0;
     const int row = t >> 2, q = t & 3;
     double s = 0.0;
 #pragma unroll
@@ -495,7 +593,7 @@ __global__ __launch_bounds__(256) void k_back_step(int64_t n, int64_t kb, int bs
 
 // c = Q [0; w] = H_0 ... H_d [0; w] and R a = z1 - M12 w; writes c and a into
 // the fit (one workgroup).
-__global__ __launch_bounds__(1024) void k_tps_coeffs(int64_t n, int np, const double* __restrict__ A,
+__global__ __launch_bounds__(1024) void k_tps_coeffs(int64_t n, int64_t ld, int np, const double* __restrict__ A,
                                                      const double* __restrict__ V, const double* __restrict__ tau,
                                                      const double* __restrict__ R, const double* __restrict__ z,
                                                      const double* __restrict__ w, double* __restrict__ c,
@@ -505,7 +603,7 @@ __global__ __launch_bounds__(1024) void k_tps_coeffs(int64_t n, int np, const do
     const int t = threadIdx.x;
     for (int k = 0; k < np; ++k) {   // z1_k - sum_j M[k][np + j] w_j
         double s = 0.0;
-        for (int64_t j = np + t; j < n; j += blockDim.x) s = fma(A[k * n + j], w[j - np], s);
+        for (int64_t j = np + t; j < n; j += blockDim.x) s = fma(A[k * ld + j], w[j - np], s);
         s = block_sum(s, red);
         if (t == 0) rhs[k] = z[k] - s;
     }
@@ -638,10 +736,10 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
     const int d = P.d, np = d + 1;
     const int64_t G = P.G;
     TpsFitResult res{kTpsOk, 0, hipSuccess};
-    int64_t n = 0, n2 = 0;
+    int64_t n = 0, n2 = 0, ld = 0;
     int bad = 0;
     char* small = nullptr;   // idx [G], n, bad flag; tau, R, kappa
-    double* big = nullptr;   // A [n n], z [n] as its row n, V and P [n (d + 1)], y, p, w [n], Ld
+    double* big = nullptr;   // A [n ld], z [n] as its row n, V and P [n (d + 1)], y, p, w [n], Ld
     double* fitmem = nullptr;
     int64_t* d_idx = nullptr;
     int64_t* d_n = nullptr;
@@ -674,16 +772,19 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
     }
     {
         const size_t nn = static_cast<size_t>(n);
-        const size_t big_count = nn * nn + 2 * nn * np + 4 * nn + kNB * (nn + kNB);
+        // the reduced system's rows begin on a cache line: row stride and first column in 16 doubles
+        ld = (n + 15) / 16 * 16;
+        const size_t lead = 16 - np, full = static_cast<size_t>(ld);
+        const size_t big_count = lead + (nn + 1) * full + 2 * nn * np + 3 * nn + kNB * (nn + kNB);
         if (hipMalloc(&big, sizeof(double) * big_count) != hipSuccess ||
             hipMalloc(&fitmem, sizeof(double) * (nn * d + nn + np)) != hipSuccess) {
             (void)hipGetLastError();
             res.code = kTpsNoMem;
             goto done;
         }
-        A = big;
-        z = A + nn * nn;
-        V = z + nn;
+        A = big + lead;
+        z = A + nn * full;
+        V = z + full;
         Pm = V + nn * np;
         y = Pm + nn * np;
         pv = y + nn;
@@ -698,38 +799,40 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
     TPS_TRY(hipGetLastError());
     {
         const dim3 grid(static_cast<unsigned>((n + 255) / 256), static_cast<unsigned>(n));
-        if (d == 1) hipLaunchKernelGGL(k_tps_matrix<1>, grid, dim3(256), 0, s, n, U, lam, A);
-        else if (d == 2) hipLaunchKernelGGL(k_tps_matrix<2>, grid, dim3(256), 0, s, n, U, lam, A);
-        else hipLaunchKernelGGL(k_tps_matrix<3>, grid, dim3(256), 0, s, n, U, lam, A);
+        if (d == 1) hipLaunchKernelGGL(k_tps_matrix<1>, grid, dim3(256), 0, s, n, ld, U, lam, A);
+        else if (d == 2) hipLaunchKernelGGL(k_tps_matrix<2>, grid, dim3(256), 0, s, n, ld, U, lam, A);
+        else hipLaunchKernelGGL(k_tps_matrix<3>, grid, dim3(256), 0, s, n, ld, U, lam, A);
     }
     TPS_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_tps_qr, dim3(1), dim3(1024), 0, s, n, d, Pm, V, d_tau, d_R, d_bad);
     TPS_TRY(hipGetLastError());
     for (int k = 0; k < np; ++k) {   // M = Q^T A Q, one reflector at a time from both sides
-        hipLaunchKernelGGL(k_tps_gemv, dim3(static_cast<unsigned>(n)), dim3(256), 0, s, n, np, k, A, V, d_tau, pv);
+        hipLaunchKernelGGL(k_tps_gemv, dim3(static_cast<unsigned>(n)), dim3(256), 0, s, n, ld, np, k, A, V, d_tau, pv);
         hipLaunchKernelGGL(k_tps_kappa, dim3(1), dim3(1024), 0, s, n, np, k, V, d_tau, pv, d_kappa);
         hipLaunchKernelGGL(k_tps_rank2, dim3(static_cast<unsigned>((n + 255) / 256), static_cast<unsigned>(n)),
-                           dim3(256), 0, s, n, np, k, V, pv, d_kappa, A);
+                           dim3(256), 0, s, n, ld, np, k, V, pv, d_kappa, A);
         TPS_TRY(hipGetLastError());
     }
     hipLaunchKernelGGL(k_tps_qty, dim3(1), dim3(1024), 0, s, n, np, V, d_tau, y, z);
     TPS_TRY(hipGetLastError());
     n2 = n - np;
-    M = A + np * n + np;   // the reduced system, row stride n; its row n2 is z2
+    M = A + np * ld + np;   // the reduced system; its row n2 is z2
     for (int64_t kb = 0; kb < n2; kb += kNB) {   // M22 = L L^T, L t = z2
         const int bs = static_cast<int>(std::min<int64_t>(kNB, n2 - kb));
         const int64_t panels = (n2 + 1 - kb - bs + kNB - 1) / kNB;
-        const int64_t tiles = kb > 0 && kb + kNB < n2 ? (n2 + 1 - kb - kNB + kNB - 1) / kNB : 0;
+        const int64_t step = kb / kNB;
+        const int depth = step == 0 ? 0 : step % 2 == 0 ? 2 : 1;
+        const int64_t tiles = depth == 2 && kb + kNB < n2 ? (n2 + 1 - kb - kNB + kNB - 1) / kNB : 0;
         hipLaunchKernelGGL(k_chol_step, dim3(static_cast<unsigned>(1 + panels + tiles * (tiles + 1) / 2)), dim3(256), 0,
-                           s, n, kb, bs, n2, static_cast<int>(panels), M, Ld, d_bad);
+                           s, ld, kb, bs, n2, static_cast<int>(panels), depth, M, Ld, d_bad);
         TPS_TRY(hipGetLastError());
     }
     for (int64_t kb = ((n2 - 1) / kNB) * kNB; kb >= 0; kb -= kNB) {   // L^T w = t
         const int bs = static_cast<int>(std::min<int64_t>(kNB, n2 - kb));
-        hipLaunchKernelGGL(k_back_step, dim3(static_cast<unsigned>(std::max<int64_t>(1, kb / kNB))), dim3(256), 0, s, n,
+        hipLaunchKernelGGL(k_back_step, dim3(static_cast<unsigned>(std::max<int64_t>(1, kb / kNB))), dim3(256), 0, s, ld,
                            kb, bs, M, Ld, z + np, w);
     }
-    hipLaunchKernelGGL(k_tps_coeffs, dim3(1), dim3(1024), 0, s, n, np, A, V, d_tau, d_R, z, w, c, a);
+    hipLaunchKernelGGL(k_tps_coeffs, dim3(1), dim3(1024), 0, s, n, ld, np, A, V, d_tau, d_R, z, w, c, a);
     TPS_TRY(hipGetLastError());
     TPS_TRY(hipMemcpyAsync(&bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, s));
     TPS_TRY(hipStreamSynchronize(s));
