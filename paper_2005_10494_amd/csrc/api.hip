@@ -318,6 +318,18 @@ bmd_status ensure(void** buf, size_t* cap, size_t need) {
     return BMD_OK;
 }
 
+// The problem's host memory for results (allocated once): a kernel that writes
+// there spares the copy a small result took (4 us of device time and the
+// round trip of a copy to pageable memory, twice for a best design).
+bmd_status ensure_readback(bmd_problem* p) {
+    if (p->h_read) return BMD_OK;
+    const hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&p->h_read), sizeof(double) * kReadback, hipHostMallocDefault);
+    if (e == hipSuccess) return BMD_OK;
+    p->h_read = nullptr;
+    (void)hipGetLastError();
+    return fail(BMD_ENOMEM, "readback memory: %s", hipGetErrorString(e));
+}
+
 template <typename T>
 bmd_status upload(T** dst, const T* src, size_t n) {
     hipError_t e = hipMalloc(dst, sizeof(T) * std::max<size_t>(n, 1));
@@ -355,6 +367,7 @@ void free_problem(bmd_problem* p) {
     f(p->d_Wf);
     f(p->d_ws);
     f(p->d_ws2);
+    if (p->h_read) (void)hipHostFree(p->h_read);
     tps_release(p);
     for (auto& e : p->ev)
         if (e) (void)hipEventDestroy(e);
@@ -367,6 +380,12 @@ bool valid_prec(int32_t prec) { return prec == BMD_FP64 || prec == BMD_FP32_COMP
 // workgroups, so the partly filled last round costs little; slices of at
 // least 64 draws, whole draw chunks of the matrix-core sweep, and for that
 // sweep no more staged draw bytes per slice than the problem's slice budget.
+// Calls that slices of 64 draws would leave with fewer than two workgroups a
+// compute unit take slices of down to 16 (201 designs x 10,000 draws FP64, one
+// workgroup of designs: the call 207 -> 101 us with
+// the shared reduction and readback; below 16 a slice's design
+// constants, formed by every workgroup, outweigh its draws), as long as the
+// workspace stays within the scratch of a call without allocation.
 void sweep_slices(bmd_problem* p, int prec, int64_t M, int64_t* n_slices_out, int64_t* slice_len_out) {
     const int64_t bx = sweep_tiles(p, prec);
     if (p->sweep_bpc[prec] == 0) p->sweep_bpc[prec] = sweep_blocks_per_cu(p, prec);
@@ -378,7 +397,13 @@ void sweep_slices(bmd_problem* p, int prec, int64_t M, int64_t* n_slices_out, in
         const int64_t len = std::max<int64_t>(chunk, p->slice_bytes / per_draw / chunk * chunk);
         n_slices = std::max<int64_t>(n_slices, (M + len - 1) / len);
     }
-    n_slices = std::max<int64_t>(1, std::min<int64_t>({n_slices, (M + 63) / 64, 65535}));
+    int64_t least = 64;
+    const auto few = [&](int64_t len) { return bx * ((M + len - 1) / len) < 2 * p->n_cu; };
+    while (least > 16 && few(least)) least /= 2;
+    if (least < 64 && draw_workspace_bytes(p, prec, M) + 16 * static_cast<size_t>(p->P.G) * (M / least + 1) >
+                          BMD_NOALLOC_SCRATCH_BYTES / 2)
+        least = 64;
+    n_slices = std::max<int64_t>(1, std::min<int64_t>({n_slices, (M + least - 1) / least, 65535}));
     int64_t slice_len = (M + n_slices - 1) / n_slices;
     slice_len = (slice_len + chunk - 1) / chunk * chunk;
     *n_slices_out = (M + slice_len - 1) / slice_len;
@@ -967,17 +992,17 @@ bmd_status bmd_argmax(bmd_problem* p, const double* d_surface, int64_t* h_index,
     const int64_t n = p->P.G;
     const int n_part = static_cast<int>(std::min<int64_t>(1024, (n + 255) / 256));
     bmd_status st = ensure(&p->d_ws2, &p->ws2_cap, std::max<size_t>(sizeof(double) * n, 16 * 1024 + 256));
+    if (st == BMD_OK) st = ensure_readback(p);
     if (st != BMD_OK) return st;
     double* pv = static_cast<double*>(p->d_ws2);
     int64_t* pi = reinterpret_cast<int64_t*>(static_cast<char*>(p->d_ws2) + 8 * 1024);
     mark(p, 8, s);
-    HIP_TRY(launch_argmax(p, d_surface, n, pv, pi, n_part, s), "argmax kernels");
+    int64_t* h_i = reinterpret_cast<int64_t*>(p->h_read + 1);
+    HIP_TRY(launch_argmax(d_surface, n, pv, pi, n_part, p->h_read, h_i, s), "argmax kernels");
     mark(p, 9, s);
-    double v;
-    int64_t i;
-    HIP_TRY(hipMemcpyAsync(&v, pv, sizeof v, hipMemcpyDeviceToHost, s), "argmax readback");
-    HIP_TRY(hipMemcpyAsync(&i, pi, sizeof i, hipMemcpyDeviceToHost, s), "argmax readback");
     HIP_TRY(hipStreamSynchronize(s), "argmax sync");
+    double v = p->h_read[0];
+    int64_t i = *h_i;
     if (i == INT64_MAX) {
         i = 0;
         v = NAN;
@@ -1358,19 +1383,18 @@ bmd_status tune_phase(bmd_problem* const* ps, std::vector<BatchPlan> pl, int pre
 bmd_status smoothed_at(bmd_problem* p, const double* d_surface, const double* q, double* S, double* g, double* H,
                        hipStream_t s) {
     const int d = p->P.d;
-    bmd_status st = ensure(&p->d_ws2, &p->ws2_cap, smooth_local_bytes() + 2 * kMaxDim * kMaxDim * sizeof(double) + 1024);
+    bmd_status st = ensure(&p->d_ws2, &p->ws2_cap, smooth_local_bytes());
+    if (st == BMD_OK) st = ensure_readback(p);
     if (st != BMD_OK) return st;
     double lo[kMaxDim], hi[kMaxDim];
     for (int j = 0; j < d; ++j) axis_range(p->desc, j, &lo[j], &hi[j]);
     double* ws = static_cast<double*>(p->d_ws2);
-    double* out = ws + smooth_local_bytes() / sizeof(double);
-    HIP_TRY(launch_smooth_local(p, d_surface, q, lo, hi, ws, out, s), "smoothing at a point");
+    HIP_TRY(launch_smooth_local(p, d_surface, q, lo, hi, ws, p->h_read, s), "smoothing at a point");
     const int na = 1 + d + d * (d + 1) / 2;
-    double acc[2 * (1 + kMaxDim + kMaxDim * (kMaxDim + 1) / 2)];
-    HIP_TRY(hipMemcpyAsync(acc, out, sizeof(double) * 2 * na, hipMemcpyDeviceToHost, s), "smoothing readback");
+    static_assert(2 * (1 + kMaxDim + kMaxDim * (kMaxDim + 1) / 2) <= kReadback, "readback memory");
     HIP_TRY(hipStreamSynchronize(s), "smoothing sync");
-    const double* F = acc;
-    const double* W = acc + na;
+    const double* F = p->h_read;
+    const double* W = F + na;
     if (!(W[0] > 0.0)) return fail(BMD_ERANGE, "no design with a value carries weight at this point");
     double Nj[kMaxDim], Dj[kMaxDim], Njl[kMaxDim][kMaxDim], Djl[kMaxDim][kMaxDim];
     int k = 1 + d;
@@ -1611,10 +1635,10 @@ bmd_status tps_at_design(bmd_problem* p, const double* q, double* S, double* g, 
         w[j] = hi - lo;
         u[j] = (q[j] - lo) / w[j];
     }
-    bmd_status st = ensure(&p->d_ws2, &p->ws2_cap, 16 * sizeof(double));
+    const bmd_status st = ensure_readback(p);
     if (st != BMD_OK) return st;
-    double h[16];
-    const hipError_t e = tps_at_unit(p, u, static_cast<double*>(p->d_ws2), h, s);
+    const double* h = p->h_read;
+    const hipError_t e = tps_at_unit(p, u, p->h_read, s);
     if (e != hipSuccess) return fail(BMD_EDEVICE, "thin-plate spline at a point: %s", hipGetErrorString(e));
     *S = h[0];
     int k = 1 + d;

@@ -15,6 +15,7 @@ constexpr int kMaxGH = 128;          // Gauss-Hermite nodes, upper bound
 constexpr int kPrecomputeGH = 128;   // nodes for the per-design subgroup fraction r
 constexpr int kGLTable = 200;        // packed Gauss-Legendre rules n = 4..24
 constexpr int kEvalBlock = 256;      // designs per workgroup in the eval kernels
+constexpr int kReadback = 64;        // doubles of a problem's readback memory
 constexpr int kSweepRounds = 8;      // rounds of resident workgroups a grid sweep is sliced into
 // Staged draw bytes (node tables, drift quads, thresholds) of one matrix-core
 // sweep slice, at most: the resident workgroups of a slice start at different
@@ -136,6 +137,7 @@ struct bmd_problem {
     size_t ws_cap = 0;
     void* d_ws2 = nullptr;           // second workspace (smoothing ping-pong, argmax partials)
     size_t ws2_cap = 0;
+    double* h_read = nullptr;        // kReadback doubles of host memory that kernels write results to
     std::vector<double> gh_host[2];  // host copies of the eval GH rules
     bool force_direct = false;      // BMD_SWEEP=direct: use the direct sweep everywhere
     int64_t slice_bytes = bmd::kSliceBytes;   // staged draw bytes per matrix-core sweep slice (0: no limit)
@@ -180,8 +182,8 @@ struct TpsFitResult {
 };
 TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double* d_out, hipStream_t s);
 // Value, gradient and Hessian (rows j <= l) of the fit in unit-box coordinates
-// u: h_out [1 + d + d (d + 1) / 2]; d_scratch holds 16 doubles.  Synchronises s.
-hipError_t tps_at_unit(const bmd_problem* p, const double* u, double* d_scratch, double* h_out, hipStream_t s);
+// u: h_out [1 + d + d (d + 1) / 2], host memory the device can write.  Synchronises s.
+hipError_t tps_at_unit(const bmd_problem* p, const double* u, double* h_out, hipStream_t s);
 void tps_release(bmd_problem* p);
 int tps_dims(const bmd_problem* p);   // 0 without a fit
 int nested3_blocks_per_cu(int prec);
@@ -241,8 +243,8 @@ hipError_t launch_finalize_dalpha(const bmd_problem* p, int64_t M, const double*
                                   double* mean, double* dmean, hipStream_t s);
 hipError_t launch_smooth(const bmd_problem* p, int prec, const double* in, double* out,
                          double* tmp, hipStream_t s);
-hipError_t launch_argmax(const bmd_problem* p, const double* v, int64_t n, double* part_v,
-                         int64_t* part_i, int n_part, hipStream_t s);
+hipError_t launch_argmax(const double* v, int64_t n, double* part_v, int64_t* part_i, int n_part, double* out_v,
+                         int64_t* out_i, hipStream_t s);
 // The smoothed surface's numerator and denominator sums with their first and
 // second derivatives at the continuous design q (axis ranges lo, hi): out gets
 // 2 (1 + d + d (d + 1) / 2) FP64 values (kernels_post.hip); ws holds

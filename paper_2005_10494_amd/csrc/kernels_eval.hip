@@ -48,20 +48,65 @@ __global__ __launch_bounds__(kEvalBlock) void k_eval_mfma_da(EvalArgs<T> a, Mfma
     mfma_tile_body<T, D, NMAX, kDAlpha>(a, geo, sweep_tile(), blockIdx.y, lds, cells);
 }
 
-// mean = sums / M in slice order; second: nothing (mode 0), the sample
-// variance from the sums of squares (1), the second sums / M (2).
-__global__ void k_finalize(int64_t G, int64_t M, int n_slices, const double* __restrict__ part,
-                           double* __restrict__ mean, double* __restrict__ second, int mode) {
-    const int64_t g = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (g >= G) return;
+// Sum of x[first], x[first + step], ... below n (elements `stride` apart), in
+// order, eight loads in flight.
+__device__ __forceinline__ double strided_sum(const double* __restrict__ x, int64_t stride, int first, int step, int n) {
+    double s = 0.0;
+    int i = first;
+    for (; i + 7 * step < n; i += 8 * step) {
+        double v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = x[(i + q * step) * stride];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s += v[q];
+    }
+    for (; i < n; i += step) s += x[i * stride];
+    return s;
+}
+
+// mean = sums / M; second: nothing (mode 0), the sample variance from the sums
+// of squares (1), the second sums / M (2).  SPLIT threads share a design, each
+// with every SPLIT-th slice, and their sums are added in order.  Bound for few
+// designs: the latency of one thread's loads one after another (201 designs, 157
+// slices: 37 us), so these take SPLIT = 16.
+template <int SPLIT>
+__global__ __launch_bounds__(256) void k_finalize(int64_t G, int64_t M, int n_slices, const double* __restrict__ part,
+                                                  double* __restrict__ mean, double* __restrict__ second, int mode) {
+    constexpr int W = 256 / SPLIT;   // designs of a workgroup
+    __shared__ double red[2][SPLIT][W];
+    const int at = threadIdx.x % W, own = threadIdx.x / W;
+    const int64_t g = static_cast<int64_t>(blockIdx.x) * W + at;
     double s1 = 0.0, s2 = 0.0;
-    for (int s = 0; s < n_slices; ++s) s1 += part[static_cast<int64_t>(s) * 2 * G + g];
+    if (g < G) {
+        s1 = strided_sum(part + g, 2 * G, own, SPLIT, n_slices);
+        if (mode != 0) s2 = strided_sum(part + G + g, 2 * G, own, SPLIT, n_slices);
+    }
+    if constexpr (SPLIT > 1) {
+        red[0][own][at] = s1;
+        red[1][own][at] = s2;
+        __syncthreads();
+        if (own != 0) return;
+        for (int q = 1; q < SPLIT; ++q) {
+            s1 += red[0][q][at];
+            s2 += red[1][q][at];
+        }
+    }
+    if (g >= G) return;
     const double Md = static_cast<double>(M);
     mean[g] = s1 / Md;
-    if (mode != 0) {
-        for (int s = 0; s < n_slices; ++s) s2 += part[static_cast<int64_t>(s) * 2 * G + G + g];
-        second[g] = mode == 2 ? s2 / Md : M > 1 ? fmax(0.0, (s2 - s1 * s1 / Md) / (Md - 1.0)) : 0.0;
-    }
+    if (mode != 0) second[g] = mode == 2 ? s2 / Md : M > 1 ? fmax(0.0, (s2 - s1 * s1 / Md) / (Md - 1.0)) : 0.0;
+}
+
+// Workgroups of whole designs leave the chip idle below 64 Ki designs; with
+// fewer than 16 slices there is nothing to share.
+void run_finalize(int64_t G, int64_t M, int n_slices, const double* part, double* mean, double* second, int mode,
+                  hipStream_t s) {
+    if (G < 65536 && n_slices >= 16)
+        hipLaunchKernelGGL(k_finalize<16>, dim3(static_cast<unsigned>((G + 15) / 16)), dim3(256), 0, s, G, M, n_slices, part,
+                           mean, second, mode);
+    else
+        hipLaunchKernelGGL(k_finalize<1>, dim3(static_cast<unsigned>((G + 255) / 256)), dim3(256), 0, s, G, M, n_slices, part,
+                           mean, second, mode);
 }
 
 // Prefix/suffix split with the least tile padding (ties: the later split).
@@ -254,17 +299,13 @@ hipError_t launch_eval_mode(const bmd_problem* p, int prec, int64_t M, const voi
 
 hipError_t launch_finalize(const bmd_problem* p, int64_t M, const double* partials, int n_slices, double* mean,
                            double* var, hipStream_t s) {
-    const int64_t G = p->P.G;
-    hipLaunchKernelGGL(k_finalize, dim3(static_cast<unsigned>((G + 255) / 256)), dim3(256), 0, s, G, M, n_slices,
-                       partials, mean, var, var ? 1 : 0);
+    run_finalize(p->P.G, M, n_slices, partials, mean, var, var ? 1 : 0, s);
     return hipGetLastError();
 }
 
 hipError_t launch_finalize_dalpha(const bmd_problem* p, int64_t M, const double* partials, int n_slices, double* mean,
                                   double* dmean, hipStream_t s) {
-    const int64_t G = p->P.G;
-    hipLaunchKernelGGL(k_finalize, dim3(static_cast<unsigned>((G + 255) / 256)), dim3(256), 0, s, G, M, n_slices,
-                       partials, mean, dmean, 2);
+    run_finalize(p->P.G, M, n_slices, partials, mean, dmean, 2, s);
     return hipGetLastError();
 }
 

@@ -59,7 +59,28 @@ __global__ __launch_bounds__(64) void k_smooth_mfma(const T* __restrict__ W, int
         for (int t = 0; t < CT; ++t)
 #pragma unroll
             for (int ib = 0; ib < NI; ++ib) acc[t][ib] = acc_t{0, 0, 0, 0};
-        for (int h0 = 0; h0 < m; h0 += 4) {
+        int h0 = 0;
+        if constexpr (NI * CT == 1) {
+            // few columns: a wavefront's only loads; those of eight steps are in
+            // flight together (the addresses stay inside by the loop's bound and
+            // the clamps; rows and columns past the end are zeroed)
+            constexpr int U = 8;
+            const int i = min(b0 * 16 + r, m - 1);
+            const bool row = b0 * 16 + r < m;
+            for (; h0 + 4 * U <= m; h0 += 4 * U) {
+                T a[U], b[U];
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    const int h = h0 + 4 * q + kq;
+                    a[q] = W[static_cast<int64_t>(i) * m + h];
+                    b[q] = static_cast<T>(in[base[0] + h * inner]);
+                }
+#pragma unroll
+                for (int q = 0; q < U; ++q)
+                    acc[0][0] = mfma_step(row ? a[q] : T(0), valid[0] ? b[q] : T(0), acc[0][0]);
+            }
+        }
+        for (; h0 < m; h0 += 4) {
             const int h = h0 + kq;
             T b[CT];
 #pragma unroll
@@ -250,10 +271,11 @@ __device__ void block_best(double& v, int64_t& i) {
 }
 
 // Stage 1: per-block best of a grid-strided range; NaN counts as -inf.
-__global__ void k_argmax_part(const double* __restrict__ x, int64_t n, double* __restrict__ pv,
-                              int64_t* __restrict__ pi) {
+__global__ __launch_bounds__(1024) void k_argmax_part(const double* __restrict__ x, int64_t n, double* __restrict__ pv,
+                                                      int64_t* __restrict__ pi) {
     double v = -DBL_MAX;
     int64_t i = INT64_MAX;
+#pragma unroll 4
     for (int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; t < n;
          t += static_cast<int64_t>(gridDim.x) * blockDim.x) {
         const double xv = x[t];
@@ -263,15 +285,16 @@ __global__ void k_argmax_part(const double* __restrict__ x, int64_t n, double* _
     if (threadIdx.x == 0) { pv[blockIdx.x] = v; pi[blockIdx.x] = i; }
 }
 
-// Stage 2: one block over the partial results; result in pv[0], pi[0].
-__global__ void k_argmax_final(int n_part, double* __restrict__ pv, int64_t* __restrict__ pi) {
+// Stage 2: one block over the partial results.
+__global__ __launch_bounds__(1024) void k_argmax_final(int n_part, const double* __restrict__ pv,
+                                                       const int64_t* __restrict__ pi, double* __restrict__ out_v,
+                                                       int64_t* __restrict__ out_i) {
     double v = -DBL_MAX;
     int64_t i = INT64_MAX;
     for (int t = threadIdx.x; t < n_part; t += blockDim.x)
         if (better(pv[t], pi[t], v, i)) { v = pv[t]; i = pi[t]; }
     block_best(v, i);
-    __syncthreads();
-    if (threadIdx.x == 0) { pv[0] = v; pi[0] = i; }
+    if (threadIdx.x == 0) { *out_v = v; *out_i = i; }
 }
 
 // Surfaces where some designs have no value (NaN): the smoother over the
@@ -459,13 +482,19 @@ hipError_t launch_smooth_local(const bmd_problem* p, const double* in, const dou
     return hipGetLastError();
 }
 
-hipError_t launch_argmax(const bmd_problem* p, const double* v, int64_t n, double* part_v, int64_t* part_i,
-                         int n_part, hipStream_t s) {
-    (void)p;
+// The result goes to host memory that the device can write.  Up to 16 Ki values
+// one workgroup reads them all (16 loads a thread) and no second launch
+// follows.
+hipError_t launch_argmax(const double* v, int64_t n, double* part_v, int64_t* part_i, int n_part, double* out_v,
+                         int64_t* out_i, hipStream_t s) {
+    if (n <= 16384) {
+        hipLaunchKernelGGL(k_argmax_part, dim3(1), dim3(1024), 0, s, v, n, out_v, out_i);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_argmax_part, dim3(n_part), dim3(256), 0, s, v, n, part_v, part_i);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_argmax_final, dim3(1), dim3(1024), 0, s, n_part, part_v, part_i);
+    hipLaunchKernelGGL(k_argmax_final, dim3(1), dim3(1024), 0, s, n_part, part_v, part_i, out_v, out_i);
     return hipGetLastError();
 }
 

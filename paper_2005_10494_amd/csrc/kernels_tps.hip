@@ -862,19 +862,17 @@ done:
     return res;
 }
 
-hipError_t tps_at_unit(const bmd_problem* p, const double* u, double* d_scratch, double* h_out, hipStream_t s) {
+hipError_t tps_at_unit(const bmd_problem* p, const double* u, double* h_out, hipStream_t s) {
     const TpsFit& F = *p->tps;
     const int d = F.d;
     const double* U = F.mem;
     const double* c = U + F.n * d;
     const double* a = c + F.n;
     const double u1 = d > 1 ? u[1] : 0.0, u2 = d > 2 ? u[2] : 0.0;
-    if (d == 1) hipLaunchKernelGGL(k_tps_at<1>, dim3(1), dim3(1024), 0, s, F.n, U, c, a, u[0], u1, u2, d_scratch);
-    else if (d == 2) hipLaunchKernelGGL(k_tps_at<2>, dim3(1), dim3(1024), 0, s, F.n, U, c, a, u[0], u1, u2, d_scratch);
-    else hipLaunchKernelGGL(k_tps_at<3>, dim3(1), dim3(1024), 0, s, F.n, U, c, a, u[0], u1, u2, d_scratch);
+    if (d == 1) hipLaunchKernelGGL(k_tps_at<1>, dim3(1), dim3(1024), 0, s, F.n, U, c, a, u[0], u1, u2, h_out);
+    else if (d == 2) hipLaunchKernelGGL(k_tps_at<2>, dim3(1), dim3(1024), 0, s, F.n, U, c, a, u[0], u1, u2, h_out);
+    else hipLaunchKernelGGL(k_tps_at<3>, dim3(1), dim3(1024), 0, s, F.n, U, c, a, u[0], u1, u2, h_out);
     hipError_t e = hipGetLastError();
-    const int na = 1 + d + d * (d + 1) / 2;
-    if (e == hipSuccess) e = hipMemcpyAsync(h_out, d_scratch, sizeof(double) * na, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     return e;
 }
