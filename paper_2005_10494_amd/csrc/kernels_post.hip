@@ -242,6 +242,126 @@ void launch_smooth_pass(const T* W, int m, const double* in, double* out, int64_
         launch_smooth_group<T, 2, 16>(W, m, in, out, C, inner, s);
 }
 
+// The last two axes in one pass, FP64: every ma x mb matrix X of the surface (one
+// contiguous block) becomes Wa X Wb^T.  The first product is formed transposed,
+// D[h2][i1] = sum_h1 X[h1][h2] Wa[i1][h1], so that its result registers are the
+// operand of the second, which sums over h2 (element v of lane (kq, r16) is row
+// kq + 4 v, column r16; an operand's element is column r16, inner index kq).
+// N: blocks of 16 of the longer axis.  (FP32 sums would be added in another order.
+// Two axes further up, 16 designs below them at a time through LDS, took as
+// long as their two passes: 55 us.)
+// The weights' operands come from LDS: in registers they left two wavefronts
+// per SIMD.
+template <int N>
+struct PairWeights {
+    static constexpr int kLd = 16 * N + 2;   // an operand read touches every bank twice
+    double (*wa)[kLd];
+    double (*wb)[kLd];
+    int at, kq;
+    __device__ __forceinline__ void fill(const double* __restrict__ Wa, int ma, const double* __restrict__ Wb, int mb) const {
+        for (int e = threadIdx.x; e < 256 * N * N; e += blockDim.x) {
+            const int i = e / (16 * N), h = e % (16 * N);
+            wa[i][h] = i < ma && h < ma ? Wa[i * ma + h] : 0.0;
+            wb[i][h] = i < mb && h < mb ? Wb[i * mb + h] : 0.0;
+        }
+    }
+    __device__ __forceinline__ double a(int n, int s) const { return wa[16 * n + at][4 * s + kq]; }
+    __device__ __forceinline__ double b(int n, int s) const { return wb[16 * n + at][4 * s + kq]; }
+};
+
+// Bound: the matrix cores (24 x 24: 48 products, 20 us of the 24^5 surface) beside
+// memory (27 us).  Wavefronts as many as are resident take matrices in turn, the
+// next one's loads in flight during a matrix's second product.  24^5: the two
+// axes' passes 26.6 + 34.6 us, this 44.
+template <int N>
+__global__ __launch_bounds__(256) void k_smooth_last_pair(const double* __restrict__ Wa, int ma,
+                                                          const double* __restrict__ Wb, int mb,
+                                                          const double* __restrict__ in, double* __restrict__ out,
+                                                          int64_t mats) {
+    const int lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
+    const int64_t step = static_cast<int64_t>(gridDim.x) * 4;
+    int64_t mat = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    __shared__ double wa[16 * N][PairWeights<N>::kLd], wb[16 * N][PairWeights<N>::kLd];
+    const PairWeights<N> w{wa, wb, r16, kq};
+    const int64_t size = static_cast<int64_t>(ma) * mb;
+    // X[s][n]: row 4 s + kq, column 16 n + r16 of the matrix, past its end the last one (no branch
+    // or use between the loads, so that all are in flight)
+    double X[4 * N][N];
+    const auto load = [&](int64_t which) {
+        const double* from = in + which * size;
+#pragma unroll
+        for (int s = 0; s < 4 * N; ++s)
+#pragma unroll
+            for (int n = 0; n < N; ++n) X[s][n] = from[min(4 * s + kq, ma - 1) * mb + min(16 * n + r16, mb - 1)];
+    };
+    load(min<int64_t>(mat, mats - 1));
+    w.fill(Wa, ma, Wb, mb);
+    __syncthreads();
+#pragma unroll 1
+    for (; mat < mats; mat += step) {
+        mfma_d4 d[N][N], e[N][N];
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int j = 0; j < N; ++j) d[i][j] = e[i][j] = mfma_d4{0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < 4 * N; ++s)
+            if (4 * s < ma)   // wave-uniform, as below
+#pragma unroll
+                for (int n = 0; n < N; ++n)
+                    if (16 * n < mb) {
+                        const double x = 4 * s + kq < ma && 16 * n + r16 < mb ? X[s][n] : 0.0;
+#pragma unroll
+                        for (int i = 0; i < N; ++i)
+                            if (16 * i < ma) d[n][i] = mfma_step(x, w.a(i, s), d[n][i]);
+                    }
+        load(min<int64_t>(mat + step, mats - 1));
+#pragma unroll
+        for (int s = 0; s < 4 * N; ++s)
+            if (4 * s < mb)
+#pragma unroll
+                for (int n = 0; n < N; ++n)
+                    if (16 * n < mb) {
+                        const double b = w.b(n, s);
+#pragma unroll
+                        for (int i = 0; i < N; ++i)
+                            if (16 * i < ma) e[i][n] = mfma_step(d[s / 4][i][s % 4], b, e[i][n]);
+                    }
+        double* to = out + mat * size;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int n = 0; n < N; ++n)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int i1 = 16 * i + kq + 4 * v, i2 = 16 * n + r16;
+                    if (i1 < ma && i2 < mb) to[i1 * mb + i2] = e[i][n][v];
+                }
+    }
+}
+
+// Whether the last two axes go in one pass: at most 32 points each (two blocks of
+// 16) and enough matrices to fill the chip.
+bool smooth_in_pair(const DevProblem& P) {
+    if (P.d < 2) return false;
+    const int ma = P.m[P.d - 2], mb = P.m[P.d - 1];
+    return std::max(ma, mb) <= 32 && P.G / (static_cast<int64_t>(ma) * mb) >= 4096;
+}
+
+hipError_t launch_smooth_pair(const bmd_problem* p, const double* in, double* out, hipStream_t s) {
+    const DevProblem& P = p->P;
+    const int j = P.d - 2, ma = P.m[j], mb = P.m[j + 1];
+    const int64_t mats = P.G / (static_cast<int64_t>(ma) * mb);
+    const double* Wa = p->d_W + p->w_off[j];
+    const double* Wb = p->d_W + p->w_off[j + 1];
+    const bool one = std::max(ma, mb) <= 16;
+    const int64_t resident = static_cast<int64_t>(p->n_cu) * (one ? 8 : 3);
+    const dim3 grid(static_cast<unsigned>(std::min((mats + 3) / 4, resident)));
+    if (one) hipLaunchKernelGGL(k_smooth_last_pair<1>, grid, dim3(256), 0, s, Wa, ma, Wb, mb, in, out, mats);
+    else hipLaunchKernelGGL(k_smooth_last_pair<2>, grid, dim3(256), 0, s, Wa, ma, Wb, mb, in, out, mats);
+    return hipGetLastError();
+}
+
 __device__ __forceinline__ bool better(double va, int64_t ia, double vb, int64_t ib) {
     return va > vb || (va == vb && ia < ib);
 }
@@ -434,17 +554,22 @@ hipError_t launch_smooth(const bmd_problem* p, int prec, const double* in, doubl
                          hipStream_t s) {
     const int d = p->P.d;
     const int64_t G = p->P.G;
+    const bool pair = prec == BMD_FP64 && smooth_in_pair(p->P);   // the last two axes in one pass
+    int left = pair ? d - 1 : d;
     const double* src = in;
-    for (int j = 0; j < d; ++j) {
-        double* dst = ((d - 1 - j) % 2 == 0) ? out : tmp;
+    for (int j = 0; left > 0; ++j) {
+        double* dst = --left % 2 == 0 ? out : tmp;
         const int m = p->P.m[j];
         const int64_t inner = p->P.stride[j];
         const int64_t C = G / m;   // columns: every (outer, inner) pair of axis j
-        if (prec == BMD_FP64)
+        hipError_t e = hipSuccess;
+        if (pair && left == 0)
+            e = launch_smooth_pair(p, src, dst, s);
+        else if (prec == BMD_FP64)
             launch_smooth_pass<double>(p->d_W + p->w_off[j], m, src, dst, C, inner, s);
         else
             launch_smooth_pass<float>(p->d_Wf + p->w_off[j], m, src, dst, C, inner, s);
-        const hipError_t e = hipGetLastError();
+        if (e == hipSuccess) e = hipGetLastError();
         if (e != hipSuccess) return e;
         src = dst;
     }
