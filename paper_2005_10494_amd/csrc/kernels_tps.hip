@@ -25,8 +25,11 @@ struct TpsFit {
 
 namespace {
 
+constexpr int kMaxTpsDim = 3;
 constexpr int kNB = 64;          // Cholesky and triangular-solve block, and the update's output tile
 constexpr int kLS = kNB + 2;     // LDS row stride of a tile: a 16 x 4 operand read touches every bank twice
+constexpr int kHalf = kNB / 2;   // columns staged at a time
+constexpr int kHS = kHalf + 2;   // their LDS row stride (as kLS)
 constexpr int kIS = 18;          // LDS row stride of a 16 x 16 inverse
 
 // The radial function for D dimensions, fixed at compile time: with the
@@ -35,10 +38,10 @@ constexpr int kIS = 18;          // LDS row stride of a 16 x 16 inverse
 // square root (NaN at r = 0), so every kernel that evaluates phi is a
 // template on D.
 template <int D>
-__device__ __forceinline__ double tps_phi(double r) {
-    if constexpr (D == 1) return r * r * r;
-    else if constexpr (D == 2) return r > 0.0 ? r * r * log(r) : 0.0;
-    else return -r;
+__device__ __forceinline__ double tps_phi(double r2) {   // of the squared distance
+    if constexpr (D == 1) return r2 * sqrt(r2);
+    else if constexpr (D == 2) return r2 > 0.0 ? 0.5 * r2 * log(r2) : 0.0;
+    else return -sqrt(r2);
 }
 
 // Unit-box coordinates of grid design g.
@@ -113,21 +116,6 @@ __global__ void k_tps_points(DevProblem P, int64_t n, const int64_t* __restrict_
     y[i] = f[idx[i]];
 }
 
-// A = Phi + lam I (n x n, row stride ld).
-template <int D>
-__global__ void k_tps_matrix(int64_t n, int64_t ld, const double* __restrict__ U, double lam, double* __restrict__ A) {
-    const int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t i = blockIdx.y;
-    if (k >= n) return;
-    double r2 = 0.0;
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        const double s = U[i * D + j] - U[k * D + j];
-        r2 = fma(s, s, r2);
-    }
-    A[i * ld + k] = tps_phi<D>(sqrt(r2)) + (i == k ? lam : 0.0);
-}
-
 // Householder QR of P [n][d + 1] (one workgroup): reflector k is
 // I - tau_k v_k v_k^T with v_k zero above row k; R [(d+1)^2] upper
 // triangular.  A column whose remaining norm is below 1e-12 of its first
@@ -173,39 +161,123 @@ __global__ __launch_bounds__(1024) void k_tps_qr(int64_t n, int d, double* __res
     }
 }
 
-// p = tau_k A v_k, one workgroup per row.
-__global__ __launch_bounds__(256) void k_tps_gemv(int64_t n, int64_t ld, int np, int k, const double* __restrict__ A,
-                                                  const double* __restrict__ V, const double* __restrict__ tau,
-                                                  double* __restrict__ p) {
+// Row blockIdx.x of A = Phi + lam I (n x n, row stride ld) and of Y = A V, one
+// workgroup: the reflectors' products with the row while it is formed.
+template <int D>
+__global__ __launch_bounds__(256) void k_tps_matrix(int64_t n, int64_t ld, const double* __restrict__ U, double lam,
+                                                    const double* __restrict__ V, double* __restrict__ A,
+                                                    double* __restrict__ Y) {
+    constexpr int NP = D + 1;
     __shared__ double red[4];
     const int64_t i = blockIdx.x;
-    double s = 0.0;
-    for (int64_t j = threadIdx.x + k; j < n; j += blockDim.x) s = fma(A[i * ld + j], V[j * np + k], s);
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) p[i] = tau[k] * s;
+    double u[D], s[NP] = {};
+#pragma unroll
+    for (int j = 0; j < D; ++j) u[j] = U[i * D + j];
+    for (int64_t k = threadIdx.x; k < n; k += 256) {
+        double r2 = 0.0;
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            const double t = u[j] - U[k * D + j];
+            r2 = fma(t, t, r2);
+        }
+        const double a = tps_phi<D>(r2) + (i == k ? lam : 0.0);
+        A[i * ld + k] = a;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) s[q] = fma(a, V[k * NP + q], s[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+        const double v = block_sum(s[q], red);
+        if (threadIdx.x == 0) Y[i * NP + q] = v;
+    }
 }
 
-// K = tau_k / 2 v_k^T p (one workgroup).
-__global__ __launch_bounds__(1024) void k_tps_kappa(int64_t n, int np, int k, const double* __restrict__ V,
-                                                    const double* __restrict__ tau, const double* __restrict__ p,
-                                                    double* __restrict__ kappa) {
-    __shared__ double red[16];
-    double s = 0.0;
-    for (int64_t i = threadIdx.x + k; i < n; i += blockDim.x) s = fma(V[i * np + k], p[i], s);
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) *kappa = 0.5 * tau[k] * s;
+// The reflectors together, Q = H_0 ... H_d = I - V T V^T with T upper triangular
+// (T_kk = tau_k, column k above it -tau_k T V^T v_k), give
+//   Q^T A Q = A - Z V^T - V Z^T,  Z = Y T - V T^T (V^T Y) T / 2.
+// One workgroup forms T (to Tm) and B = T^T (V^T Y) T / 2 (to Tm + np^2).
+__global__ __launch_bounds__(1024) void k_tps_wy(int64_t n, int np, const double* __restrict__ V, const double* __restrict__ Y,
+                                                 const double* __restrict__ tau, double* __restrict__ Tm) {
+    constexpr int NP = kMaxTpsDim + 1;
+    __shared__ double red[16], VV[NP][NP], VY[NP][NP];
+    double sv[NP][NP] = {}, sy[NP][NP] = {};
+    for (int64_t i = threadIdx.x; i < n; i += 1024) {
+        double v[NP], y[NP];
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            v[q] = q < np ? V[i * np + q] : 0.0;
+            y[q] = q < np ? Y[i * np + q] : 0.0;
+        }
+#pragma unroll
+        for (int a = 0; a < NP; ++a)
+#pragma unroll
+            for (int b = 0; b < NP; ++b) {
+                if (a < b) sv[a][b] = fma(v[a], v[b], sv[a][b]);
+                sy[a][b] = fma(v[a], y[b], sy[a][b]);
+            }
+    }
+#pragma unroll
+    for (int a = 0; a < NP; ++a)
+#pragma unroll
+        for (int b = 0; b < NP; ++b) {
+            if (a >= np || b >= np) continue;   // uniform
+            const double x = a < b ? block_sum(sv[a][b], red) : 0.0;
+            const double y = block_sum(sy[a][b], red);
+            if (threadIdx.x == 0) {
+                VV[a][b] = x;
+                VY[a][b] = y;
+            }
+        }
+    if (threadIdx.x != 0) return;
+    double T[NP][NP] = {}, X[NP][NP];
+    for (int k = 0; k < np; ++k) {
+        T[k][k] = tau[k];
+        for (int a = 0; a < k; ++a) {
+            double x = 0.0;
+            for (int b = a; b < k; ++b) x = fma(T[a][b], VV[b][k], x);
+            T[a][k] = -tau[k] * x;
+        }
+    }
+    for (int a = 0; a < np; ++a)
+        for (int b = 0; b < np; ++b) {
+            double x = 0.0;
+            for (int k = 0; k <= b; ++k) x = fma(VY[a][k], T[k][b], x);
+            X[a][b] = x;
+        }
+    for (int a = 0; a < np; ++a)
+        for (int b = 0; b < np; ++b) {
+            double x = 0.0;
+            for (int k = 0; k <= a; ++k) x = fma(T[k][a], X[k][b], x);
+            Tm[a * np + b] = T[a][b];
+            Tm[np * np + a * np + b] = 0.5 * x;
+        }
 }
 
-// A <- H A H = A - v w^T - w v^T with w = p - K v.
-__global__ void k_tps_rank2(int64_t n, int64_t ld, int np, int k, const double* __restrict__ V, const double* __restrict__ p,
-                            const double* __restrict__ kappa, double* __restrict__ A) {
-    const int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t i = blockIdx.y;
-    if (j >= n) return;
-    const double K = *kappa;
-    const double vi = V[i * np + k], vj = V[j * np + k];
-    const double wi = p[i] - K * vi, wj = p[j] - K * vj;
-    A[i * ld + j] -= vi * wj + wi * vj;
+// Z, one thread per row.
+__global__ void k_tps_z(int64_t n, int np, const double* __restrict__ V, const double* __restrict__ Y,
+                        const double* __restrict__ Tm, double* __restrict__ Z) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    for (int k = 0; k < np; ++k) {
+        double z = 0.0;
+        for (int j = 0; j < np; ++j) z += Y[i * np + j] * Tm[j * np + k] - V[i * np + j] * Tm[np * np + j * np + k];
+        Z[i * np + k] = z;
+    }
+}
+
+// A <- A - Z V^T - V Z^T where it is read afterwards: the first np rows and the
+// lower triangle.  (One reflector after another, both sides each, read the
+// whole matrix twice and wrote it once for every reflector: 414 us for 5,754
+// centres and three of them, against 106 with T, B and Z.)
+template <int NP>
+__global__ __launch_bounds__(256) void k_tps_reduce(int64_t n, int64_t ld, const double* __restrict__ V,
+                                                    const double* __restrict__ Z, double* __restrict__ A) {
+    const int64_t i = blockIdx.y, j = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (j >= n || (j > i && i >= NP)) return;
+    double x = A[i * ld + j];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) x -= V[i * NP + k] * Z[j * NP + k] + Z[i * NP + k] * V[j * NP + k];
+    A[i * ld + j] = x;
 }
 
 // FP64 16x16x4 matrix instruction: lane l supplies A[l % 16][l / 16] and
@@ -235,31 +307,31 @@ __device__ __forceinline__ double rcp64(double x) {
     return fma(y, fma(e, e, e), y);
 }
 
-// The kNB columns [c0, c0 + kNB) of rows [r0, r0 + kNB) of the reduced system
+// The kHalf columns [c0, c0 + kHalf) of rows [r0, r0 + kNB) of the reduced system
 // (rows from `rows` on: 0), consecutive lanes on consecutive columns, and
 // their place in LDS.
-constexpr int kTileIt = kNB * kNB / 256;
+constexpr int kTileIt = kNB * kHalf / 256, kTileStep = 256 / kHalf;
 __device__ __forceinline__ void load_tile(const double* __restrict__ M, int64_t ld, int64_t r0, int64_t rows, int64_t c0,
                                           double (&v)[kTileIt]) {
-    const int c = threadIdx.x % kNB, r = threadIdx.x / kNB, left = static_cast<int>(min<int64_t>(rows - r0, kNB));
+    const int c = threadIdx.x % kHalf, r = threadIdx.x / kHalf, left = static_cast<int>(min<int64_t>(rows - r0, kNB));
     const uint32_t off = static_cast<uint32_t>(r * static_cast<int>(ld) + c);
     if (left == kNB) {   // whole tiles without a branch per load
 #pragma unroll
-        for (int q = 0; q < kTileIt; ++q) v[q] = (M + (r0 + 4 * q) * ld + c0)[off];
+        for (int q = 0; q < kTileIt; ++q) v[q] = (M + (r0 + kTileStep * q) * ld + c0)[off];
     } else {
 #pragma unroll
-        for (int q = 0; q < kTileIt; ++q) v[q] = r + 4 * q < left ? (M + (r0 + 4 * q) * ld + c0)[off] : 0.0;
+        for (int q = 0; q < kTileIt; ++q) v[q] = r + kTileStep * q < left ? (M + (r0 + kTileStep * q) * ld + c0)[off] : 0.0;
     }
 }
-__device__ __forceinline__ void store_tile(const double (&v)[kTileIt], double (*X)[kLS]) {
-    const int c = threadIdx.x % kNB, r = threadIdx.x / kNB;
+__device__ __forceinline__ void store_tile(const double (&v)[kTileIt], double (*X)[kHS]) {
+    const int c = threadIdx.x % kHalf, r = threadIdx.x / kHalf;
 #pragma unroll
-    for (int q = 0; q < kTileIt; ++q) X[r + 4 * q][c] = v[q];
+    for (int q = 0; q < kTileIt; ++q) X[r + kTileStep * q][c] = v[q];
 }
 
 // Cholesky factor L of the kNB x kNB block in the lower triangle of S by four
-// wavefronts, in blocks of 16: N receives -L below its diagonal blocks, Iv[j]
-// the inverse of diagonal block j.  Each wavefront eliminates the diagonal
+// wavefronts, in blocks of 16: block (j, i) of S, i > j, receives -L's block (i, j),
+// Iv[j] the inverse of diagonal block j.  Each wavefront eliminates the diagonal
 // block by itself in registers, its rows in lanes 0..15 and the rows of the
 // unit matrix in lanes 16..31 (the same steps turn those into the inverse's
 // transpose; a column's elements go to all lanes as scalars).  Columns are
@@ -268,7 +340,7 @@ __device__ __forceinline__ void store_tile(const double (&v)[kTileIt], double (*
 // wavefronts form the same inverse, so each goes on without waiting for the
 // others; a panel block is formed transposed, which is the operand of its
 // product either way.  True if a pivot was not positive.
-__device__ __forceinline__ bool factor_block(double (*S)[kLS], double (*N)[kLS], double (*Iv)[16][kIS], double (*T)[kIS]) {
+__device__ __forceinline__ bool factor_block(double (*S)[kLS], double (*Iv)[16][kIS], double (*T)[kIS]) {
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63, r16 = lane & 15, kq = lane >> 4;
     bool neg = false;
 #pragma unroll 1
@@ -325,7 +397,7 @@ __device__ __forceinline__ bool factor_block(double (*S)[kLS], double (*N)[kLS],
             if (bi != bk) z = panel(bi);
             else {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) N[16 * bk + r16][j0 + 4 * v + kq] = -y[v];
+                for (int v = 0; v < 4; ++v) S[j0 + r16][16 * bk + 4 * v + kq] = -y[v];
             }
             tps_d4 x{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -351,24 +423,32 @@ __device__ __forceinline__ bool factor_block(double (*S)[kLS], double (*N)[kLS],
 //     the backward solve.
 //   The others: one tile of the trailing update each, four wavefronts of 32 x 32.
 // The trailing matrix is updated at every second step, by two block columns at
-// once (the steps between update their own block column only): 118 us at 5,700
+// once (the steps between update their own block column only): 113 us at 5,700
 // rows, where two updates by one take 88 each.  It costs as much in matrix
 // instructions (59 us) as in reading and writing that matrix (57 us), and the
 // two overlap little.  A step without it is the factor's serial chain (14 of
 // 25 us).  5,754 centres: a launch for the factor (22 us) and one for the
 // update (26 us) per 32 columns, and two (9 us) for the solves, took 12.0 ms;
 // a launch per 64 columns (a square root and a division in each column's chain)
-// and one (5.5 us) for the backward solve 4.5 ms; this 4.2 ms.  Giving each
-// XCD a compact part of the tiles changes nothing.
+// and one (5.5 us) for the backward solve 4.5 ms; this 4.1 ms.  Half a block
+// column staged at a time lets three workgroups share a compute unit (two: 118
+// us); giving each XCD a compact part of the tiles changes nothing.
 // A pivot <= 0 raises *bad.
-__global__ __launch_bounds__(256, 2) void k_chol_step(int64_t ld, int64_t kb, int bs, int64_t n2, int panels, int depth,
+__global__ __launch_bounds__(256, 3) void k_chol_step(int64_t ld, int64_t kb, int bs, int64_t n2, int panels, int depth,
                                                       double* __restrict__ M, double* __restrict__ Ld,
                                                       int* __restrict__ bad) {
-    __shared__ double Xi[kNB][kLS], Xk[kNB][kLS];
+    // the staged halves of the previous block columns, then the block being factored
+    constexpr int kTile = 2 * kNB * kHS;
+    static_assert(kTile >= kNB * kLS, "the block fits the staged tiles' place");
+    __shared__ double tiles[kTile];
+    double (*Xi)[kHS] = reinterpret_cast<double (*)[kHS]>(tiles);
+    double (*Xk)[kHS] = reinterpret_cast<double (*)[kHS]>(tiles + kNB * kHS);
+    double (*S)[kLS] = reinterpret_cast<double (*)[kLS]>(tiles);
     __shared__ double Iv[kNB / 16][16][kIS], T[16][kIS];
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63, r16 = lane & 15, kq = lane >> 4;
     const int64_t rows = n2 + 1;
-    double vi[kTileIt], vk[kTileIt];   // the next block column's tiles, in flight during a product
+    double vi[kTileIt], vk[kTileIt];   // the next half's tiles, in flight during a product
+    const int64_t done = kb - depth * kNB;   // first column of the update
     if (static_cast<int>(blockIdx.x) > panels) {
         // workgroup b -> lower-triangle tile (ti, tk), tk <= ti, b = ti (ti + 1) / 2 + tk
         const int64_t b = static_cast<int64_t>(blockIdx.x) - panels - 1;
@@ -384,8 +464,8 @@ __global__ __launch_bounds__(256, 2) void k_chol_step(int64_t ld, int64_t kb, in
             const int i = rb + kq + 16 * p + 4 * v, k = cb + r16 + 16 * q;
             return i0 + i < rows && k0 + k < n2 && k0 + k <= i0 + i;
         };
-        load_tile(M, ld, i0, rows, kb - depth * kNB, vi);
-        load_tile(M, ld, k0, rows, kb - depth * kNB, vk);
+        load_tile(M, ld, i0, rows, done, vi);
+        load_tile(M, ld, k0, rows, done, vk);
         const bool whole = i0 + kNB <= rows && k0 + kNB <= n2 && k0 < i0;
         double old[2][2][4];
         const auto load_old = [&](auto in) {
@@ -405,17 +485,17 @@ __global__ __launch_bounds__(256, 2) void k_chol_step(int64_t ld, int64_t kb, in
 #pragma unroll
             for (int q = 0; q < 2; ++q) acc[p][q] = tps_d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
-        for (int back = depth; back > 0; --back) {
-            if (back < depth) __syncthreads();
+        for (int64_t from = done; from < kb; from += kHalf) {
+            if (from > done) __syncthreads();
             store_tile(vi, Xi);
             store_tile(vk, Xk);
             __syncthreads();
-            if (back > 1) {
-                load_tile(M, ld, i0, rows, kb - (back - 1) * kNB, vi);
-                load_tile(M, ld, k0, rows, kb - (back - 1) * kNB, vk);
+            if (from + kHalf < kb) {
+                load_tile(M, ld, i0, rows, from + kHalf, vi);
+                load_tile(M, ld, k0, rows, from + kHalf, vk);
             }
 #pragma unroll
-            for (int c0 = 0; c0 < kNB; c0 += 4) {
+            for (int c0 = 0; c0 < kHalf; c0 += 4) {
                 const double x0 = Xi[rb + r16][c0 + kq], x1 = Xi[rb + 16 + r16][c0 + kq];
                 const double y0 = Xk[cb + r16][c0 + kq], y1 = Xk[cb + 16 + r16][c0 + kq];
                 acc[0][0] = mfma64(x0, y0, acc[0][0]);
@@ -472,69 +552,70 @@ __global__ __launch_bounds__(256, 2) void k_chol_step(int64_t ld, int64_t kb, in
         load_block([&](int i, int k) { return i < bs && k < bs; },
                    [&](int i, int k) { return !unit && r0 + i < rows && k < bs; });
     if (depth > 0) {
-        if (!unit) load_tile(M, ld, r0, rows, kb - depth * kNB, vi);
-        load_tile(M, ld, kb, kb + bs, kb - depth * kNB, vk);
+        if (!unit) load_tile(M, ld, r0, rows, done, vi);
+        load_tile(M, ld, kb, kb + bs, done, vk);
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) Xi[16 * wave + r][lane] = own[r];
+    for (int r = 0; r < 16; ++r) S[16 * wave + r][lane] = own[r];
     wave_sync();
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) x[q][v] = Xi[16 * wave + r16][16 * q + kq + 4 * v];
+        for (int v = 0; v < 4; ++v) x[q][v] = S[16 * wave + r16][16 * q + kq + 4 * v];
     __syncthreads();
 #pragma unroll 1
-    for (int back = depth; back > 0; --back) {
-        if (back < depth) {
-            if (!unit) load_tile(M, ld, r0, rows, kb - back * kNB, vi);
-            load_tile(M, ld, kb, kb + bs, kb - back * kNB, vk);
-        }
+    for (int64_t from = done; from < kb; from += kHalf) {
         if (!unit) store_tile(vi, Xi);
         store_tile(vk, Xk);
         __syncthreads();
+        if (from + kHalf < kb) {
+            if (!unit) load_tile(M, ld, r0, rows, from + kHalf, vi);
+            load_tile(M, ld, kb, kb + bs, from + kHalf, vk);
+        }
 #pragma unroll 4
-        for (int c0 = 0; c0 < kNB; c0 += 4)
+        for (int c0 = 0; c0 < kHalf; c0 += 4)
 #pragma unroll
             for (int q = 0; q < 3; ++q) diag[q] = mfma64(-Xk[16 * bi[q] + r16][c0 + kq], Xk[16 * bk[q] + r16][c0 + kq], diag[q]);
         if (!unit) {
 #pragma unroll 4
-            for (int c0 = 0; c0 < kNB; c0 += 4) {
+            for (int c0 = 0; c0 < kHalf; c0 += 4) {
                 const double y = Xi[16 * wave + r16][c0 + kq];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) x[q] = mfma64(-Xk[16 * q + r16][c0 + kq], y, x[q]);
             }
         }
-        __syncthreads();   // Xk takes the next block column, at the end the diagonal block
+        __syncthreads();   // the tiles' place takes the next half, at the end the diagonal block
     }
 #pragma unroll
     for (int q = 0; q < 3; ++q)
 #pragma unroll
         for (int v = 0; v < 4; ++v)   // the tenth block comes from waves 1..3 alike
-            Xk[16 * bi[q] + kq + 4 * v][16 * bk[q] + r16] = diag[q][v];
+            S[16 * bi[q] + kq + 4 * v][16 * bk[q] + r16] = diag[q][v];
     __syncthreads();
-    const bool neg = factor_block(Xk, Xi, Iv, T);
+    const bool neg = factor_block(S, Iv, T);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
 #pragma unroll
         for (int e = 0; e < q; ++e)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) x[q] = mfma64(Xi[16 * q + r16][16 * e + 4 * k + kq], x[e][k], x[q]);
+            for (int k = 0; k < 4; ++k) x[q] = mfma64(S[16 * e + r16][16 * q + 4 * k + kq], x[e][k], x[q]);
         tps_d4 y{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int k = 0; k < 4; ++k) y = mfma64(Iv[q][r16][4 * k + kq], x[q][k], y);
         x[q] = y;
     }
+    __syncthreads();   // S is read by all until here
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) Xk[16 * wave + r16][16 * q + kq + 4 * v] = x[q][v];
+        for (int v = 0; v < 4; ++v) S[16 * wave + r16][16 * q + kq + 4 * v] = x[q][v];
     wave_sync();
     double* to = unit ? Ld + kb * kNB + lane : M + r0 * ld + kb + lane;
     const int64_t stride = unit ? kNB : ld;
     const int left = unit || whole ? kNB : static_cast<int>(min<int64_t>(rows - r0, kNB));
 #pragma unroll
     for (int r = 0; r < 16; ++r)
-        if (16 * wave + r < left && (unit || lane < bs)) to[(16 * wave + r) * stride] = Xk[16 * wave + r][lane];
+        if (16 * wave + r < left && (unit || lane < bs)) to[(16 * wave + r) * stride] = S[16 * wave + r][lane];
     if (unit && t == 0 && neg) *bad = 1;
 }
 
@@ -648,7 +729,7 @@ __global__ __launch_bounds__(256) void k_tps_eval_grid(DevProblem P, int64_t n, 
             const double s = u[j] - U[i * D + j];
             r2 = fma(s, s, r2);
         }
-        v = fma(c[i], tps_phi<D>(sqrt(r2)), v);
+        v = fma(c[i], tps_phi<D>(r2), v);
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
@@ -680,7 +761,7 @@ __global__ __launch_bounds__(1024) void k_tps_at(int64_t n, const double* __rest
             r2 = fma(s[j], s[j], r2);
         }
         const double r = sqrt(r2);
-        acc[0] = fma(c[i], tps_phi<D>(r), acc[0]);
+        acc[0] = fma(c[i], tps_phi<D>(r2), acc[0]);
         if (r == 0.0) continue;
         double p1, p2;   // phi'(r), phi''(r)
         if constexpr (D == 1) {
@@ -738,17 +819,17 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
     TpsFitResult res{kTpsOk, 0, hipSuccess};
     int64_t n = 0, n2 = 0, ld = 0;
     int bad = 0;
-    char* small = nullptr;   // idx [G], n, bad flag; tau, R, kappa
-    double* big = nullptr;   // A [n ld], z [n] as its row n, V and P [n (d + 1)], y, p, w [n], Ld
+    char* small = nullptr;   // idx [G], n, bad flag; tau, R, T and B
+    double* big = nullptr;   // A [n ld], z [n] as its row n, V, P, Y and Z [n (d + 1)], y, w [n], Ld
     double* fitmem = nullptr;
     int64_t* d_idx = nullptr;
     int64_t* d_n = nullptr;
     int* d_bad = nullptr;
-    double *d_tau = nullptr, *d_R = nullptr, *d_kappa = nullptr;
-    double *A = nullptr, *V = nullptr, *Pm = nullptr, *y = nullptr, *z = nullptr, *pv = nullptr, *M = nullptr;
+    double *d_tau = nullptr, *d_R = nullptr, *d_T = nullptr;
+    double *A = nullptr, *V = nullptr, *Pm = nullptr, *y = nullptr, *z = nullptr, *Y = nullptr, *Z = nullptr, *M = nullptr;
     double *Ld = nullptr, *w = nullptr;   // inverses of the factor's diagonal blocks; the reduced system's solution
     double *U = nullptr, *c = nullptr, *a = nullptr;
-    const size_t small_bytes = sizeof(int64_t) * (G + 2) + 64 + sizeof(double) * (2 * np + np * np + 8);
+    const size_t small_bytes = sizeof(int64_t) * (G + 2) + 64 + sizeof(double) * (2 * np + 3 * np * np + 8);
     if (hipMalloc(&small, small_bytes) != hipSuccess) {
         (void)hipGetLastError();
         res.code = kTpsNoMem;
@@ -759,7 +840,7 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
     d_bad = reinterpret_cast<int*>(d_n + 1);
     d_tau = reinterpret_cast<double*>(small + sizeof(int64_t) * (G + 2) + 64);
     d_R = d_tau + np;
-    d_kappa = d_R + np * np;
+    d_T = d_R + np * np;
     TPS_TRY(hipMemsetAsync(d_bad, 0, sizeof(int), s));
     hipLaunchKernelGGL(k_tps_compact, dim3(1), dim3(1024), 0, s, G, d_in, d_idx, d_n);
     TPS_TRY(hipGetLastError());
@@ -775,7 +856,7 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
         // the reduced system's rows begin on a cache line: row stride and first column in 16 doubles
         ld = (n + 15) / 16 * 16;
         const size_t lead = 16 - np, full = static_cast<size_t>(ld);
-        const size_t big_count = lead + (nn + 1) * full + 2 * nn * np + 3 * nn + kNB * (nn + kNB);
+        const size_t big_count = lead + (nn + 1) * full + 4 * nn * np + 2 * nn + kNB * (nn + kNB);
         if (hipMalloc(&big, sizeof(double) * big_count) != hipSuccess ||
             hipMalloc(&fitmem, sizeof(double) * (nn * d + nn + np)) != hipSuccess) {
             (void)hipGetLastError();
@@ -786,9 +867,10 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
         z = A + nn * full;
         V = z + full;
         Pm = V + nn * np;
-        y = Pm + nn * np;
-        pv = y + nn;
-        w = pv + nn;
+        Y = Pm + nn * np;
+        Z = Y + nn * np;
+        y = Z + nn * np;
+        w = y + nn;
         Ld = w + nn;
         U = fitmem;
         c = U + nn * d;
@@ -797,20 +879,19 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
     hipLaunchKernelGGL(k_tps_points, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, P, n, d_idx, d_in,
                        U, y, Pm);
     TPS_TRY(hipGetLastError());
-    {
-        const dim3 grid(static_cast<unsigned>((n + 255) / 256), static_cast<unsigned>(n));
-        if (d == 1) hipLaunchKernelGGL(k_tps_matrix<1>, grid, dim3(256), 0, s, n, ld, U, lam, A);
-        else if (d == 2) hipLaunchKernelGGL(k_tps_matrix<2>, grid, dim3(256), 0, s, n, ld, U, lam, A);
-        else hipLaunchKernelGGL(k_tps_matrix<3>, grid, dim3(256), 0, s, n, ld, U, lam, A);
-    }
-    TPS_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_tps_qr, dim3(1), dim3(1024), 0, s, n, d, Pm, V, d_tau, d_R, d_bad);
     TPS_TRY(hipGetLastError());
-    for (int k = 0; k < np; ++k) {   // M = Q^T A Q, one reflector at a time from both sides
-        hipLaunchKernelGGL(k_tps_gemv, dim3(static_cast<unsigned>(n)), dim3(256), 0, s, n, ld, np, k, A, V, d_tau, pv);
-        hipLaunchKernelGGL(k_tps_kappa, dim3(1), dim3(1024), 0, s, n, np, k, V, d_tau, pv, d_kappa);
-        hipLaunchKernelGGL(k_tps_rank2, dim3(static_cast<unsigned>((n + 255) / 256), static_cast<unsigned>(n)),
-                           dim3(256), 0, s, n, ld, np, k, V, pv, d_kappa, A);
+    {
+        const dim3 grid(static_cast<unsigned>(n)), part(static_cast<unsigned>((n + 255) / 256), static_cast<unsigned>(n));
+        if (d == 1) hipLaunchKernelGGL(k_tps_matrix<1>, grid, dim3(256), 0, s, n, ld, U, lam, V, A, Y);
+        else if (d == 2) hipLaunchKernelGGL(k_tps_matrix<2>, grid, dim3(256), 0, s, n, ld, U, lam, V, A, Y);
+        else hipLaunchKernelGGL(k_tps_matrix<3>, grid, dim3(256), 0, s, n, ld, U, lam, V, A, Y);
+        TPS_TRY(hipGetLastError());
+        hipLaunchKernelGGL(k_tps_wy, dim3(1), dim3(1024), 0, s, n, np, V, Y, d_tau, d_T);   // M = Q^T A Q
+        hipLaunchKernelGGL(k_tps_z, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, n, np, V, Y, d_T, Z);
+        if (d == 1) hipLaunchKernelGGL(k_tps_reduce<2>, part, dim3(256), 0, s, n, ld, V, Z, A);
+        else if (d == 2) hipLaunchKernelGGL(k_tps_reduce<3>, part, dim3(256), 0, s, n, ld, V, Z, A);
+        else hipLaunchKernelGGL(k_tps_reduce<4>, part, dim3(256), 0, s, n, ld, V, Z, A);
         TPS_TRY(hipGetLastError());
     }
     hipLaunchKernelGGL(k_tps_qty, dim3(1), dim3(1024), 0, s, n, np, V, d_tau, y, z);
