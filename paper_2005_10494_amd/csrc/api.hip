@@ -1571,12 +1571,6 @@ bmd_status newton_ascent(bmd_problem* p, Eval eval, const double* h_q0, int32_t 
         bmin = std::min(bmin, p->desc.bandwidth[j]);
     }
     constexpr double kArmijo = 1e-4;
-    // A Newton step whose gain lies below what the value resolves (a thin-plate
-    // value, a sum of thousands of cancelling terms, is 1e-14 off) passes the
-    // test or fails it by chance, and a failure cost forty evaluations and left
-    // the design up to 1e-9 short: such steps are taken while they shrink.
-    constexpr double kTinyGain = 1e-12, kTinyStep = 1e-6;
-    double last = kTinyStep;
     double q[kMaxDim], g[kMaxDim], H[kMaxDim * kMaxDim], f = 0.0;
     for (int j = 0; j < d; ++j) q[j] = std::min(hi[j], std::max(lo[j], h_q0[j]));
     bmd_status st = eval(q, &f, g, H);
@@ -1584,8 +1578,7 @@ bmd_status newton_ascent(bmd_problem* p, Eval eval, const double* h_q0, int32_t 
     int it = 0;
     while (it < max_iter) {
         double dir[kMaxDim];
-        const bool newton = newton_direction(d, H, g, dir);
-        if (!newton) {
+        if (!newton_direction(d, H, g, dir)) {
             double gn = 0.0;
             for (int j = 0; j < d; ++j) gn = std::max(gn, std::fabs(g[j]));
             if (gn == 0.0) break;
@@ -1594,16 +1587,14 @@ bmd_status newton_ascent(bmd_problem* p, Eval eval, const double* h_q0, int32_t 
         double t = 1.0, qn[kMaxDim], fn = 0.0, gnext[kMaxDim], Hn[kMaxDim * kMaxDim];
         bool ok = false;
         for (int bt = 0; bt < 40 && !ok; ++bt, t *= 0.5) {
-            double slope = 0.0, step = 0.0;
+            double slope = 0.0;
             for (int j = 0; j < d; ++j) {
                 qn[j] = std::min(hi[j], std::max(lo[j], q[j] + t * dir[j]));
                 slope += g[j] * (qn[j] - q[j]);
-                step = std::max(step, std::fabs(qn[j] - q[j]));
             }
             st = eval(qn, &fn, gnext, Hn);
             if (st != BMD_OK) return st;
-            const bool tiny = newton && bt == 0 && std::isfinite(fn) && step <= 0.5 * last && slope <= kTinyGain * std::fabs(f);
-            ok = (fn >= f + kArmijo * slope || tiny) && slope >= 0.0;
+            ok = fn >= f + kArmijo * slope && slope >= 0.0;
         }
         if (!ok) break;
         ++it;
@@ -1615,7 +1606,6 @@ bmd_status newton_ascent(bmd_problem* p, Eval eval, const double* h_q0, int32_t 
         }
         std::copy(Hn, Hn + d * d, H);
         f = fn;
-        last = std::min(last, move);
         if (move <= tol) break;
     }
     for (int j = 0; j < d; ++j) h_q[j] = q[j];

@@ -25,12 +25,8 @@ struct TpsFit {
 
 namespace {
 
-constexpr int kMaxTpsDim = 3;
-constexpr int kNB = 64;          // Cholesky and triangular-solve block, and the update's output tile
-constexpr int kLS = kNB + 2;     // LDS row stride of a tile: a 16 x 4 operand read touches every bank twice
-constexpr int kHalf = kNB / 2;   // columns staged at a time
-constexpr int kHS = kHalf + 2;   // their LDS row stride (as kLS)
-constexpr int kIS = 18;          // LDS row stride of a 16 x 16 inverse
+constexpr int kNB = 32;          // Cholesky and triangular-solve block
+constexpr int kUT = 64;          // trailing-update tile (kUT x kUT outputs per workgroup)
 
 // The radial function for D dimensions, fixed at compile time: with the
 // dimension chosen at run time inside one function, the gfx950 code of an
@@ -38,10 +34,10 @@ constexpr int kIS = 18;          // LDS row stride of a 16 x 16 inverse
 // square root (NaN at r = 0), so every kernel that evaluates phi is a
 // template on D.
 template <int D>
-__device__ __forceinline__ double tps_phi(double r2) {   // of the squared distance
-    if constexpr (D == 1) return r2 * sqrt(r2);
-    else if constexpr (D == 2) return r2 > 0.0 ? 0.5 * r2 * log(r2) : 0.0;
-    else return -sqrt(r2);
+__device__ __forceinline__ double tps_phi(double r) {
+    if constexpr (D == 1) return r * r * r;
+    else if constexpr (D == 2) return r > 0.0 ? r * r * log(r) : 0.0;
+    else return -r;
 }
 
 // Unit-box coordinates of grid design g.
@@ -116,6 +112,21 @@ __global__ void k_tps_points(DevProblem P, int64_t n, const int64_t* __restrict_
     y[i] = f[idx[i]];
 }
 
+// A = Phi + lam I (n x n, row-major).
+template <int D>
+__global__ void k_tps_matrix(int64_t n, const double* __restrict__ U, double lam, double* __restrict__ A) {
+    const int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t i = blockIdx.y;
+    if (k >= n) return;
+    double r2 = 0.0;
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+        const double s = U[i * D + j] - U[k * D + j];
+        r2 = fma(s, s, r2);
+    }
+    A[i * n + k] = tps_phi<D>(sqrt(r2)) + (i == k ? lam : 0.0);
+}
+
 // Householder QR of P [n][d + 1] (one workgroup): reflector k is
 // I - tau_k v_k v_k^T with v_k zero above row k; R [(d+1)^2] upper
 // triangular.  A column whose remaining norm is below 1e-12 of its first
@@ -161,462 +172,211 @@ __global__ __launch_bounds__(1024) void k_tps_qr(int64_t n, int d, double* __res
     }
 }
 
-// Row blockIdx.x of A = Phi + lam I (n x n, row stride ld) and of Y = A V, one
-// workgroup: the reflectors' products with the row while it is formed.
-template <int D>
-__global__ __launch_bounds__(256) void k_tps_matrix(int64_t n, int64_t ld, const double* __restrict__ U, double lam,
-                                                    const double* __restrict__ V, double* __restrict__ A,
-                                                    double* __restrict__ Y) {
-    constexpr int NP = D + 1;
+// p = tau_k A v_k, one workgroup per row.
+__global__ __launch_bounds__(256) void k_tps_gemv(int64_t n, int np, int k, const double* __restrict__ A,
+                                                  const double* __restrict__ V, const double* __restrict__ tau,
+                                                  double* __restrict__ p) {
     __shared__ double red[4];
     const int64_t i = blockIdx.x;
-    double u[D], s[NP] = {};
-#pragma unroll
-    for (int j = 0; j < D; ++j) u[j] = U[i * D + j];
-    for (int64_t k = threadIdx.x; k < n; k += 256) {
-        double r2 = 0.0;
-#pragma unroll
-        for (int j = 0; j < D; ++j) {
-            const double t = u[j] - U[k * D + j];
-            r2 = fma(t, t, r2);
-        }
-        const double a = tps_phi<D>(r2) + (i == k ? lam : 0.0);
-        A[i * ld + k] = a;
-#pragma unroll
-        for (int q = 0; q < NP; ++q) s[q] = fma(a, V[k * NP + q], s[q]);
-    }
-#pragma unroll
-    for (int q = 0; q < NP; ++q) {
-        const double v = block_sum(s[q], red);
-        if (threadIdx.x == 0) Y[i * NP + q] = v;
-    }
+    double s = 0.0;
+    for (int64_t j = threadIdx.x + k; j < n; j += blockDim.x) s = fma(A[i * n + j], V[j * np + k], s);
+    s = block_sum(s, red);
+    if (threadIdx.x == 0) p[i] = tau[k] * s;
 }
 
-// The reflectors together, Q = H_0 ... H_d = I - V T V^T with T upper triangular
-// (T_kk = tau_k, column k above it -tau_k T V^T v_k), give
-//   Q^T A Q = A - Z V^T - V Z^T,  Z = Y T - V T^T (V^T Y) T / 2.
-// One workgroup forms T (to Tm) and B = T^T (V^T Y) T / 2 (to Tm + np^2).
-__global__ __launch_bounds__(1024) void k_tps_wy(int64_t n, int np, const double* __restrict__ V, const double* __restrict__ Y,
-                                                 const double* __restrict__ tau, double* __restrict__ Tm) {
-    constexpr int NP = kMaxTpsDim + 1;
-    __shared__ double red[16], VV[NP][NP], VY[NP][NP];
-    double sv[NP][NP] = {}, sy[NP][NP] = {};
-    for (int64_t i = threadIdx.x; i < n; i += 1024) {
-        double v[NP], y[NP];
+// K = tau_k / 2 v_k^T p (one workgroup).
+__global__ __launch_bounds__(1024) void k_tps_kappa(int64_t n, int np, int k, const double* __restrict__ V,
+                                                    const double* __restrict__ tau, const double* __restrict__ p,
+                                                    double* __restrict__ kappa) {
+    __shared__ double red[16];
+    double s = 0.0;
+    for (int64_t i = threadIdx.x + k; i < n; i += blockDim.x) s = fma(V[i * np + k], p[i], s);
+    s = block_sum(s, red);
+    if (threadIdx.x == 0) *kappa = 0.5 * tau[k] * s;
+}
+
+// A <- H A H = A - v w^T - w v^T with w = p - K v.
+__global__ void k_tps_rank2(int64_t n, int np, int k, const double* __restrict__ V, const double* __restrict__ p,
+                            const double* __restrict__ kappa, double* __restrict__ A) {
+    const int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t i = blockIdx.y;
+    if (j >= n) return;
+    const double K = *kappa;
+    const double vi = V[i * np + k], vj = V[j * np + k];
+    const double wi = p[i] - K * vi, wj = p[j] - K * vj;
+    A[i * n + j] -= vi * wj + wi * vj;
+}
+
+// Panel slices are kPanelRows rows: thread t of a slice owns its row t.
+constexpr int kPanelRows = 128;
+
+// The bs x bs block at blk (row stride n) into L by NT threads: thread t
+// takes column t % kNB of rows t / kNB + (NT / kNB) i, all loads in flight
+// before the first LDS write.
+template <int NT>
+__device__ __forceinline__ void stage_block(const double* __restrict__ blk, int64_t n, int bs, double (*L)[kNB + 1]) {
+    constexpr int kStep = NT / kNB, kIt = kNB / kStep;
+    const int t = threadIdx.x, c = t % kNB, r = t / kNB;
+    double v[kIt];
 #pragma unroll
-        for (int q = 0; q < NP; ++q) {
-            v[q] = q < np ? V[i * np + q] : 0.0;
-            y[q] = q < np ? Y[i * np + q] : 0.0;
-        }
+    for (int i = 0; i < kIt; ++i) v[i] = (r + kStep * i < bs && c < bs) ? blk[(r + kStep * i) * n + c] : 0.0;
 #pragma unroll
-        for (int a = 0; a < NP; ++a)
+    for (int i = 0; i < kIt; ++i) L[r + kStep * i][c] = v[i];
+}
+
+// Rows [0, nr) x columns [0, bs) of the slice at base (row stride n) into X:
+// thread t takes column t % kNB of rows t / kNB + 4 i, every load issued
+// before the first LDS write so the loads' latencies overlap.
+__device__ __forceinline__ void stage_rows(const double* __restrict__ base, int64_t n, int nr, int bs,
+                                           double (*X)[kNB + 1]) {
+    static_assert(kPanelRows == 4 * kNB, "four rows per pass");
+    const int t = threadIdx.x, c = t % kNB, r = t / kNB;
+    double v[kNB];
 #pragma unroll
-            for (int b = 0; b < NP; ++b) {
-                if (a < b) sv[a][b] = fma(v[a], v[b], sv[a][b]);
-                sy[a][b] = fma(v[a], y[b], sy[a][b]);
+    for (int i = 0; i < kNB; ++i) v[i] = (r + 4 * i < nr && c < bs) ? base[(r + 4 * i) * n + c] : 0.0;
+#pragma unroll
+    for (int i = 0; i < kNB; ++i) X[r + 4 * i][c] = v[i];
+}
+
+// One step of the blocked Cholesky M22 = L L^T at block column kb: the kNB x
+// kNB diagonal block, then the panel below it, L21 = A21 L11^-T.  Every
+// workgroup factors the diagonal block itself in its first wavefront (lane r
+// holds row r in registers; per column j every lane reads the pivot from lane
+// j, lanes below scale their element of column j and update their rows with
+// the other lanes' column-j elements, read from their lanes), so the step is
+// one launch; A's diagonal block is only read, and workgroup 0 stores the
+// factor in Ld (row stride kNB, zeros above the diagonal) for the triangular
+// solves.  The panel's row segments go through LDS with consecutive lanes on
+// consecutive columns (a thread walking its own row in memory would touch a
+// different cache line per lane on every load).  A pivot <= 0 raises *bad.
+__global__ __launch_bounds__(kPanelRows) void k_chol_step(int64_t n, int64_t o, int64_t kb, int bs, int64_t n2,
+                                                          double* __restrict__ A, double* __restrict__ Ld,
+                                                          int* __restrict__ bad) {
+    __shared__ double L[kNB][kNB + 1];
+    __shared__ double X[kPanelRows][kNB + 1];
+    const int t = threadIdx.x;
+    const int64_t r0 = kb + bs + static_cast<int64_t>(blockIdx.x) * kPanelRows;
+    const int nr = static_cast<int>(max<int64_t>(0, min<int64_t>(kPanelRows, n2 - r0)));
+    double* base = A + (o + r0) * n + o + kb;
+    if (nr > 0) stage_rows(base, n, nr, bs, X);
+    if (t < 64) {   // the first wavefront
+        double row[kNB];
+#pragma unroll
+        for (int c = 0; c < kNB; ++c) row[c] = (t < bs && c <= t) ? A[(o + kb + t) * n + o + kb + c] : 0.0;
+        bool neg = false;
+#pragma unroll
+        for (int j = 0; j < kNB; ++j) {
+            if (j < bs) {   // wave-uniform
+                const double pv = lane_value(row[j], j);
+                neg |= !(pv > 0.0);
+                const double dj = pv > 0.0 ? sqrt(pv) : 1.0;
+                const double lrj = (t > j) ? row[j] / dj : (t == j ? dj : row[j]);
+                row[j] = lrj;
+#pragma unroll
+                for (int c = j + 1; c < kNB; ++c) {
+                    const double lcj = lane_value(lrj, c);   // column j of row c
+                    if (t >= c) row[c] -= lrj * lcj;
+                }
             }
+        }
+        if (t < kNB) {
+#pragma unroll
+            for (int c = 0; c < kNB; ++c) L[t][c] = c <= t ? row[c] : 0.0;
+        }
+        if (blockIdx.x == 0 && t == 0 && neg) *bad = 1;
     }
+    __syncthreads();
+    if (blockIdx.x == 0) {
+        double* ld = Ld + kb * kNB;
+        for (int e = t; e < kNB * kNB; e += kPanelRows) ld[e] = L[e / kNB][e % kNB];
+    }
+    if (nr == 0) return;   // workgroup-uniform
+    if (t < nr) {
+        double x[kNB];
 #pragma unroll
-    for (int a = 0; a < NP; ++a)
+        for (int c = 0; c < kNB; ++c) {
+            if (c < bs) {
+                double s = X[t][c];
 #pragma unroll
-        for (int b = 0; b < NP; ++b) {
-            if (a >= np || b >= np) continue;   // uniform
-            const double x = a < b ? block_sum(sv[a][b], red) : 0.0;
-            const double y = block_sum(sy[a][b], red);
-            if (threadIdx.x == 0) {
-                VV[a][b] = x;
-                VY[a][b] = y;
+                for (int e = 0; e < kNB; ++e)
+                    if (e < c) s -= x[e] * L[c][e];
+                x[c] = s / L[c][c];
             }
         }
-    if (threadIdx.x != 0) return;
-    double T[NP][NP] = {}, X[NP][NP];
-    for (int k = 0; k < np; ++k) {
-        T[k][k] = tau[k];
-        for (int a = 0; a < k; ++a) {
-            double x = 0.0;
-            for (int b = a; b < k; ++b) x = fma(T[a][b], VV[b][k], x);
-            T[a][k] = -tau[k] * x;
-        }
-    }
-    for (int a = 0; a < np; ++a)
-        for (int b = 0; b < np; ++b) {
-            double x = 0.0;
-            for (int k = 0; k <= b; ++k) x = fma(VY[a][k], T[k][b], x);
-            X[a][b] = x;
-        }
-    for (int a = 0; a < np; ++a)
-        for (int b = 0; b < np; ++b) {
-            double x = 0.0;
-            for (int k = 0; k <= a; ++k) x = fma(T[k][a], X[k][b], x);
-            Tm[a * np + b] = T[a][b];
-            Tm[np * np + a * np + b] = 0.5 * x;
-        }
-}
-
-// Z, one thread per row.
-__global__ void k_tps_z(int64_t n, int np, const double* __restrict__ V, const double* __restrict__ Y,
-                        const double* __restrict__ Tm, double* __restrict__ Z) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    for (int k = 0; k < np; ++k) {
-        double z = 0.0;
-        for (int j = 0; j < np; ++j) z += Y[i * np + j] * Tm[j * np + k] - V[i * np + j] * Tm[np * np + j * np + k];
-        Z[i * np + k] = z;
-    }
-}
-
-// A <- A - Z V^T - V Z^T where it is read afterwards: the first np rows and the
-// lower triangle.  (One reflector after another, both sides each, read the
-// whole matrix twice and wrote it once for every reflector: 414 us for 5,754
-// centres and three of them, against 106 with T, B and Z.)
-template <int NP>
-__global__ __launch_bounds__(256) void k_tps_reduce(int64_t n, int64_t ld, const double* __restrict__ V,
-                                                    const double* __restrict__ Z, double* __restrict__ A) {
-    const int64_t i = blockIdx.y, j = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (j >= n || (j > i && i >= NP)) return;
-    double x = A[i * ld + j];
 #pragma unroll
-    for (int k = 0; k < NP; ++k) x -= V[i * NP + k] * Z[j * NP + k] + Z[i * NP + k] * V[j * NP + k];
-    A[i * ld + j] = x;
+        for (int c = 0; c < kNB; ++c)
+            if (c < bs) X[t][c] = x[c];
+    }
+    __syncthreads();
+    const int c = t % kNB, r = t / kNB;
+#pragma unroll
+    for (int i = 0; i < kNB; ++i)
+        if (r + 4 * i < nr && c < bs) base[(r + 4 * i) * n + c] = X[r + 4 * i][c];
 }
 
-// FP64 16x16x4 matrix instruction: lane l supplies A[l % 16][l / 16] and
-// B[l / 16][l % 16]; element v of its result is row l / 16 + 4 v, column
-// l % 16.  So a result's element v is also the B operand of the v-th slice of
-// four of a following product's 16 inner indices.
+// Trailing update A22 -= L21 L21^T on the lower triangle, kUT x kUT output
+// tiles on the matrix cores (FP64 16x16x4): four wavefronts, each a 32 x 32
+// quarter as 2 x 2 blocks of 16 x 16; the tile's rows of L21 (both factors)
+// staged in LDS; one workgroup per tile on or below the diagonal.  Operand layout of the
+// instruction: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]; its
+// result element v is row l / 16 + 4 v, column l % 16.
 typedef double tps_d4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ tps_d4 mfma64(double a, double b, tps_d4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
 
-// Orders a wavefront's LDS writes before its other lanes' reads.
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// 1/sqrt(x) and 1/x: the hardware's estimates (2^-24) and one third-order step.
-__device__ __forceinline__ double rsqrt64(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-(x * y), y, 1.0);
-    return fma(y * e, fma(e, 0.375, 0.5), y);
-}
-__device__ __forceinline__ double rcp64(double x) {
-    const double y = __builtin_amdgcn_rcp(x);
-    const double e = fma(-x, y, 1.0);
-    return fma(y, fma(e, e, e), y);
-}
-
-// The kHalf columns [c0, c0 + kHalf) of rows [r0, r0 + kNB) of the reduced system
-// (rows from `rows` on: 0), consecutive lanes on consecutive columns, and
-// their place in LDS.
-constexpr int kTileIt = kNB * kHalf / 256, kTileStep = 256 / kHalf;
-__device__ __forceinline__ void load_tile(const double* __restrict__ M, int64_t ld, int64_t r0, int64_t rows, int64_t c0,
-                                          double (&v)[kTileIt]) {
-    const int c = threadIdx.x % kHalf, r = threadIdx.x / kHalf, left = static_cast<int>(min<int64_t>(rows - r0, kNB));
-    const uint32_t off = static_cast<uint32_t>(r * static_cast<int>(ld) + c);
-    if (left == kNB) {   // whole tiles without a branch per load
+__global__ __launch_bounds__(256) void k_chol_update(int64_t n, int64_t o, int64_t kb, int bs, int64_t n2,
+                                                     double* __restrict__ A) {
+    const int64_t t0 = kb + bs;
+    // workgroup b -> lower-triangle tile (ti, tk), tk <= ti, b = ti (ti + 1) / 2 + tk
+    const int64_t b = blockIdx.x;
+    int64_t ti = static_cast<int64_t>((sqrt(8.0 * static_cast<double>(b) + 1.0) - 1.0) * 0.5);
+    while (ti * (ti + 1) / 2 > b) --ti;
+    while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
+    const int64_t tk = b - ti * (ti + 1) / 2;
+    __shared__ double Li[kUT][kNB + 1], Lk[kUT][kNB + 1];
+    const int t = threadIdx.x;
+    const int64_t i0 = t0 + ti * kUT, k0 = t0 + tk * kUT;
+    {   // thread t takes column t % kNB of rows t / kNB + 8 q; every load issued before the first LDS write
+        constexpr int kIt = kUT * kNB / 256;
+        const int c = t % kNB, r = t / kNB;
+        double vi[kIt], vk[kIt];
 #pragma unroll
-        for (int q = 0; q < kTileIt; ++q) v[q] = (M + (r0 + kTileStep * q) * ld + c0)[off];
-    } else {
+        for (int q = 0; q < kIt; ++q) {
+            const int rr = r + 8 * q;
+            vi[q] = (i0 + rr < n2 && c < bs) ? A[(o + i0 + rr) * n + o + kb + c] : 0.0;
+            vk[q] = (k0 + rr < n2 && c < bs) ? A[(o + k0 + rr) * n + o + kb + c] : 0.0;
+        }
 #pragma unroll
-        for (int q = 0; q < kTileIt; ++q) v[q] = r + kTileStep * q < left ? (M + (r0 + kTileStep * q) * ld + c0)[off] : 0.0;
+        for (int q = 0; q < kIt; ++q) {
+            Li[r + 8 * q][c] = vi[q];
+            Lk[r + 8 * q][c] = vk[q];
+        }
     }
-}
-__device__ __forceinline__ void store_tile(const double (&v)[kTileIt], double (*X)[kHS]) {
-    const int c = threadIdx.x % kHalf, r = threadIdx.x / kHalf;
+    __syncthreads();
+    const int wave = t >> 6, lane = t & 63;
+    const int r16 = lane & 15, kq = lane >> 4;
+    const int rb = (wave >> 1) * 32, cb = (wave & 1) * 32;
+    tps_d4 acc[2][2];
 #pragma unroll
-    for (int q = 0; q < kTileIt; ++q) X[r + kTileStep * q][c] = v[q];
-}
-
-// Cholesky factor L of the kNB x kNB block in the lower triangle of S by four
-// wavefronts, in blocks of 16: block (j, i) of S, i > j, receives -L's block (i, j),
-// Iv[j] the inverse of diagonal block j.  Each wavefront eliminates the diagonal
-// block by itself in registers, its rows in lanes 0..15 and the rows of the
-// unit matrix in lanes 16..31 (the same steps turn those into the inverse's
-// transpose; a column's elements go to all lanes as scalars).  Columns are
-// scaled by 1/sqrt(pivot) afterwards, and the next pivot is formed beside the
-// row updates, so a column's chain is a reciprocal and two operations.  All
-// wavefronts form the same inverse, so each goes on without waiting for the
-// others; a panel block is formed transposed, which is the operand of its
-// product either way.  True if a pivot was not positive.
-__device__ __forceinline__ bool factor_block(double (*S)[kLS], double (*Iv)[16][kIS], double (*T)[kIS]) {
-    const int t = threadIdx.x, wave = t >> 6, lane = t & 63, r16 = lane & 15, kq = lane >> 4;
-    bool neg = false;
-#pragma unroll 1
-    for (int j = 0; j < kNB / 16; ++j) {
-        const int j0 = 16 * j;
-        double row[16];
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            const double v = S[j0 + r16][j0 + c];
-            row[c] = lane < 16 ? (c <= r16 ? v : 0.0) : lane < 32 && c == r16 ? 1.0 : 0.0;
-        }
-        double pv = lane_value(row[0], 0), mine = 1.0;   // mine: pivot r16
+        for (int b = 0; b < 2; ++b) acc[a][b] = tps_d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            const bool ok = pv > 0.0;
-            neg |= !ok;
-            pv = ok ? pv : 1.0;
-            mine = r16 == c ? pv : mine;
-            const double inv = rcp64(pv);
-            if (c < 15) {
-                const double a = lane_value(row[c], c + 1);
-                pv = fma(-(a * inv), a, lane_value(row[c + 1], c + 1));
-            }
-            const double u = row[c] * inv;
-#pragma unroll
-            for (int e = c + 1; e < 16; ++e) row[e] = fma(-u, lane_value(row[c], e), row[e]);
-        }
-        if (kq == 1) {
-#pragma unroll
-            for (int c = 0; c < 16; ++c) T[c][r16] = row[c];
-        }
-        wave_sync();
-        const double rs = rsqrt64(mine);
-        double inv[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            inv[k] = T[r16][4 * k + kq] * rs;
-            Iv[j][r16][4 * k + kq] = inv[k];
-        }
-        const auto panel = [&](int b) {   // element (4 v + kq, r16) of block (b, j)'s transpose
-            tps_d4 x{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) x = mfma64(inv[k], S[16 * b + r16][j0 + 4 * k + kq], x);
-            return x;
-        };
-#pragma unroll 1
-        for (int b = wave, bi = j + 1, bk = j + 1;; ++bk) {   // blocks (bi, bk), j < bk <= bi, every fourth
-            if (bk > bi) bk = j + 1, ++bi;
-            if (bi == kNB / 16) break;
-            if (b-- != 0) continue;
-            b = 3;
-            const tps_d4 y = panel(bk);
-            tps_d4 z = y;
-            if (bi != bk) z = panel(bi);
-            else {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) S[j0 + r16][16 * bk + 4 * v + kq] = -y[v];
-            }
-            tps_d4 x{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) x = mfma64(z[k], y[k], x);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) S[16 * bi + kq + 4 * v][16 * bk + r16] -= x[v];
-        }
-        __syncthreads();
+    for (int c0 = 0; c0 < kNB; c0 += 4) {
+        const double x0 = Li[rb + r16][c0 + kq], x1 = Li[rb + 16 + r16][c0 + kq];
+        const double y0 = Lk[cb + r16][c0 + kq], y1 = Lk[cb + 16 + r16][c0 + kq];
+        acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y0, acc[0][0], 0, 0, 0);
+        acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y1, acc[0][1], 0, 0, 0);
+        acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y0, acc[1][0], 0, 0, 0);
+        acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y1, acc[1][1], 0, 0, 0);
     }
-    return neg;
-}
-
-// Step kb of the blocked Cholesky M22 = L L^T, one launch: the update by the
-// previous `depth` block columns (A -= L21 L21^T) and, in the same launch, block
-// column kb's factor.  M is the reduced system, lower triangle, its row n2 the
-// right-hand side z2, which the steps turn into the forward solve L^-1 z2.
-//   Workgroups 0 .. panels: the block column.  Each updates the diagonal block
-//     for itself (it is only read: no workgroup sees another's results within
-//     a launch), factors it, then updates its own kNB rows below it and solves
-//     them, X L11^T = A21, sixteen rows a wavefront: held transposed, each
-//     16 x 16 block's result is the next product's operand as it stands.
-//     Workgroup 0 solves the unit matrix instead and stores Ld = L11^-T for
-//     the backward solve.
-//   The others: one tile of the trailing update each, four wavefronts of 32 x 32.
-// The trailing matrix is updated at every second step, by two block columns at
-// once (the steps between update their own block column only): 113 us at 5,700
-// rows, where two updates by one take 88 each.  It costs as much in matrix
-// instructions (59 us) as in reading and writing that matrix (57 us), and the
-// two overlap little.  A step without it is the factor's serial chain (14 of
-// 25 us).  5,754 centres: a launch for the factor (22 us) and one for the
-// update (26 us) per 32 columns, and two (9 us) for the solves, took 12.0 ms;
-// a launch per 64 columns (a square root and a division in each column's chain)
-// and one (5.5 us) for the backward solve 4.5 ms; this 4.1 ms.  Half a block
-// column staged at a time lets three workgroups share a compute unit (two: 118
-// us); giving each XCD a compact part of the tiles changes nothing.
-// A pivot <= 0 raises *bad.
-__global__ __launch_bounds__(256, 3) void k_chol_step(int64_t ld, int64_t kb, int bs, int64_t n2, int panels, int depth,
-                                                      double* __restrict__ M, double* __restrict__ Ld,
-                                                      int* __restrict__ bad) {
-    // the staged halves of the previous block columns, then the block being factored
-    constexpr int kTile = 2 * kNB * kHS;
-    static_assert(kTile >= kNB * kLS, "the block fits the staged tiles' place");
-    __shared__ double tiles[kTile];
-    double (*Xi)[kHS] = reinterpret_cast<double (*)[kHS]>(tiles);
-    double (*Xk)[kHS] = reinterpret_cast<double (*)[kHS]>(tiles + kNB * kHS);
-    double (*S)[kLS] = reinterpret_cast<double (*)[kLS]>(tiles);
-    __shared__ double Iv[kNB / 16][16][kIS], T[16][kIS];
-    const int t = threadIdx.x, wave = t >> 6, lane = t & 63, r16 = lane & 15, kq = lane >> 4;
-    const int64_t rows = n2 + 1;
-    double vi[kTileIt], vk[kTileIt];   // the next half's tiles, in flight during a product
-    const int64_t done = kb - depth * kNB;   // first column of the update
-    if (static_cast<int>(blockIdx.x) > panels) {
-        // workgroup b -> lower-triangle tile (ti, tk), tk <= ti, b = ti (ti + 1) / 2 + tk
-        const int64_t b = static_cast<int64_t>(blockIdx.x) - panels - 1;
-        int ti = __builtin_amdgcn_readfirstlane(static_cast<int>((sqrt(8.0 * static_cast<double>(b) + 1.0) - 1.0) * 0.5));
-        while (ti * (ti + 1) / 2 > b) --ti;
-        while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
-        const int64_t i0 = kb + kNB + ti * kNB, k0 = kb + kNB + (b - ti * (ti + 1) / 2) * kNB;
-        const int rb = (wave >> 1) * 32, cb = (wave & 1) * 32;
-        // element v of block (p, q) of the wavefront's quarter: row 16 p + 4 v + rb + kq, column 16 q + cb + r16
-        double* tile = M + i0 * ld + k0;
-        const uint32_t off = static_cast<uint32_t>((rb + kq) * static_cast<int>(ld) + cb + r16);
-        const auto inside = [&](int p, int q, int v) {
-            const int i = rb + kq + 16 * p + 4 * v, k = cb + r16 + 16 * q;
-            return i0 + i < rows && k0 + k < n2 && k0 + k <= i0 + i;
-        };
-        load_tile(M, ld, i0, rows, done, vi);
-        load_tile(M, ld, k0, rows, done, vk);
-        const bool whole = i0 + kNB <= rows && k0 + kNB <= n2 && k0 < i0;
-        double old[2][2][4];
-        const auto load_old = [&](auto in) {
 #pragma unroll
-            for (int p = 0; p < 2; ++p)
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-                for (int q = 0; q < 2; ++q)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) old[p][q][v] = in(p, q, v) ? (tile + (16 * p + 4 * v) * ld + 16 * q)[off] : 0.0;
-        };
-        const auto all = [](int, int, int) { return true; };
-        if (whole) load_old(all);
-        else load_old(inside);
-        tps_d4 acc[2][2];
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int q = 0; q < 2; ++q) acc[p][q] = tps_d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
-        for (int64_t from = done; from < kb; from += kHalf) {
-            if (from > done) __syncthreads();
-            store_tile(vi, Xi);
-            store_tile(vk, Xk);
-            __syncthreads();
-            if (from + kHalf < kb) {
-                load_tile(M, ld, i0, rows, from + kHalf, vi);
-                load_tile(M, ld, k0, rows, from + kHalf, vk);
-            }
-#pragma unroll
-            for (int c0 = 0; c0 < kHalf; c0 += 4) {
-                const double x0 = Xi[rb + r16][c0 + kq], x1 = Xi[rb + 16 + r16][c0 + kq];
-                const double y0 = Xk[cb + r16][c0 + kq], y1 = Xk[cb + 16 + r16][c0 + kq];
-                acc[0][0] = mfma64(x0, y0, acc[0][0]);
-                acc[0][1] = mfma64(x0, y1, acc[0][1]);
-                acc[1][0] = mfma64(x1, y0, acc[1][0]);
-                acc[1][1] = mfma64(x1, y1, acc[1][1]);
-            }
-        }
-        const auto store = [&](auto in) {
-#pragma unroll
-            for (int p = 0; p < 2; ++p)
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (in(p, q, v)) (tile + (16 * p + 4 * v) * ld + 16 * q)[off] = old[p][q][v] - acc[p][q][v];
-        };
-        if (whole) store(all);
-        else store(inside);
-        return;
-    }
-    const bool unit = blockIdx.x == 0;
-    const int64_t r0 = kb + bs + (static_cast<int64_t>(blockIdx.x) - 1) * kNB;   // this workgroup's rows
-    // diag[q]: block 4 q + wave of the ten lower 16 x 16 blocks of the diagonal block (past the
-    // block column's end: the unit matrix); x[q]: columns 16 q .. of rows 16 wave .., transposed
-    tps_d4 diag[3], x[4];
-    int bi[3], bk[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        const int b = min(4 * q + wave, 9);
-        bi[q] = b < 1 ? 0 : b < 3 ? 1 : b < 6 ? 2 : 3;
-        bk[q] = b - bi[q] * (bi[q] + 1) / 2;
-    }
-    double own[16];
-    const auto load_block = [&](auto in, auto below) {
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
+        for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int i = 16 * bi[q] + kq + 4 * v, k = 16 * bk[q] + r16;
-                diag[q][v] = in(i, k) ? M[(kb + i) * ld + kb + k] : i == k ? 1.0 : 0.0;
+                const int64_t i = i0 + rb + 16 * a + kq + 4 * v, k = k0 + cb + 16 * b + r16;
+                if (i < n2 && k <= i) A[(o + i) * n + o + k] -= acc[a][b][v];
             }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {   // the wavefront's rows, a row at a time
-            const int i = 16 * wave + r;
-            own[r] = below(i, lane) ? M[(r0 + i) * ld + kb + lane] : unit && i == lane ? 1.0 : 0.0;
-        }
-    };
-    const bool whole = bs == kNB && r0 + kNB <= rows && !unit;
-    const auto all = [](int, int) { return true; };
-    if (whole)   // with the diagonal blocks' upper elements, which factor_block leaves out
-        load_block(all, all);
-    else
-        load_block([&](int i, int k) { return i < bs && k < bs; },
-                   [&](int i, int k) { return !unit && r0 + i < rows && k < bs; });
-    if (depth > 0) {
-        if (!unit) load_tile(M, ld, r0, rows, done, vi);
-        load_tile(M, ld, kb, kb + bs, done, vk);
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) S[16 * wave + r][lane] = own[r];
-    wave_sync();
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) x[q][v] = S[16 * wave + r16][16 * q + kq + 4 * v];
-    __syncthreads();
-#pragma unroll 1
-    for (int64_t from = done; from < kb; from += kHalf) {
-        if (!unit) store_tile(vi, Xi);
-        store_tile(vk, Xk);
-        __syncthreads();
-        if (from + kHalf < kb) {
-            if (!unit) load_tile(M, ld, r0, rows, from + kHalf, vi);
-            load_tile(M, ld, kb, kb + bs, from + kHalf, vk);
-        }
-#pragma unroll 4
-        for (int c0 = 0; c0 < kHalf; c0 += 4)
-#pragma unroll
-            for (int q = 0; q < 3; ++q) diag[q] = mfma64(-Xk[16 * bi[q] + r16][c0 + kq], Xk[16 * bk[q] + r16][c0 + kq], diag[q]);
-        if (!unit) {
-#pragma unroll 4
-            for (int c0 = 0; c0 < kHalf; c0 += 4) {
-                const double y = Xi[16 * wave + r16][c0 + kq];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) x[q] = mfma64(-Xk[16 * q + r16][c0 + kq], y, x[q]);
-            }
-        }
-        __syncthreads();   // the tiles' place takes the next half, at the end the diagonal block
-    }
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)   // the tenth block comes from waves 1..3 alike
-            S[16 * bi[q] + kq + 4 * v][16 * bk[q] + r16] = diag[q][v];
-    __syncthreads();
-    const bool neg = factor_block(S, Iv, T);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-#pragma unroll
-        for (int e = 0; e < q; ++e)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) x[q] = mfma64(S[16 * e + r16][16 * q + 4 * k + kq], x[e][k], x[q]);
-        tps_d4 y{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) y = mfma64(Iv[q][r16][4 * k + kq], x[q][k], y);
-        x[q] = y;
-    }
-    __syncthreads();   // S is read by all until here
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) S[16 * wave + r16][16 * q + kq + 4 * v] = x[q][v];
-    wave_sync();
-    double* to = unit ? Ld + kb * kNB + lane : M + r0 * ld + kb + lane;
-    const int64_t stride = unit ? kNB : ld;
-    const int left = unit || whole ? kNB : static_cast<int>(min<int64_t>(rows - r0, kNB));
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-        if (16 * wave + r < left && (unit || lane < bs)) to[(16 * wave + r) * stride] = S[16 * wave + r][lane];
-    if (unit && t == 0 && neg) *bad = 1;
 }
 
 // z = Q^T y = H_d ... H_0 y (one workgroup).
@@ -635,60 +395,85 @@ __global__ __launch_bounds__(1024) void k_tps_qty(int64_t n, int np, const doubl
     }
 }
 
-// One block of kNB rows of the backward solve L^T w = t: every workgroup forms
-// the block's w = L11^-T t from Ld (four threads a row), workgroup 0 stores
-// it, and each subtracts L[kb ..][r]^T w from kNB of the rows r above (sixteen
-// block rows a wavefront, loaded before w is formed).  The block's own
-// elements of t are only read.
-__global__ __launch_bounds__(256) void k_back_step(int64_t ld, int64_t kb, int bs, const double* __restrict__ M,
-                                                   const double* __restrict__ Ld, double* __restrict__ tv,
-                                                   double* __restrict__ w) {
-    __shared__ double wb[kNB];
-    __shared__ double part[4][kNB];
-    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    const int64_t r = static_cast<int64_t>(blockIdx.x) * kNB + lane;
-    double l[16];
-#pragma unroll
-    for (int c = 0; c < 16; ++c) l[c] = r < kb && 16 * wave + c < bs ? M[(kb + 16 * wave + c) * ld + r] : 0.0;
-    const int row = t >> 2, q = t & 3;
+// One block of kNB rows of M22 w = z2 with M22 = L L^T, forward (L t = z2)
+// or backward (L^T w = t): every workgroup solves the block's own rows in its
+// first wavefront from the factor in Ld (lane l holds element l; per row r
+// the solved value is read from lane r and subtracted from the lanes below
+// it, or above it for L^T), workgroup 0 stores them in out, and each
+// workgroup updates its slice of the remaining rows of in: forward the rows
+// below, b[r] -= L[r][kb..] x (row segments through LDS as in the Cholesky
+// step), backward the rows above, b[r] -= L[kb..][r]^T x (consecutive
+// threads on consecutive elements).  The block's own elements of in are only
+// read, so no workgroup sees another's results within a launch.
+__global__ __launch_bounds__(kPanelRows) void k_trsv_step(int64_t n, int64_t o, int64_t kb, int bs, int64_t n2,
+                                                          bool upper, const double* __restrict__ A,
+                                                          const double* __restrict__ Ld, double* __restrict__ in,
+                                                          double* __restrict__ out) {
+    __shared__ double Lb[kNB][kNB + 1];
+    __shared__ double X[kPanelRows][kNB + 1];
+    __shared__ double xb[kNB];
+    const int t = threadIdx.x;
+    stage_block<kPanelRows>(Ld + kb * kNB, kNB, bs, Lb);
+    int64_t r0 = 0;
+    int nr = 0;
+    if (!upper) {
+        r0 = kb + bs + static_cast<int64_t>(blockIdx.x) * kPanelRows;
+        nr = static_cast<int>(max<int64_t>(0, min<int64_t>(kPanelRows, n2 - r0)));
+        if (nr > 0) stage_rows(A + (o + r0) * n + o + kb, n, nr, bs, X);
+    }
+    __syncthreads();
+    if (t < 64) {   // the first wavefront
+        double x = t < bs ? in[kb + t] : 0.0;
+        if (!upper) {
+            for (int r = 0; r < bs; ++r) {
+                const double xr = lane_value(x, r) / Lb[r][r];
+                if (t == r) x = xr;
+                if (t > r && t < bs) x -= Lb[t][r] * xr;
+            }
+        } else {
+            for (int r = bs - 1; r >= 0; --r) {
+                const double xr = lane_value(x, r) / Lb[r][r];
+                if (t == r) x = xr;
+                if (t < r) x -= Lb[r][t] * xr;
+            }
+        }
+        if (t < bs) {
+            xb[t] = x;
+            if (blockIdx.x == 0) out[kb + t] = x;
+        }
+    }
+    __syncthreads();
     double s = 0.0;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {   // columns 4 j + q: the four threads of a row read one segment
-        const int c = 4 * j + q;
-        if (c < bs) s = fma(Ld[(kb + row) * kNB + c], tv[kb + c], s);
+    if (!upper) {
+        if (t < nr) {
+            for (int c = 0; c < bs; ++c) s = fma(X[t][c], xb[c], s);
+            in[r0 + t] -= s;
+        }
+    } else {
+        const int64_t r = static_cast<int64_t>(blockIdx.x) * kPanelRows + t;
+        if (r < kb) {
+            for (int c = 0; c < bs; ++c) s = fma(A[(o + kb + c) * n + o + r], xb[c], s);
+            in[r] -= s;
+        }
     }
-    s += __shfl_xor(s, 1);
-    s += __shfl_xor(s, 2);
-    if (q == 0) {
-        wb[row] = s;
-        if (blockIdx.x == 0 && row < bs) w[kb + row] = s;
-    }
-    __syncthreads();
-    double a = 0.0;
-#pragma unroll
-    for (int c = 0; c < 16; ++c) a = fma(l[c], wb[16 * wave + c], a);
-    part[wave][lane] = a;
-    __syncthreads();
-    if (wave == 0 && r < kb) tv[r] -= (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
 }
 
 // c = Q [0; w] = H_0 ... H_d [0; w] and R a = z1 - M12 w; writes c and a into
 // the fit (one workgroup).
-__global__ __launch_bounds__(1024) void k_tps_coeffs(int64_t n, int64_t ld, int np, const double* __restrict__ A,
+__global__ __launch_bounds__(1024) void k_tps_coeffs(int64_t n, int np, const double* __restrict__ A,
                                                      const double* __restrict__ V, const double* __restrict__ tau,
                                                      const double* __restrict__ R, const double* __restrict__ z,
-                                                     const double* __restrict__ w, double* __restrict__ c,
-                                                     double* __restrict__ a) {
+                                                     double* __restrict__ c, double* __restrict__ a) {
     __shared__ double red[16];
     __shared__ double rhs[kMaxDim + 1];
     const int t = threadIdx.x;
     for (int k = 0; k < np; ++k) {   // z1_k - sum_j M[k][np + j] w_j
         double s = 0.0;
-        for (int64_t j = np + t; j < n; j += blockDim.x) s = fma(A[k * ld + j], w[j - np], s);
+        for (int64_t j = np + t; j < n; j += blockDim.x) s = fma(A[k * n + j], z[j], s);
         s = block_sum(s, red);
         if (t == 0) rhs[k] = z[k] - s;
     }
-    for (int64_t i = t; i < n; i += blockDim.x) c[i] = i < np ? 0.0 : w[i - np];
+    for (int64_t i = t; i < n; i += blockDim.x) c[i] = i < np ? 0.0 : z[i];
     __syncthreads();
     for (int k = np - 1; k >= 0; --k) {
         double s = 0.0;
@@ -729,7 +514,7 @@ __global__ __launch_bounds__(256) void k_tps_eval_grid(DevProblem P, int64_t n, 
             const double s = u[j] - U[i * D + j];
             r2 = fma(s, s, r2);
         }
-        v = fma(c[i], tps_phi<D>(r2), v);
+        v = fma(c[i], tps_phi<D>(sqrt(r2)), v);
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
@@ -761,7 +546,7 @@ __global__ __launch_bounds__(1024) void k_tps_at(int64_t n, const double* __rest
             r2 = fma(s[j], s[j], r2);
         }
         const double r = sqrt(r2);
-        acc[0] = fma(c[i], tps_phi<D>(r2), acc[0]);
+        acc[0] = fma(c[i], tps_phi<D>(r), acc[0]);
         if (r == 0.0) continue;
         double p1, p2;   // phi'(r), phi''(r)
         if constexpr (D == 1) {
@@ -817,19 +602,19 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
     const int d = P.d, np = d + 1;
     const int64_t G = P.G;
     TpsFitResult res{kTpsOk, 0, hipSuccess};
-    int64_t n = 0, n2 = 0, ld = 0;
+    int64_t n = 0, n2 = 0, o = 0;
     int bad = 0;
-    char* small = nullptr;   // idx [G], n, bad flag; tau, R, T and B
-    double* big = nullptr;   // A [n ld], z [n] as its row n, V, P, Y and Z [n (d + 1)], y, w [n], Ld
+    char* small = nullptr;   // idx [G], n, bad flag; tau, R, kappa
+    double* big = nullptr;   // A [n n], V and P [n (d + 1)], y, z, p [n]
     double* fitmem = nullptr;
     int64_t* d_idx = nullptr;
     int64_t* d_n = nullptr;
     int* d_bad = nullptr;
-    double *d_tau = nullptr, *d_R = nullptr, *d_T = nullptr;
-    double *A = nullptr, *V = nullptr, *Pm = nullptr, *y = nullptr, *z = nullptr, *Y = nullptr, *Z = nullptr, *M = nullptr;
-    double *Ld = nullptr, *w = nullptr;   // inverses of the factor's diagonal blocks; the reduced system's solution
+    double *d_tau = nullptr, *d_R = nullptr, *d_kappa = nullptr;
+    double *A = nullptr, *V = nullptr, *Pm = nullptr, *y = nullptr, *z = nullptr, *pv = nullptr;
+    double *Ld = nullptr, *T = nullptr;   // diagonal blocks of the factor; the forward solve's result
     double *U = nullptr, *c = nullptr, *a = nullptr;
-    const size_t small_bytes = sizeof(int64_t) * (G + 2) + 64 + sizeof(double) * (2 * np + 3 * np * np + 8);
+    const size_t small_bytes = sizeof(int64_t) * (G + 2) + 64 + sizeof(double) * (2 * np + np * np + 8);
     if (hipMalloc(&small, small_bytes) != hipSuccess) {
         (void)hipGetLastError();
         res.code = kTpsNoMem;
@@ -840,7 +625,7 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
     d_bad = reinterpret_cast<int*>(d_n + 1);
     d_tau = reinterpret_cast<double*>(small + sizeof(int64_t) * (G + 2) + 64);
     d_R = d_tau + np;
-    d_T = d_R + np * np;
+    d_kappa = d_R + np * np;
     TPS_TRY(hipMemsetAsync(d_bad, 0, sizeof(int), s));
     hipLaunchKernelGGL(k_tps_compact, dim3(1), dim3(1024), 0, s, G, d_in, d_idx, d_n);
     TPS_TRY(hipGetLastError());
@@ -853,25 +638,21 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
     }
     {
         const size_t nn = static_cast<size_t>(n);
-        // the reduced system's rows begin on a cache line: row stride and first column in 16 doubles
-        ld = (n + 15) / 16 * 16;
-        const size_t lead = 16 - np, full = static_cast<size_t>(ld);
-        const size_t big_count = lead + (nn + 1) * full + 4 * nn * np + 2 * nn + kNB * (nn + kNB);
+        const size_t big_count = nn * nn + 2 * nn * np + 4 * nn + kNB * (nn + kNB);
         if (hipMalloc(&big, sizeof(double) * big_count) != hipSuccess ||
             hipMalloc(&fitmem, sizeof(double) * (nn * d + nn + np)) != hipSuccess) {
             (void)hipGetLastError();
             res.code = kTpsNoMem;
             goto done;
         }
-        A = big + lead;
-        z = A + nn * full;
-        V = z + full;
+        A = big;
+        V = A + nn * nn;
         Pm = V + nn * np;
-        Y = Pm + nn * np;
-        Z = Y + nn * np;
-        y = Z + nn * np;
-        w = y + nn;
-        Ld = w + nn;
+        y = Pm + nn * np;
+        z = y + nn;
+        pv = z + nn;
+        Ld = pv + nn;
+        T = Ld + kNB * (nn + kNB);
         U = fitmem;
         c = U + nn * d;
         a = c + nn;
@@ -879,41 +660,49 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
     hipLaunchKernelGGL(k_tps_points, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, P, n, d_idx, d_in,
                        U, y, Pm);
     TPS_TRY(hipGetLastError());
+    {
+        const dim3 grid(static_cast<unsigned>((n + 255) / 256), static_cast<unsigned>(n));
+        if (d == 1) hipLaunchKernelGGL(k_tps_matrix<1>, grid, dim3(256), 0, s, n, U, lam, A);
+        else if (d == 2) hipLaunchKernelGGL(k_tps_matrix<2>, grid, dim3(256), 0, s, n, U, lam, A);
+        else hipLaunchKernelGGL(k_tps_matrix<3>, grid, dim3(256), 0, s, n, U, lam, A);
+    }
+    TPS_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_tps_qr, dim3(1), dim3(1024), 0, s, n, d, Pm, V, d_tau, d_R, d_bad);
     TPS_TRY(hipGetLastError());
-    {
-        const dim3 grid(static_cast<unsigned>(n)), part(static_cast<unsigned>((n + 255) / 256), static_cast<unsigned>(n));
-        if (d == 1) hipLaunchKernelGGL(k_tps_matrix<1>, grid, dim3(256), 0, s, n, ld, U, lam, V, A, Y);
-        else if (d == 2) hipLaunchKernelGGL(k_tps_matrix<2>, grid, dim3(256), 0, s, n, ld, U, lam, V, A, Y);
-        else hipLaunchKernelGGL(k_tps_matrix<3>, grid, dim3(256), 0, s, n, ld, U, lam, V, A, Y);
+    for (int k = 0; k < np; ++k) {   // M = Q^T A Q, one reflector at a time from both sides
+        hipLaunchKernelGGL(k_tps_gemv, dim3(static_cast<unsigned>(n)), dim3(256), 0, s, n, np, k, A, V, d_tau, pv);
+        hipLaunchKernelGGL(k_tps_kappa, dim3(1), dim3(1024), 0, s, n, np, k, V, d_tau, pv, d_kappa);
+        hipLaunchKernelGGL(k_tps_rank2, dim3(static_cast<unsigned>((n + 255) / 256), static_cast<unsigned>(n)),
+                           dim3(256), 0, s, n, np, k, V, pv, d_kappa, A);
         TPS_TRY(hipGetLastError());
-        hipLaunchKernelGGL(k_tps_wy, dim3(1), dim3(1024), 0, s, n, np, V, Y, d_tau, d_T);   // M = Q^T A Q
-        hipLaunchKernelGGL(k_tps_z, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, n, np, V, Y, d_T, Z);
-        if (d == 1) hipLaunchKernelGGL(k_tps_reduce<2>, part, dim3(256), 0, s, n, ld, V, Z, A);
-        else if (d == 2) hipLaunchKernelGGL(k_tps_reduce<3>, part, dim3(256), 0, s, n, ld, V, Z, A);
-        else hipLaunchKernelGGL(k_tps_reduce<4>, part, dim3(256), 0, s, n, ld, V, Z, A);
+    }
+    o = np;
+    n2 = n - np;
+    for (int64_t kb = 0; kb < n2; kb += kNB) {   // M22 = L L^T
+        const int bs = static_cast<int>(std::min<int64_t>(kNB, n2 - kb));
+        const int64_t rest = n2 - kb - bs;
+        hipLaunchKernelGGL(k_chol_step, dim3(static_cast<unsigned>(std::max<int64_t>(1, (rest + kPanelRows - 1) / kPanelRows))),
+                           dim3(kPanelRows), 0, s, n, o, kb, bs, n2, A, Ld, d_bad);
+        if (rest > 0) {
+            const int64_t tiles = (rest + kUT - 1) / kUT;
+            hipLaunchKernelGGL(k_chol_update, dim3(static_cast<unsigned>(tiles * (tiles + 1) / 2)), dim3(256), 0, s, n,
+                               o, kb, bs, n2, A);
+        }
         TPS_TRY(hipGetLastError());
     }
     hipLaunchKernelGGL(k_tps_qty, dim3(1), dim3(1024), 0, s, n, np, V, d_tau, y, z);
-    TPS_TRY(hipGetLastError());
-    n2 = n - np;
-    M = A + np * ld + np;   // the reduced system; its row n2 is z2
-    for (int64_t kb = 0; kb < n2; kb += kNB) {   // M22 = L L^T, L t = z2
+    for (int64_t kb = 0; kb < n2; kb += kNB) {   // L t = z2: z2 = z [o, n) in, t out
         const int bs = static_cast<int>(std::min<int64_t>(kNB, n2 - kb));
-        const int64_t panels = (n2 + 1 - kb - bs + kNB - 1) / kNB;
-        const int64_t step = kb / kNB;
-        const int depth = step == 0 ? 0 : step % 2 == 0 ? 2 : 1;
-        const int64_t tiles = depth == 2 && kb + kNB < n2 ? (n2 + 1 - kb - kNB + kNB - 1) / kNB : 0;
-        hipLaunchKernelGGL(k_chol_step, dim3(static_cast<unsigned>(1 + panels + tiles * (tiles + 1) / 2)), dim3(256), 0,
-                           s, ld, kb, bs, n2, static_cast<int>(panels), depth, M, Ld, d_bad);
-        TPS_TRY(hipGetLastError());
+        const int64_t rest = n2 - kb - bs;
+        hipLaunchKernelGGL(k_trsv_step, dim3(static_cast<unsigned>(std::max<int64_t>(1, (rest + kPanelRows - 1) / kPanelRows))),
+                           dim3(kPanelRows), 0, s, n, o, kb, bs, n2, false, A, Ld, z + o, T);
     }
-    for (int64_t kb = ((n2 - 1) / kNB) * kNB; kb >= 0; kb -= kNB) {   // L^T w = t
+    for (int64_t kb = ((n2 - 1) / kNB) * kNB; kb >= 0; kb -= kNB) {   // L^T w = t: t in, w out to z [o, n)
         const int bs = static_cast<int>(std::min<int64_t>(kNB, n2 - kb));
-        hipLaunchKernelGGL(k_back_step, dim3(static_cast<unsigned>(std::max<int64_t>(1, kb / kNB))), dim3(256), 0, s, ld,
-                           kb, bs, M, Ld, z + np, w);
+        hipLaunchKernelGGL(k_trsv_step, dim3(static_cast<unsigned>(std::max<int64_t>(1, (kb + kPanelRows - 1) / kPanelRows))),
+                           dim3(kPanelRows), 0, s, n, o, kb, bs, n2, true, A, Ld, T, z + o);
     }
-    hipLaunchKernelGGL(k_tps_coeffs, dim3(1), dim3(1024), 0, s, n, ld, np, A, V, d_tau, d_R, z, w, c, a);
+    hipLaunchKernelGGL(k_tps_coeffs, dim3(1), dim3(1024), 0, s, n, np, A, V, d_tau, d_R, z, c, a);
     TPS_TRY(hipGetLastError());
     TPS_TRY(hipMemcpyAsync(&bad, d_bad, sizeof(int), hipMemcpyDeviceToHost, s));
     TPS_TRY(hipStreamSynchronize(s));
