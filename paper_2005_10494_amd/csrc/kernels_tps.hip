@@ -292,15 +292,17 @@ __global__ __launch_bounds__(kPanelRows) void k_chol_step(int64_t n, int64_t o, 
     }
     if (nr == 0) return;   // workgroup-uniform
     if (t < nr) {
+        // each solved column goes off all later ones at once: independent
+        // operations, each element's in the same order
         double x[kNB];
 #pragma unroll
-        for (int c = 0; c < kNB; ++c) {
-            if (c < bs) {
-                double s = X[t][c];
+        for (int c = 0; c < kNB; ++c) x[c] = X[t][c];
 #pragma unroll
-                for (int e = 0; e < kNB; ++e)
-                    if (e < c) s -= x[e] * L[c][e];
-                x[c] = s / L[c][c];
+        for (int e = 0; e < kNB; ++e) {
+            if (e < bs) {
+                x[e] = x[e] / L[e][e];
+#pragma unroll
+                for (int c = e + 1; c < kNB; ++c) x[c] = fma(-x[e], L[c][e], x[c]);
             }
         }
 #pragma unroll
@@ -350,10 +352,20 @@ __global__ __launch_bounds__(256) void k_chol_update(int64_t n, int64_t o, int64
             Lk[r + 8 * q][c] = vk[q];
         }
     }
-    __syncthreads();
     const int wave = t >> 6, lane = t & 63;
     const int r16 = lane & 15, kq = lane >> 4;
     const int rb = (wave >> 1) * 32, cb = (wave & 1) * 32;
+    double old[2][2][4];   // in flight during the products
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t i = i0 + rb + 16 * a + kq + 4 * v, k = k0 + cb + 16 * b + r16;
+                old[a][b][v] = i < n2 && k <= i ? A[(o + i) * n + o + k] : 0.0;
+            }
+    __syncthreads();
     tps_d4 acc[2][2];
 #pragma unroll
     for (int a = 0; a < 2; ++a)
@@ -375,7 +387,7 @@ __global__ __launch_bounds__(256) void k_chol_update(int64_t n, int64_t o, int64
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int64_t i = i0 + rb + 16 * a + kq + 4 * v, k = k0 + cb + 16 * b + r16;
-                if (i < n2 && k <= i) A[(o + i) * n + o + k] -= acc[a][b][v];
+                if (i < n2 && k <= i) A[(o + i) * n + o + k] = old[a][b][v] - acc[a][b][v];
             }
 }
 
@@ -416,6 +428,12 @@ __global__ __launch_bounds__(kPanelRows) void k_trsv_step(int64_t n, int64_t o, 
     stage_block<kPanelRows>(Ld + kb * kNB, kNB, bs, Lb);
     int64_t r0 = 0;
     int nr = 0;
+    double up[kNB];   // backward: this row's factors, in flight while the block is solved
+    const int64_t ru = static_cast<int64_t>(blockIdx.x) * kPanelRows + t;
+    if (upper) {
+#pragma unroll
+        for (int c = 0; c < kNB; ++c) up[c] = ru < kb && c < bs ? A[(o + kb + c) * n + o + ru] : 0.0;
+    }
     if (!upper) {
         r0 = kb + bs + static_cast<int64_t>(blockIdx.x) * kPanelRows;
         nr = static_cast<int>(max<int64_t>(0, min<int64_t>(kPanelRows, n2 - r0)));
@@ -450,10 +468,11 @@ __global__ __launch_bounds__(kPanelRows) void k_trsv_step(int64_t n, int64_t o, 
             in[r0 + t] -= s;
         }
     } else {
-        const int64_t r = static_cast<int64_t>(blockIdx.x) * kPanelRows + t;
-        if (r < kb) {
-            for (int c = 0; c < bs; ++c) s = fma(A[(o + kb + c) * n + o + r], xb[c], s);
-            in[r] -= s;
+        if (ru < kb) {
+#pragma unroll
+            for (int c = 0; c < kNB; ++c)
+                if (c < bs) s = fma(up[c], xb[c], s);
+            in[ru] -= s;
         }
     }
 }
