@@ -270,12 +270,12 @@ __global__ __launch_bounds__(kPanelRows) void k_chol_step(int64_t n, int64_t o, 
                 const double pv = lane_value(row[j], j);
                 neg |= !(pv > 0.0);
                 const double dj = pv > 0.0 ? sqrt(pv) : 1.0;
-                const double lrj = (t > j) ? row[j] / dj : (t == j ? dj : row[j]);
+                const double lrj = t == j ? dj : row[j] / dj;   // above the diagonal: never read
                 row[j] = lrj;
 #pragma unroll
                 for (int c = j + 1; c < kNB; ++c) {
                     const double lcj = lane_value(lrj, c);   // column j of row c
-                    if (t >= c) row[c] -= lrj * lcj;
+                    row[c] -= lrj * lcj;
                 }
             }
         }
@@ -324,16 +324,55 @@ __global__ __launch_bounds__(kPanelRows) void k_chol_step(int64_t n, int64_t o, 
 // result element v is row l / 16 + 4 v, column l % 16.
 typedef double tps_d4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void k_chol_update(int64_t n, int64_t o, int64_t kb, int bs, int64_t n2,
-                                                     double* __restrict__ A) {
+//
+// The workgroups past the tiles take the forward solve's step of block column kb
+// (L t = z2), which needs no more than the panel just factored: each solves the
+// block's own rows in its first wavefront from the factor in Ld (lane l holds
+// element l; per row r the solved value is read from lane r and subtracted from
+// the lanes below it), the first stores them in out, and each updates kUT of
+// the rows below, b[r] -= L[r][kb..] x.  In launches of their own these steps took
+// 8.6 us each, beside the tiles they take none.
+__global__ __launch_bounds__(256) void k_chol_update(int64_t n, int64_t o, int64_t kb, int bs, int64_t n2, int64_t tiles,
+                                                     double* __restrict__ A, const double* __restrict__ Ld,
+                                                     double* __restrict__ in, double* __restrict__ out) {
     const int64_t t0 = kb + bs;
+    __shared__ double Li[kUT][kNB + 1], Lk[kUT][kNB + 1];
+    if (static_cast<int64_t>(blockIdx.x) >= tiles) {
+        double* xb = Lk[kNB];   // past the factor
+        const int t = threadIdx.x, c = t % kNB, r = t / kNB;
+        const int64_t r0 = t0 + (static_cast<int64_t>(blockIdx.x) - tiles) * kUT;
+        const int nr = static_cast<int>(max<int64_t>(0, min<int64_t>(kUT, n2 - r0)));
+        stage_block<256>(Ld + kb * kNB, kNB, bs, Lk);
+#pragma unroll
+        for (int q = 0; q < kUT * kNB / 256; ++q)
+            Li[r + 8 * q][c] = r + 8 * q < nr && c < bs ? A[(o + r0 + r + 8 * q) * n + o + kb + c] : 0.0;
+        __syncthreads();
+        if (t < 64) {
+            double x = t < bs ? in[kb + t] : 0.0;
+            for (int e = 0; e < bs; ++e) {
+                const double xe = lane_value(x, e) / Lk[e][e];
+                if (t == e) x = xe;
+                if (t > e && t < bs) x -= Lk[t][e] * xe;
+            }
+            if (t < bs) {
+                xb[t] = x;
+                if (static_cast<int64_t>(blockIdx.x) == tiles) out[kb + t] = x;
+            }
+        }
+        __syncthreads();
+        if (t < nr) {
+            double s = 0.0;
+            for (int e = 0; e < bs; ++e) s = fma(Li[t][e], xb[e], s);
+            in[r0 + t] -= s;
+        }
+        return;
+    }
     // workgroup b -> lower-triangle tile (ti, tk), tk <= ti, b = ti (ti + 1) / 2 + tk
     const int64_t b = blockIdx.x;
     int64_t ti = static_cast<int64_t>((sqrt(8.0 * static_cast<double>(b) + 1.0) - 1.0) * 0.5);
     while (ti * (ti + 1) / 2 > b) --ti;
     while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
     const int64_t tk = b - ti * (ti + 1) / 2;
-    __shared__ double Li[kUT][kNB + 1], Lk[kUT][kNB + 1];
     const int t = threadIdx.x;
     const int64_t i0 = t0 + ti * kUT, k0 = t0 + tk * kUT;
     {   // thread t takes column t % kNB of rows t / kNB + 8 q; every load issued before the first LDS write
@@ -407,53 +446,32 @@ __global__ __launch_bounds__(1024) void k_tps_qty(int64_t n, int np, const doubl
     }
 }
 
-// One block of kNB rows of M22 w = z2 with M22 = L L^T, forward (L t = z2)
-// or backward (L^T w = t): every workgroup solves the block's own rows in its
-// first wavefront from the factor in Ld (lane l holds element l; per row r
-// the solved value is read from lane r and subtracted from the lanes below
-// it, or above it for L^T), workgroup 0 stores them in out, and each
-// workgroup updates its slice of the remaining rows of in: forward the rows
-// below, b[r] -= L[r][kb..] x (row segments through LDS as in the Cholesky
-// step), backward the rows above, b[r] -= L[kb..][r]^T x (consecutive
-// threads on consecutive elements).  The block's own elements of in are only
-// read, so no workgroup sees another's results within a launch.
-__global__ __launch_bounds__(kPanelRows) void k_trsv_step(int64_t n, int64_t o, int64_t kb, int bs, int64_t n2,
-                                                          bool upper, const double* __restrict__ A,
-                                                          const double* __restrict__ Ld, double* __restrict__ in,
-                                                          double* __restrict__ out) {
+// One block of kNB rows of the backward solve L^T w = t: every workgroup solves
+// the block's own rows in its first wavefront from the factor in Ld (lane l
+// holds element l; per row r the solved value is read from lane r and
+// subtracted from the lanes above it), workgroup 0 stores them in out, and
+// each workgroup updates its slice of the rows above, b[r] -= L[kb..][r]^T x
+// (consecutive threads on consecutive elements, loaded before the block is
+// solved).  The block's own elements of in are only read, so no workgroup sees
+// another's results within a launch.
+__global__ __launch_bounds__(kPanelRows) void k_trsv_step(int64_t n, int64_t o, int64_t kb, int bs,
+                                                          const double* __restrict__ A, const double* __restrict__ Ld,
+                                                          double* __restrict__ in, double* __restrict__ out) {
     __shared__ double Lb[kNB][kNB + 1];
-    __shared__ double X[kPanelRows][kNB + 1];
     __shared__ double xb[kNB];
     const int t = threadIdx.x;
     stage_block<kPanelRows>(Ld + kb * kNB, kNB, bs, Lb);
-    int64_t r0 = 0;
-    int nr = 0;
-    double up[kNB];   // backward: this row's factors, in flight while the block is solved
+    double up[kNB];
     const int64_t ru = static_cast<int64_t>(blockIdx.x) * kPanelRows + t;
-    if (upper) {
 #pragma unroll
-        for (int c = 0; c < kNB; ++c) up[c] = ru < kb && c < bs ? A[(o + kb + c) * n + o + ru] : 0.0;
-    }
-    if (!upper) {
-        r0 = kb + bs + static_cast<int64_t>(blockIdx.x) * kPanelRows;
-        nr = static_cast<int>(max<int64_t>(0, min<int64_t>(kPanelRows, n2 - r0)));
-        if (nr > 0) stage_rows(A + (o + r0) * n + o + kb, n, nr, bs, X);
-    }
+    for (int c = 0; c < kNB; ++c) up[c] = ru < kb && c < bs ? A[(o + kb + c) * n + o + ru] : 0.0;
     __syncthreads();
     if (t < 64) {   // the first wavefront
         double x = t < bs ? in[kb + t] : 0.0;
-        if (!upper) {
-            for (int r = 0; r < bs; ++r) {
-                const double xr = lane_value(x, r) / Lb[r][r];
-                if (t == r) x = xr;
-                if (t > r && t < bs) x -= Lb[t][r] * xr;
-            }
-        } else {
-            for (int r = bs - 1; r >= 0; --r) {
-                const double xr = lane_value(x, r) / Lb[r][r];
-                if (t == r) x = xr;
-                if (t < r) x -= Lb[r][t] * xr;
-            }
+        for (int r = bs - 1; r >= 0; --r) {
+            const double xr = lane_value(x, r) / Lb[r][r];
+            if (t == r) x = xr;
+            if (t < r) x -= Lb[r][t] * xr;
         }
         if (t < bs) {
             xb[t] = x;
@@ -461,19 +479,12 @@ __global__ __launch_bounds__(kPanelRows) void k_trsv_step(int64_t n, int64_t o, 
         }
     }
     __syncthreads();
-    double s = 0.0;
-    if (!upper) {
-        if (t < nr) {
-            for (int c = 0; c < bs; ++c) s = fma(X[t][c], xb[c], s);
-            in[r0 + t] -= s;
-        }
-    } else {
-        if (ru < kb) {
+    if (ru < kb) {
+        double s = 0.0;
 #pragma unroll
-            for (int c = 0; c < kNB; ++c)
-                if (c < bs) s = fma(up[c], xb[c], s);
-            in[ru] -= s;
-        }
+        for (int c = 0; c < kNB; ++c)
+            if (c < bs) s = fma(up[c], xb[c], s);
+        in[ru] -= s;
     }
 }
 
@@ -697,29 +708,21 @@ TpsFitResult tps_fit_grid(bmd_problem* p, const double* d_in, double lam, double
     }
     o = np;
     n2 = n - np;
+    hipLaunchKernelGGL(k_tps_qty, dim3(1), dim3(1024), 0, s, n, np, V, d_tau, y, z);
     for (int64_t kb = 0; kb < n2; kb += kNB) {   // M22 = L L^T
         const int bs = static_cast<int>(std::min<int64_t>(kNB, n2 - kb));
         const int64_t rest = n2 - kb - bs;
         hipLaunchKernelGGL(k_chol_step, dim3(static_cast<unsigned>(std::max<int64_t>(1, (rest + kPanelRows - 1) / kPanelRows))),
                            dim3(kPanelRows), 0, s, n, o, kb, bs, n2, A, Ld, d_bad);
-        if (rest > 0) {
-            const int64_t tiles = (rest + kUT - 1) / kUT;
-            hipLaunchKernelGGL(k_chol_update, dim3(static_cast<unsigned>(tiles * (tiles + 1) / 2)), dim3(256), 0, s, n,
-                               o, kb, bs, n2, A);
-        }
+        const int64_t side = (rest + kUT - 1) / kUT, tiles = side * (side + 1) / 2;
+        hipLaunchKernelGGL(k_chol_update, dim3(static_cast<unsigned>(tiles + std::max<int64_t>(1, side))), dim3(256), 0, s,
+                           n, o, kb, bs, n2, tiles, A, Ld, z + o, T);   // and L t = z2: z [o, n) in, t out
         TPS_TRY(hipGetLastError());
-    }
-    hipLaunchKernelGGL(k_tps_qty, dim3(1), dim3(1024), 0, s, n, np, V, d_tau, y, z);
-    for (int64_t kb = 0; kb < n2; kb += kNB) {   // L t = z2: z2 = z [o, n) in, t out
-        const int bs = static_cast<int>(std::min<int64_t>(kNB, n2 - kb));
-        const int64_t rest = n2 - kb - bs;
-        hipLaunchKernelGGL(k_trsv_step, dim3(static_cast<unsigned>(std::max<int64_t>(1, (rest + kPanelRows - 1) / kPanelRows))),
-                           dim3(kPanelRows), 0, s, n, o, kb, bs, n2, false, A, Ld, z + o, T);
     }
     for (int64_t kb = ((n2 - 1) / kNB) * kNB; kb >= 0; kb -= kNB) {   // L^T w = t: t in, w out to z [o, n)
         const int bs = static_cast<int>(std::min<int64_t>(kNB, n2 - kb));
         hipLaunchKernelGGL(k_trsv_step, dim3(static_cast<unsigned>(std::max<int64_t>(1, (kb + kPanelRows - 1) / kPanelRows))),
-                           dim3(kPanelRows), 0, s, n, o, kb, bs, n2, true, A, Ld, T, z + o);
+                           dim3(kPanelRows), 0, s, n, o, kb, bs, A, Ld, T, z + o);
     }
     hipLaunchKernelGGL(k_tps_coeffs, dim3(1), dim3(1024), 0, s, n, np, A, V, d_tau, d_R, z, c, a);
     TPS_TRY(hipGetLastError());
