@@ -848,7 +848,7 @@ def bench_two_layer(args):
                       "designs": G, "feasible_designs": feas, "n_outer": N1, "n_inner": N2},
            "roofline": {"bound": "alu", "achieved": rate, "peak": peak, "unit": "comparisons/s",
                         "frac": rate / peak, "traffic": None,
-                        "kernel": "k_two_layer<float, 3> (256 inner draws per workgroup, outer thresholds via LDS)",
+                        "kernel": "k_two_layer_bits<float, 3> (ranks of the outer thresholds among sorted inner draws)",
                         "comparisons_per_call": cmp_},
            "fp64": {"ms_per_step": 1e3 * t64, "comparisons_per_s": cmp_ / t64},
            "result": {"max_abs_fp32_fp64": float((m32 - m64)[ok].abs().max()),
