@@ -97,11 +97,11 @@ __global__ __launch_bounds__(256) void k_finalize(int64_t G, int64_t M, int n_sl
     if (mode != 0) second[g] = mode == 2 ? s2 / Md : M > 1 ? fmax(0.0, (s2 - s1 * s1 / Md) / (Md - 1.0)) : 0.0;
 }
 
-// Workgroups of whole designs leave the chip idle below 64 Ki designs; with
+// Workgroups of whole designs leave most of the chip idle below 16 Ki designs; with
 // fewer than 16 slices there is nothing to share.
 void run_finalize(int64_t G, int64_t M, int n_slices, const double* part, double* mean, double* second, int mode,
                   hipStream_t s) {
-    if (G < 65536 && n_slices >= 16)
+    if (G < 16384 && n_slices >= 16)
         hipLaunchKernelGGL(k_finalize<16>, dim3(static_cast<unsigned>((G + 15) / 16)), dim3(256), 0, s, G, M, n_slices, part,
                            mean, second, mode);
     else
