@@ -1019,18 +1019,19 @@ bmd_status bmd_argmax(bmd_problem* p, const double* d_surface, int64_t* h_index,
     return BMD_OK;
 }
 
-// The launches of a gradient call; draws_ready as launch_grad's.
-static bmd_status grad_design(bmd_problem* p, const double* d_q, int64_t B, int64_t M, int32_t prec, bool draws_ready,
+// The launches of a gradient call.  *drawn: whether the workspace holds this
+// problem's draws 0..M-1 in precision prec, before and after the call.
+static bmd_status grad_design(bmd_problem* p, const double* d_q, int64_t B, int64_t M, int32_t prec, bool* drawn,
                               double* d_obj, double* d_grad_q, double* d_grad_mu, hipStream_t s) {
-    int n_slices = 0;
-    int64_t slice_len = 0;
-    grad_slices(p, prec, B, M, &n_slices, &slice_len);
-    const size_t need = grad_workspace_bytes(p, prec, B, n_slices, M, slice_len);
-    draws_ready = draws_ready && p->d_ws && p->ws_cap >= need;   // a new workspace holds no draws
+    const GradPlan g = grad_plan(p, prec, B, M);
+    const size_t need = grad_workspace_bytes(p, prec, B, g);
+    // a new workspace holds no draws
+    const bool ready = grad_draws_ready(*drawn, g, M) && p->d_ws && p->ws_cap >= need;
+    *drawn = false;
     bmd_status st = ensure(&p->d_ws, &p->ws_cap, need);
     if (st != BMD_OK) return st;
-    HIP_TRY(launch_grad(p, prec, d_q, B, M, p->d_ws, n_slices, slice_len, draws_ready, d_obj, d_grad_q, d_grad_mu, s),
-            "gradient kernels");
+    HIP_TRY(launch_grad(p, prec, d_q, B, M, p->d_ws, g, ready, d_obj, d_grad_q, d_grad_mu, s), "gradient kernels");
+    *drawn = grad_leaves_draws(g, M);
     return BMD_OK;
 }
 
@@ -1046,7 +1047,8 @@ bmd_status bmd_grad_design(bmd_problem* p, const double* d_q, int64_t B, uint64_
         return fail(BMD_ENOTSUP, "grad_design needs the step prior and cutoff designs");
     DeviceGuard guard(p->device);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    return grad_design(p, d_q, B, static_cast<int64_t>(n_draws), prec, false, d_obj, d_grad_q, d_grad_mu, s);
+    bool drawn = false;
+    return grad_design(p, d_q, B, static_cast<int64_t>(n_draws), prec, &drawn, d_obj, d_grad_q, d_grad_mu, s);
 }
 
 namespace {
@@ -1486,11 +1488,9 @@ bmd_status bmd_refine_design(bmd_problem* p, const double* h_q0, uint64_t n_draw
     // objective and gradient at the n points of tq (host) -> tf, tg
     auto evaluate = [&](int n) -> bmd_status {
         HIP_TRY(hipMemcpyAsync(d_q, tq.data(), sizeof(double) * n * d, hipMemcpyHostToDevice, s), "refine upload");
-        // every evaluation uses the same draws: generated by the first, found by the others where
-        // one pass holds them all
-        const bmd_status st = grad_design(p, d_q, n, static_cast<int64_t>(n_draws), prec, drawn, d_f, d_g, nullptr, s);
+        // every evaluation uses the same draws: those that one made in a single pass, the next finds
+        const bmd_status st = grad_design(p, d_q, n, static_cast<int64_t>(n_draws), prec, &drawn, d_f, d_g, nullptr, s);
         if (st != BMD_OK) return st;
-        drawn = true;
         HIP_TRY(hipMemcpyAsync(tf.data(), d_f, sizeof(double) * n, hipMemcpyDeviceToHost, s), "refine download");
         HIP_TRY(hipMemcpyAsync(tg.data(), d_g, sizeof(double) * n * d, hipMemcpyDeviceToHost, s), "refine download");
         HIP_TRY(hipStreamSynchronize(s), "refine sync");

@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "bmd.h"
+#include "grad_plan.hpp"
 
 namespace bmd {
 
@@ -252,14 +253,13 @@ hipError_t launch_argmax(const double* v, int64_t n, double* part_v, int64_t* pa
 size_t smooth_local_bytes();
 hipError_t launch_smooth_local(const bmd_problem* p, const double* in, const double* q, const double* lo,
                                const double* hi, double* ws, double* out, hipStream_t s);
-size_t grad_workspace_bytes(const bmd_problem* p, int prec, int64_t B, int n_slices, int64_t M, int64_t slice_len);
-int64_t grad_pass_draws(const bmd_problem* p, int prec, int64_t M, int64_t slice_len);
-void grad_slices(bmd_problem* p, int prec, int64_t B, int64_t M, int* n_slices, int64_t* slice_len);
-// draws_ready: the workspace still holds this problem's draws 0..M-1 in precision
-// prec from an earlier call on the same M (used when one pass holds them all).
+// Slices and passes of a gradient call (grad_plan.hpp).
+GradPlan grad_plan(const bmd_problem* p, int prec, int64_t B, int64_t M);
+size_t grad_workspace_bytes(const bmd_problem* p, int prec, int64_t B, const GradPlan& g);
+// draws_ready: the workspace holds this problem's draws 0..M-1 in precision prec
+// (grad_draws_ready).
 hipError_t launch_grad(const bmd_problem* p, int prec, const double* d_q, int64_t B, int64_t M, void* ws,
-                       int n_slices, int64_t slice_len, bool draws_ready, double* obj, double* gq, double* gmu,
-                       hipStream_t s);
+                       const GradPlan& g, bool draws_ready, double* obj, double* gq, double* gmu, hipStream_t s);
 // Draws with the node table draw-minor, B[m][j][M], for the gradient kernel.
 hipError_t launch_grad_draws(const bmd_problem* p, int prec, uint64_t k0, int64_t M, void* ws, hipStream_t s);
 // Batched form.  Sweep records are filled on the host (batch_record_bytes, the

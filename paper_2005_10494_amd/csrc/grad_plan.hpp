@@ -1,0 +1,40 @@
+// How a gradient call over B points and M draws splits its draws: slices (a
+// workgroup takes one slice of draws and one row of points), and passes (whole
+// slices whose draws are in device memory together).  Host arithmetic only.
+#pragma once
+#include <algorithm>
+#include <cstddef>
+#include <cstdint>
+
+namespace bmd {
+
+struct GradPlan {
+    int64_t n_slices, slice_len;
+    int64_t pass;   // draws of a pass: M, or whole slices
+};
+
+// groups: rows of points; step: draws a workgroup has in flight (slices are whole
+// steps); resident: workgroups the chip holds at once; rounds of them the call
+// is cut into; per_draw: bytes of a draw; budget: bytes of a pass.
+inline GradPlan grad_plan_of(int64_t groups, int64_t step, int64_t resident, int64_t rounds, int64_t M, double per_draw,
+                             size_t budget) {
+    int64_t n = (rounds * resident + groups - 1) / groups;
+    n = std::max<int64_t>(1, std::min<int64_t>({n, (M + step - 1) / step, 65528}));
+    if (n >= 8) n = (n + 7) / 8 * 8;   // the XCDs take slices in turn
+    int64_t len = (M + n - 1) / n;
+    len = (len + step - 1) / step * step;
+    int64_t slices = static_cast<int64_t>(static_cast<double>(budget) / (per_draw * static_cast<double>(len)));
+    // the kernel addresses a pass's draws with 32-bit byte offsets
+    slices = std::max<int64_t>(1, std::min(slices, (int64_t(1) << 28) / len));
+    return {(M + len - 1) / len, len, std::min(M, slices * len)};
+}
+
+// Whether a call of plan g may read the draws that the call before it on the
+// same M left: only if that call made all of them in one pass (`left`), and only
+// in a single pass of its own.  Two calls of different point counts have slices of
+// different lengths, hence passes of different lengths: one may need several passes
+// (and leave the last, laid out for its own length) where the other needs one.
+inline bool grad_draws_ready(bool left, const GradPlan& g, int64_t M) { return left && g.pass >= M; }
+inline bool grad_leaves_draws(const GradPlan& g, int64_t M) { return g.pass >= M; }
+
+}  // namespace bmd

@@ -370,7 +370,7 @@ __global__ __launch_bounds__(kGradThreads, sizeof(T) == 8 ? 3 : 1) void k_grad(G
                 if constexpr (kSplit) V[p][0] = T(-1);
             }
         } else {
-            // node rows by a uniform base and the lane's byte offset (grad_pass_draws keeps it
+            // node rows by a uniform base and the lane's byte offset (grad_plan_of keeps it
             // below 2^32); the next block of nodes is in flight while one is used
             constexpr int NB = kGradNodeBlock<T>;
             const uint32_t off = static_cast<uint32_t>(kk) * static_cast<uint32_t>(sizeof(T));
@@ -567,8 +567,8 @@ hipError_t launch_grad_typed(GradArgs<T> ga, const double* info, const T* rec, c
 }
 
 template <typename T>
-hipError_t run_grad(const bmd_problem* p, int prec, const double* d_q, int64_t B, int64_t M, char* ws, int n_slices,
-                    int64_t slice_len, bool draws_ready, double* info, double* part, T* rec, T* AD, hipStream_t s) {
+hipError_t run_grad(const bmd_problem* p, int prec, const double* d_q, int64_t B, int64_t M, char* ws, const GradPlan& g,
+                    bool draws_ready, double* info, double* part, T* rec, T* AD, hipStream_t s) {
     const int d = p->P.d, K = p->tab[prec].K;
     const int per = B > kGradWidePoints ? 16 : 4;   // points per workgroup of 256: 16 or 64 lanes each
     for (int64_t b0 = 0; b0 < B; b0 += per * kGradGrid) {
@@ -589,12 +589,11 @@ hipError_t run_grad(const bmd_problem* p, int prec, const double* d_q, int64_t B
     }
     hipError_t e = hipGetLastError();
     // Passes over the draws: generate a pass into HBM, then the slices it holds.
-    const int64_t pass = grad_pass_draws(p, prec, M, slice_len);
-    for (int64_t k0 = 0; k0 < M && e == hipSuccess; k0 += pass) {
-        const int64_t np = std::min<int64_t>(pass, M - k0);
-        if (!(draws_ready && pass >= M)) e = launch_grad_draws(p, prec, static_cast<uint64_t>(k0), np, ws, s);
+    for (int64_t k0 = 0; k0 < M && e == hipSuccess; k0 += g.pass) {
+        const int64_t np = std::min<int64_t>(g.pass, M - k0);
+        if (!draws_ready) e = launch_grad_draws(p, prec, static_cast<uint64_t>(k0), np, ws, s);
         if (e != hipSuccess) return e;
-        GradArgs<T> ga{p->P, B, M, K, slice_len, k0 / slice_len, (np + slice_len - 1) / slice_len,
+        GradArgs<T> ga{p->P, B, M, K, g.slice_len, k0 / g.slice_len, (np + g.slice_len - 1) / g.slice_len,
                        0, 0, 1, false, k0, part};
         DrawArrays<T> D;
         if constexpr (sizeof(T) == 8) D = draws_fp64_at(p, np, ws);
@@ -606,21 +605,6 @@ hipError_t run_grad(const bmd_problem* p, int prec, const double* d_q, int64_t B
 
 }  // namespace
 
-// Draws held in HBM per pass: whole slices, at most kGradDrawBudget bytes
-// (BMD_GRAD_BUDGET, in bytes, overrides it; small values force many passes).
-int64_t grad_pass_draws(const bmd_problem* p, int prec, int64_t M, int64_t slice_len) {
-    size_t budget = kGradDrawBudget;
-    if (const char* env = std::getenv("BMD_GRAD_BUDGET")) {
-        const long long v = std::atoll(env);
-        if (v > 0) budget = static_cast<size_t>(v);
-    }
-    const double per = static_cast<double>(draw_workspace_bytes(p, prec, 1 << 20)) / (1 << 20);
-    int64_t slices = static_cast<int64_t>(static_cast<double>(budget) / (per * slice_len));
-    // the kernel addresses a pass's draws with 32-bit byte offsets
-    slices = std::max<int64_t>(1, std::min(slices, (int64_t(1) << 28) / slice_len));
-    return std::min<int64_t>(M, slices * slice_len);
-}
-
 static size_t al256(size_t x) { return (x + 255) / 256 * 256; }
 static size_t rec_bytes(int prec, int64_t B) {
     return prec == BMD_FP64 ? sizeof(double) * kRecSize<double> * B : sizeof(float) * kRecSize<float> * B;
@@ -629,40 +613,42 @@ static size_t rec_bytes(int prec, int64_t B) {
 // Layout: the draws of a pass first (so that a later call on the same draws
 // finds them whatever its point count), then the points' records and tables,
 // then the partial sums.
-size_t grad_workspace_bytes(const bmd_problem* p, int prec, int64_t B, int n_slices, int64_t M, int64_t slice_len) {
+size_t grad_workspace_bytes(const bmd_problem* p, int prec, int64_t B, const GradPlan& g) {
     const size_t T = prec == BMD_FP64 ? 8 : 4;
     const int d = p->P.d, K = p->tab[prec].K;
-    return al256(draw_workspace_bytes(p, prec, grad_pass_draws(p, prec, M, slice_len))) +
+    return al256(draw_workspace_bytes(p, prec, g.pass)) +
            al256(sizeof(double) * kInfoFields * B) + al256(rec_bytes(prec, B)) + al256(2 * T * d * K * B) +
-           al256(sizeof(double) * (d + 3) * B * n_slices);
+           al256(sizeof(double) * (d + 3) * B * g.n_slices);
 }
 
 // Draw slices of a call: about kSweepRounds rounds of resident workgroups over
-// the point groups, whole workgroups of draws.
-void grad_slices(bmd_problem* p, int prec, int64_t B, int64_t M, int* n_slices_out, int64_t* slice_len_out) {
+// the point groups, whole workgroups of draws.  Draws held in HBM per pass: whole
+// slices, at most kGradDrawBudget bytes (BMD_GRAD_BUDGET, in bytes, overrides it;
+// small values force many passes).
+GradPlan grad_plan(const bmd_problem* p, int prec, int64_t B, int64_t M) {
     const void* f = prec == BMD_FP64 ? grad_kernel<double, kGradPoints>(p->P.d) : grad_kernel<float, kGradPoints>(p->P.d);
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kGradThreads, 0) != hipSuccess || nb < 1) {
         (void)hipGetLastError();
         nb = 1;
     }
-    const int64_t groups = grad_groups(B), draws = kGradThreads / grad_point_waves(B);   // draws in flight
-    int64_t n_slices = (static_cast<int64_t>(kSweepRounds) * p->n_cu * nb + groups - 1) / groups;
-    n_slices = std::max<int64_t>(1, std::min<int64_t>({n_slices, (M + draws - 1) / draws, 65528}));
-    if (n_slices >= 8) n_slices = (n_slices + 7) / 8 * 8;   // the XCDs take slices in turn
-    int64_t slice_len = (M + n_slices - 1) / n_slices;
-    slice_len = (slice_len + draws - 1) / draws * draws;
-    *n_slices_out = static_cast<int>((M + slice_len - 1) / slice_len);
-    *slice_len_out = slice_len;
+    size_t budget = kGradDrawBudget;
+    if (const char* env = std::getenv("BMD_GRAD_BUDGET")) {
+        const long long v = std::atoll(env);
+        if (v > 0) budget = static_cast<size_t>(v);
+    }
+    const double per = static_cast<double>(draw_workspace_bytes(p, prec, 1 << 20)) / (1 << 20);
+    return grad_plan_of(grad_groups(B), kGradThreads / grad_point_waves(B), static_cast<int64_t>(p->n_cu) * nb,
+                        kSweepRounds, M, per, budget);
 }
 
 hipError_t launch_grad(const bmd_problem* p, int prec, const double* d_q, int64_t B, int64_t M, void* ws,
-                       int n_slices, int64_t slice_len, bool draws_ready, double* obj, double* gq, double* gmu,
-                       hipStream_t s) {
+                       const GradPlan& g, bool draws_ready, double* obj, double* gq, double* gmu, hipStream_t s) {
     const size_t T = prec == BMD_FP64 ? 8 : 4;
     const int d = p->P.d, K = p->tab[prec].K;
     char* base = static_cast<char*>(ws);
-    char* c = base + al256(draw_workspace_bytes(p, prec, grad_pass_draws(p, prec, M, slice_len)));
+    const int n_slices = static_cast<int>(g.n_slices);
+    char* c = base + al256(draw_workspace_bytes(p, prec, g.pass));
     auto take = [&](size_t bytes) {
         char* at = c;
         c += al256(bytes);
@@ -674,10 +660,10 @@ hipError_t launch_grad(const bmd_problem* p, int prec, const double* d_q, int64_
     double* part = reinterpret_cast<double*>(take(sizeof(double) * (d + 3) * B * n_slices));
     hipError_t e;
     if (prec == BMD_FP64)
-        e = run_grad<double>(p, prec, d_q, B, M, base, n_slices, slice_len, draws_ready, info, part,
+        e = run_grad<double>(p, prec, d_q, B, M, base, g, draws_ready, info, part,
                              reinterpret_cast<double*>(rec), reinterpret_cast<double*>(AD), s);
     else
-        e = run_grad<float>(p, prec, d_q, B, M, base, n_slices, slice_len, draws_ready, info, part,
+        e = run_grad<float>(p, prec, d_q, B, M, base, g, draws_ready, info, part,
                             reinterpret_cast<float*>(rec), reinterpret_cast<float*>(AD), s);
     if (e != hipSuccess) return e;
     // one thread per point walking the slices is a serial chain of loads: few
