@@ -277,8 +277,9 @@ bmd_status bmd_argmax(bmd_problem *p, const double *d_surface, int64_t *h_index,
  *   d_grad_q  [B*d] d obj_b / d q_b,j (may be NULL)
  *   d_grad_mu [B*2] d obj_b / d (mu_b0, mu_b1) (may be NULL)
  * Draws are generated into the problem's workspace in passes of at most 4 GB
- * (environment variable BMD_GRAD_BUDGET, in bytes, overrides the limit) and
- * read by every point; results do not depend on the pass size.  Works on grid
+ * (environment variable BMD_GRAD_BUDGET, in bytes, overrides the limit; a pass
+ * holds at least one slice of the sums) and read by every point; results do not
+ * depend on the pass size.  Works on grid
  * and continuous problems; requires BMD_EFFECT_STEP and BMD_DESIGN_CUTOFFS
  * (ENOTSUP otherwise). */
 bmd_status bmd_grad_design(bmd_problem *p, const double *d_q, int64_t B, uint64_t n_draws,

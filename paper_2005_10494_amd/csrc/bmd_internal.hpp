@@ -24,7 +24,6 @@ constexpr int kSweepRounds = 8;      // rounds of resident workgroups a grid swe
 // the L2 of an XCD (4 MB) has to hold while the tiles re-read it.
 constexpr int64_t kSliceBytes = 2 << 20;
 constexpr size_t kBatchBudget = size_t(96) << 30;   // draw bytes one batch group may hold
-constexpr size_t kGradDrawBudget = size_t(4) << 30; // draw bytes one gradient pass may hold
 
 // Problem constants passed by value to every kernel.
 struct DevProblem {

@@ -8,6 +8,9 @@
 
 namespace bmd {
 
+constexpr size_t kGradDrawBudget = size_t(4) << 30;        // bytes of draws that a pass may hold
+constexpr int64_t kGradPassDraws = int64_t(1) << 28;       // draws of a pass: the kernel's byte offsets have 32 bits
+
 struct GradPlan {
     int64_t n_slices, slice_len;
     int64_t pass;   // draws of a pass: M, or whole slices
@@ -16,16 +19,22 @@ struct GradPlan {
 // groups: rows of points; step: draws a workgroup has in flight (slices are whole
 // steps); resident: workgroups the chip holds at once; rounds of them the call
 // is cut into; per_draw: bytes of a draw; budget: bytes of a pass.
+// Many groups fill the chip by themselves and would take few, long slices, so a
+// slice is also bounded by what one pass may hold: by kGradDrawBudget whatever
+// `budget` is, so that the slices, and with them the order of the sums, do not
+// depend on it (a budget below one slice holds one slice).
 inline GradPlan grad_plan_of(int64_t groups, int64_t step, int64_t resident, int64_t rounds, int64_t M, double per_draw,
                              size_t budget) {
+    const int64_t fits = static_cast<int64_t>(static_cast<double>(kGradDrawBudget) / per_draw);
+    const int64_t longest = std::max<int64_t>(1, std::min(fits, kGradPassDraws) / step) * step;
     int64_t n = (rounds * resident + groups - 1) / groups;
     n = std::max<int64_t>(1, std::min<int64_t>({n, (M + step - 1) / step, 65528}));
+    n = std::max(n, (M + longest - 1) / longest);
     if (n >= 8) n = (n + 7) / 8 * 8;   // the XCDs take slices in turn
     int64_t len = (M + n - 1) / n;
-    len = (len + step - 1) / step * step;
+    len = (len + step - 1) / step * step;   // at most `longest`, itself whole steps
     int64_t slices = static_cast<int64_t>(static_cast<double>(budget) / (per_draw * static_cast<double>(len)));
-    // the kernel addresses a pass's draws with 32-bit byte offsets
-    slices = std::max<int64_t>(1, std::min(slices, (int64_t(1) << 28) / len));
+    slices = std::max<int64_t>(1, std::min(slices, kGradPassDraws / len));
     return {(M + len - 1) / len, len, std::min(M, slices * len)};
 }
 

@@ -1,6 +1,7 @@
 """Slices and passes of a gradient call (csrc/grad_plan.hpp, host arithmetic,
 compiled here by itself): a refinement's evaluations never read draws that the
-workspace does not hold."""
+workspace does not hold, and no pass outgrows its memory or the kernel's 32-bit
+byte offsets."""
 import os
 import subprocess
 
@@ -48,3 +49,40 @@ def test_refinement_reuses_only_draws_that_are_there(tmp_path, budget):
                 }
     std::printf("%%ld %%ld %%ld\\n", bad, met, reused);""" % (budget, budget, budget))
     assert bad == 0 and met > 0 and reused > 0
+
+
+def test_passes_stay_within_their_bounds(tmp_path):
+    """Over point groups, draw counts, draw sizes and budgets: the slices cover the
+    draws; a pass holds whole slices, at most 2^28 draws (byte offsets below 2^32 at
+    8 bytes a draw and row need 2^29) and at most the default budget where that is the
+    budget; the slices do not depend on the budget; and a call whose slices fit
+    anyway (counted) keeps those it had without the bound."""
+    bad, kept, cut = _run(tmp_path, """
+    long bad = 0, kept = 0, cut = 0;
+    for (int64_t groups : {1L, 2L, 257L, 512L, 1125L, 6200L, 8192L, 131072L, 1L << 22})
+        for (int64_t step : {64L, 128L, 256L})
+            for (int64_t resident : {1L, 256L, 768L})
+                for (double per : {84.0, 148.0, 1144.0, 6300.0})
+                    for (double m = 1; m < 1.2e12; m *= 1.9) {
+                        const int64_t M = std::min<int64_t>(static_cast<int64_t>(m), 1L << 40);
+                        const GradPlan g = grad_plan_of(groups, step, resident, 8, M, per, kGradDrawBudget);
+                        bad += g.slice_len % step != 0 || g.n_slices * g.slice_len < M || (g.n_slices - 1) * g.slice_len >= M;
+                        bad += g.pass < 1 || (g.pass < M && g.pass % g.slice_len != 0) || g.pass > kGradPassDraws;
+                        bad += (g.pass + g.slice_len - 1) / g.slice_len > 65535;
+                        bad += static_cast<double>(g.pass) * per > static_cast<double>(kGradDrawBudget);
+                        for (size_t budget : {size_t(1), size_t(1) << 24, size_t(200) << 30}) {
+                            const GradPlan o = grad_plan_of(groups, step, resident, 8, M, per, budget);
+                            bad += o.slice_len != g.slice_len || o.n_slices != g.n_slices || o.pass > kGradPassDraws;
+                            bad += (o.pass + o.slice_len - 1) / o.slice_len > 65535;
+                            bad += static_cast<double>(o.pass) * per > std::max<double>(budget, o.slice_len * per);
+                        }
+                        int64_t n = (8 * resident + groups - 1) / groups;
+                        n = std::max<int64_t>(1, std::min<int64_t>({n, (M + step - 1) / step, 65528}));
+                        if (n >= 8) n = (n + 7) / 8 * 8;
+                        const int64_t len = ((M + n - 1) / n + step - 1) / step * step;
+                        const bool fits = len <= kGradPassDraws && len * per <= static_cast<double>(kGradDrawBudget);
+                        if (fits) bad += len != g.slice_len;
+                        (fits ? kept : cut) += 1;
+                    }
+    std::printf("%ld %ld %ld\\n", bad, kept, cut);""")
+    assert bad == 0 and kept > 0 and cut > 0
