@@ -14,8 +14,9 @@ namespace bmd {
 // is summed through n = 5 as a polynomial in u whose coefficients are
 // polynomials in v; the first term left out is below 6e-18.  Beyond the last
 // cell (x = 8.5, Phi = 1 to rounding) its density is taken as 0.  Absolute
-// error 1.2e-16 (the integrands subtract Phi from 1, so the tail's relative
-// error does not matter).  Why a table: the library's erfc costs 346 SIMD
+// error 1.2e-16: enough where Phi, or an integral of it, is subtracted from 1,
+// but not where Phi is a factor of the result (the derivatives: density_cdf).
+// Why a table: the library's erfc costs 346 SIMD
 // cycles a wavefront, this 22 operations of four to five and one 16-byte LDS
 // read; without a division or an exponential there is nothing left to branch
 // on.  A cell of 1/64 needs two polynomial terms fewer than 1/32 and keeps the

@@ -13,6 +13,7 @@
 
 #include "cdf_table.hpp"
 #include "exp2_fit.hpp"
+#include "mills_fit.hpp"
 #include "normal_cdf_fit.hpp"
 
 namespace bmd {
@@ -132,6 +133,31 @@ __device__ __forceinline__ double exp2_fast(double t) {
 #pragma unroll
     for (int i = kExp2Deg - 1; i >= 0; --i) p = fma(p, f, kExp2Fit[i]);
     return __builtin_amdgcn_ldexp(p, static_cast<int>(n));
+}
+
+// Mills' ratio M(y) = (1 - Phi(y))/phi(y), y >= 0, by the fit of mills_fit.hpp (4e-16
+// relative); the reciprocal by two Newton steps.
+__device__ __forceinline__ double mills(double y) {
+    const double a = fmin(y, 1e9) + kMillsK;
+    double r = __builtin_amdgcn_rcp(a);
+    r = fma(r, fma(-a, r, 1.0), r);
+    r = fma(r, fma(-a, r, 1.0), r);
+    const double s = fma(-2.0 * kMillsK, r, 1.0);
+    double p = kMillsFit[kMillsDeg];
+#pragma unroll
+    for (int i = kMillsDeg - 1; i >= 0; --i) p = fma(p, s, kMillsFit[i]);
+    return r * p;
+}
+
+// A density times Phi(x) with every digit of the lower tail, joint being the
+// density times phi(x): joint M(-x), or what is left of the density.  Phi from the
+// table below (absolute error 1.2e-16) has few digits there, 4e-11 relative at -5
+// and 2e-2 at -8, and the library's erfc costs 346 SIMD cycles a wavefront where this
+// takes 35 operations (a gradient call of one biomarker, 4,096 points x 200,000 draws:
+// 16.4 ms with erfc, 14.2 here).
+__device__ __forceinline__ double density_cdf(double density, double joint, double x) {
+    const double v = joint * mills(fabs(x));
+    return x < 0.0 ? v : density - v;
 }
 
 // Fill a workgroup's table of cdf_table.hpp (every thread of the block calls it;

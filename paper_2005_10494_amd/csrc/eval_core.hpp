@@ -130,8 +130,17 @@ template <typename T, int D, int NMAX>
 __device__ __forceinline__ T dalpha_term(const DevProblem& P, const DesignState<T, D, NMAX>& s, T h, T kq,
                                          const NormCdf<T>& cdf) {
     if (P.zinf & 2) return s.da1 * gauss_factor(h);
-    const T ph = gauss_factor(h) * cdf(fma(kq, s.is, -s.rs * h));
-    const T pk = gauss_factor(kq) * cdf(fma(h, s.is, -s.rs * kq));
+    const T u = fma(kq, s.is, -s.rs * h), v = fma(h, s.is, -s.rs * kq);
+    T ph = gauss_factor(h), pk = gauss_factor(kq);
+    if constexpr (sizeof(T) == 8) {
+        // phi(h) phi(u) = phi(k) phi(v), here without one of its 1/sqrt(2 pi) as well
+        const T joint = 0.39894228040143267794 * exp2_fast(fma(h, h, u * u) * -0.72134752044448170368);
+        ph = density_cdf(ph, joint, u);
+        pk = density_cdf(pk, joint, v);
+    } else {
+        ph *= cdf(u);
+        pk *= cdf(v);
+    }
     return fma(s.da1, ph, s.da2 * pk);
 }
 

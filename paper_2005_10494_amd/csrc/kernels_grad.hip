@@ -293,9 +293,10 @@ struct GradArgs {
 // Measured, d = 5: 2,048 points x 500,000 draws FP32 a call of 35.1 -> 27.4 ms; 8 points x
 // 200,000 draws FP64 1,056 -> 260 us.
 // FP64 is held to 168 registers, three wavefronts per SIMD (a refinement call 2.00 ->
-// 1.90 ms against two).
+// 1.90 ms against two); six biomarkers, which would spill 276 bytes a thread,
+// take two (256 points x 50,000 draws: 2.50 -> 1.62 ms).
 template <typename T, int D, int PP>
-__global__ __launch_bounds__(kGradThreads, sizeof(T) == 8 ? 3 : 1) void k_grad(GradArgs<T> a, const double* __restrict__ info,
+__global__ __launch_bounds__(kGradThreads, sizeof(T) == 8 ? (D == 6 ? 2 : 3) : 1) void k_grad(GradArgs<T> a, const double* __restrict__ info,
                                                        const T* __restrict__ rec, const T* __restrict__ AD,
                                                        const T* __restrict__ glw, DrawArrays<T> Dr) {
     constexpr int NMAX = kGradNmax<T>;
@@ -433,10 +434,21 @@ __global__ __launch_bounds__(kGradThreads, sizeof(T) == 8 ? 3 : 1) void k_grad(G
             if (P.zinf == 0) {
                 const BvnView<T> bc{f + kRecHead, f + kRecHead + NMAX, f[kScale]};
                 pc = bvn_cdf<NMAX>(h, kq, bc, w, n, cdf);
-                ph = norm_pdf_fast(h) * cdf((kq - rhoT * h) * isig);
-                pk = norm_pdf_fast(kq) * cdf((h - rhoT * kq) * isig);
-                const T e = (h * h - T(2) * rhoT * h * kq + kq * kq) * isig * isig;
-                pr = expT(-T(0.5) * e) * isig * T(0.15915494309189533577);
+                const T u = (kq - rhoT * h) * isig, v = (h - rhoT * kq) * isig;
+                ph = norm_pdf_fast(h);
+                pk = norm_pdf_fast(kq);
+                if constexpr (sizeof(T) == 8) {
+                    // phi(h) phi(u) = phi(k) phi(v): also the joint density without 1/sqrt(1 - rho^2)
+                    const T joint = T(0.15915494309189533577) * expT(-T(0.5) * fma(h, h, u * u));
+                    ph = density_cdf(ph, joint, u);
+                    pk = density_cdf(pk, joint, v);
+                    pr = joint * isig;
+                } else {
+                    ph *= cdf(u);
+                    pk *= cdf(v);
+                    const T e = (h * h - T(2) * rhoT * h * kq + kq * kq) * isig * isig;
+                    pr = expT(-T(0.5) * e) * isig * T(0.15915494309189533577);
+                }
             } else if (P.zinf == 2) {
                 pc = cdf(h); ph = norm_pdf_fast(h); pk = T(0); pr = T(0);
             } else if (P.zinf == 1) {
