@@ -166,14 +166,26 @@ __device__ __forceinline__ void cdf_table_fill(CdfCell* t) {
     for (int j = threadIdx.x; j < kCdfCells; j += blockDim.x) t[j] = cdf_cell(j);
 }
 
+// Keep a wave-uniform FP32 value in a vector register: a multiply-add takes 2.5 SIMD
+// cycles a wavefront from vector registers or a literal, 4.4 with a scalar
+// register operand.  It also takes the value out of the compiler's sight, so only
+// kernels that gain call it: the matrix-core sweep's sums from three biomarkers on
+// (11^5 designs x 6,000 draws 2.30 -> 2.21 ms; with squares only these five, 2.33 ->
+// 2.25, where six lose, 2.18 -> 2.39) and the kernels of three and four
+// populations (97 x 97 levels x 100,000 draws 13.65 -> 13.51).  The
+// one-design-per-thread sweeps took 14 to 30 registers more (logistic cutoffs, two to
+// six biomarkers: 2.78, 9.3, 6.7, 8.9, 8.5 ms against 1.47, 7.0, 5.9, 6.9, 7.0).
+__device__ __forceinline__ void pin_vector(float& v) { asm volatile("" : "+v"(v)); }
+
 // Where an integrand's Phi comes from: the FP32 fit, the FP64 table in LDS, or
 // (setup kernels) the library.
 template <typename T>
 struct NormCdf;
 template <>
 struct NormCdf<float> {
-    float shift = kPhiShift;   // in a vector register: |x| + shift cannot take a literal, and a scalar costs twice
-    __device__ explicit NormCdf(const CdfCell*) { asm volatile("" : "+v"(shift)); }
+    float shift = kPhiShift;
+    __device__ explicit NormCdf(const CdfCell*) {}
+    __device__ __forceinline__ void pin() { pin_vector(shift); }
     __device__ __forceinline__ float operator()(float x) const { return norm_cdf(x); }
     __device__ __forceinline__ float scaled(float xs) const { return norm_cdf_scaled(xs, shift); }   // xs = x sqrt(log2(e)/2)
 };
@@ -278,10 +290,8 @@ struct BvnView {
     T scale;
 };
 
-// The pair weights of a wavefront's rule, read once per design: FP64 in scalar
-// registers (an FP64 operation costs the same with a scalar operand), FP32 in
-// vector registers (an FP32 multiply-add takes 2.5 SIMD cycles a wavefront
-// from vector registers or a literal, 4.4 with a scalar register operand).
+// The pair weights of a wavefront's rule, read once per design into scalar
+// registers.
 template <typename T, int NMAX>
 struct BvnWeights {
     T w[NMAX / 2];
@@ -289,14 +299,16 @@ struct BvnWeights {
 #pragma unroll
         for (int i = 0; i < NMAX / 2; ++i) {
             T v = 2 * i < n ? src[i] : T(0);
-            if constexpr (sizeof(T) == 8) {
+            if constexpr (sizeof(T) == 8)
                 v = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
                                      __builtin_amdgcn_readfirstlane(__double2loint(v)));
-            } else {
-                asm volatile("" : "+v"(v));   // a vector register
-            }
             w[i] = v;
         }
+    }
+    // FP32: into vector registers (see pin_vector).
+    __device__ __forceinline__ void pin() {
+#pragma unroll
+        for (int i = 0; i < NMAX / 2; ++i) pin_vector(w[i]);
     }
     __device__ __forceinline__ T operator[](int i) const { return w[i]; }
 };

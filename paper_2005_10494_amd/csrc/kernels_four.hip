@@ -93,7 +93,8 @@ __global__ __launch_bounds__(kEvalBlock) void k_eval_four(FourArgs<T> a) {
         panel_points_fill(pts, a.gl);
         __syncthreads();
     }
-    const NormCdf<T> cdf(cells);
+    NormCdf<T> cdf(cells);
+    if constexpr (sizeof(T) == 4) cdf.pin();
     const int64_t idx = static_cast<int64_t>(blockIdx.x) * kEvalBlock + threadIdx.x;
     const bool valid = idx < a.G;
     // idle lanes shadow the last design of the order

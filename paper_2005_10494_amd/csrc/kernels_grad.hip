@@ -319,7 +319,8 @@ __global__ __launch_bounds__(kGradThreads, sizeof(T) == 8 ? (D == 6 ? 2 : 3) : 1
         cdf_table_fill(cells);
         __syncthreads();
     }
-    const NormCdf<T> cdf(cells);
+    NormCdf<T> cdf(cells);
+    if constexpr (sizeof(T) == 4) cdf.pin();
     const DevProblem& P = a.P;
     const int K = a.K;
     const T sI = static_cast<T>(P.sqrtI);

@@ -126,7 +126,8 @@ __global__ __launch_bounds__(kEvalBlock) void k_eval_nested4(Nested4Args<T> a) {
         panel_points_fill(pts, a.gl);
         __syncthreads();
     }
-    const NormCdf<T> cdf(cells);
+    NormCdf<T> cdf(cells);
+    if constexpr (sizeof(T) == 4) cdf.pin();
     const int64_t G = a.P.G;
     const int64_t idx = static_cast<int64_t>(blockIdx.y) * kEvalBlock + threadIdx.x;
     const bool valid = idx < G;

@@ -52,8 +52,8 @@ __device__ __forceinline__ void direct_body(const EvalArgs<T>& a, int64_t bx, in
     const int64_t kb = static_cast<int64_t>(slice) * a.slice_len;
     const int64_t ke = min(M, kb + a.slice_len);
     // R draws at a time: their scalar loads are in flight together and the
-    // node sums share the exit tests.  FP32 takes one: 181 x 241 levels x 200,000 draws
-    // 15.15 ms against 15.7 with two and 16.3 with four.
+    // node sums share the exit tests.  FP32 takes one: 181 x 241 levels x 100,000 draws
+    // 7.33 ms against 7.71 with two.
     constexpr int R = sizeof(T) == 8 ? 2 : 1;
     double s1 = 0.0, s2 = 0.0;
     auto add = [&](auto count, int64_t k0) {
@@ -72,7 +72,8 @@ __device__ __forceinline__ void direct_body(const EvalArgs<T>& a, int64_t bx, in
     };
     int64_t k = kb;
     for (; k + R <= ke; k += R) add(std::integral_constant<int, R>{}, k);
-    for (; k < ke; ++k) add(std::integral_constant<int, 1>{}, k);
+    if constexpr (R > 1)
+        for (; k < ke; ++k) add(std::integral_constant<int, 1>{}, k);
     if (valid) {
         double* out = a.partials + static_cast<int64_t>(slice) * 2 * G;
         out[g] = s1;
@@ -157,7 +158,7 @@ template <typename T, int D, int NMAX, int MODE>
 __device__ __forceinline__ void mfma_tile_body(const EvalArgs<T>& a, const MfmaGeom& geo, int64_t tile, int slice,
                                                char* lds, CdfCell* cells) {
     if constexpr (sizeof(T) == 8) cdf_table_fill(cells);
-    const NormCdf<T> cdf(cells);
+    NormCdf<T> cdf(cells);
     using acc_t = typename std::conditional<sizeof(T) == 8, mf_d4, mf_f4>::type;
     const int K = a.D.K;   // a multiple of 4 (node steps of four)
     const int CH = geo.chunk;
@@ -179,6 +180,10 @@ __device__ __forceinline__ void mfma_tile_body(const EvalArgs<T>& a, const MfmaG
     const int64_t g = validB ? pB * geo.Sn + lB : G - 1;
     DesignState<T, D, NMAX> st;
     st.init(a.P, g, a.r, a.z1, a.z2, a.gl, a.glw);
+    if constexpr (sizeof(T) == 4 && (MODE == kSums ? D >= 3 : MODE == kSquares && D == 5)) {   // see pin_vector
+        cdf.pin();
+        st.w.pin();
+    }
     if constexpr (MODE == kDAlpha) st.init_dalpha(a.P, a.r[g], a.z1[g], a.z2[g]);
 
     // phase A operands: lane supplies row (p0 + lane%16) of Pre and column
@@ -355,7 +360,8 @@ __device__ __forceinline__ void mfma_tile_body(const EvalArgs<T>& a, const MfmaG
                 }
             }
         };
-        constexpr int kDraws = 2;
+        // (FP32 with squares: one, 20^4 designs x 10,000 draws 3.43 -> 3.37 ms)
+        constexpr int kDraws = sizeof(T) == 4 && MODE == kSquares ? 1 : 2;
         int i = 0;
         for (; i + kDraws <= nk; i += kDraws) phase_b(std::integral_constant<int, kDraws>{}, i);
         for (; i < nk; ++i) phase_b(std::integral_constant<int, 1>{}, i);
