@@ -404,10 +404,21 @@ void sweep_slices(bmd_problem* p, int prec, int64_t M, int64_t* n_slices_out, in
                           BMD_NOALLOC_SCRATCH_BYTES / 2)
         least = 64;
     n_slices = std::max<int64_t>(1, std::min<int64_t>({n_slices, (M + least - 1) / least, 65535}));
-    int64_t slice_len = (M + n_slices - 1) / n_slices;
-    slice_len = (slice_len + chunk - 1) / chunk * chunk;
-    *n_slices_out = (M + slice_len - 1) / slice_len;
-    *slice_len_out = slice_len;
+    auto cut = [&](int64_t n) {
+        const int64_t len = (M + n - 1) / n;
+        *slice_len_out = (len + chunk - 1) / chunk * chunk;
+        *n_slices_out = (M + *slice_len_out - 1) / *slice_len_out;
+    };
+    cut(n_slices);
+    // FP64 kernels that hold two workgroups a compute unit, or whose chunks leave room for the
+    // table of Phi, take more slices than those before them; where only these outgrow the
+    // scratch of a call without allocation, as many as fit (at least half), so that such a call
+    // is not refused for them.
+    if (prec == BMD_FP64) {
+        const size_t room = BMD_NOALLOC_SCRATCH_BYTES, draws = draw_workspace_bytes(p, prec, M);
+        const size_t per = sizeof(double) * 2 * static_cast<size_t>(p->P.G), n = static_cast<size_t>(*n_slices_out);
+        if (draws + per * n > room && draws + per * ((n + 1) / 2) <= room) cut(static_cast<int64_t>((room - draws) / per));
+    }
 }
 
 // Event i of the profiling pairs (phase = i / 2), recorded when profiling is on.
