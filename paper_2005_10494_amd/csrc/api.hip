@@ -1130,6 +1130,14 @@ bool plan_phases(bmd_problem* const* ps, std::vector<BatchPlan>& pl, int prec, i
                 ph.lds = std::max(ph.lds, batch_phase_lds(ps[i], prec, ph.set.chunk));
             }
         if (ph.lds > 64 * 1024) return false;
+        // settings tuned on problems of fewer nodes: with the kernel's own LDS (the FP64 table of
+        // Phi) a smaller chunk stays within 64 KB
+        const int step = prec == BMD_FP64 ? 4 : 8;
+        while (ph.set.chunk > step && ph.lds + batch_static_lds(prec) > 64 * 1024) {
+            ph.set.chunk -= step;
+            ph.lds = 0;
+            for (int i : ph.members) ph.lds = std::max(ph.lds, batch_phase_lds(ps[i], prec, ph.set.chunk));
+        }
         const int bpc = batch_phase_blocks_per_cu(ps[ph.rep], prec, ph.lds, ph.set.variant);
         ph.grid = n_cu * bpc;
         // Slices: about `rounds` items per resident workgroup over the phase.
