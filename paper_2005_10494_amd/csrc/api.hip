@@ -1221,6 +1221,7 @@ bmd_status run_batch_group(bmd_problem* const* ps, std::vector<BatchPlan> pl, in
     for (const Phase& ph : phases)
         for (int i : ph.members) chunk_of[i] = ph.set.chunk;
     int64_t draw_tiles_total = 0, designs_total = 0;
+    size_t draw_lds_most = 0;
     for (int i = 0; i < n; ++i) {
         bmd_problem* p = ps[i];
         double* part = reinterpret_cast<double*>(base + o_part[i]);
@@ -1229,6 +1230,7 @@ bmd_status run_batch_group(bmd_problem* const* ps, std::vector<BatchPlan> pl, in
         fill_draw_job(prec, host.data() + o_job + job_b * i, p, base + o_draw[i], pl[i].M, draw_tiles_total);
         fin[i] = BatchFinal{designs_total, pl[i].G, pl[i].M, static_cast<int>(pl[i].n_slices), part, d_means[i]};
         draw_tiles_total += draw_tiles(p, prec, pl[i].M);
+        draw_lds_most = std::max(draw_lds_most, draw_tile_lds(p, prec));
         designs_total += pl[i].G;
     }
     std::memcpy(host.data() + o_fin, fin.data(), sizeof(BatchFinal) * n);
@@ -1246,7 +1248,7 @@ bmd_status run_batch_group(bmd_problem* const* ps, std::vector<BatchPlan> pl, in
     auto launches = [&](std::vector<hipEvent_t>* ev) -> hipError_t {
         hipError_t le =
             launch_batch_reset(d_left, d_tdone, d_items_per, first, n, restart_clock ? d_tstart : nullptr, cs);
-        if (le == hipSuccess) le = launch_draws_batch(prec, base + o_job, n, draw_tiles_total, cs);
+        if (le == hipSuccess) le = launch_draws_batch(prec, base + o_job, n, draw_tiles_total, draw_lds_most, cs);
         size_t k = 0;
         for (size_t f = 0; f < phases.size() && le == hipSuccess; ++f) {
             // records are indexed within the group; left / t_done by batch index

@@ -267,9 +267,11 @@ hipError_t launch_grad_draws(const bmd_problem* p, int prec, uint64_t k0, int64_
 // one sweep launch per (precision, d, kernel kind), one workgroup per item.
 DrawArrays<double> draws_fp64_at(const bmd_problem* p, int64_t M, void* ws);
 DrawArrays<float> draws_fp32_at(const bmd_problem* p, int64_t M, void* ws);
-// tiles: draw tiles of all jobs (draw_tiles of each).
+// tiles: draw tiles of all jobs (draw_tiles of each); lds: the most of theirs
+// (draw_tile_lds).
 int64_t draw_tiles(const bmd_problem* p, int prec, int64_t M);
-hipError_t launch_draws_batch(int prec, const void* jobs, int n_jobs, int64_t tiles, hipStream_t s);
+size_t draw_tile_lds(const bmd_problem* p, int prec);
+hipError_t launch_draws_batch(int prec, const void* jobs, int n_jobs, int64_t tiles, size_t lds, hipStream_t s);
 // chunk: draws per LDS chunk of the matrix-core items (0 = the one-problem
 // sweep's); variant: launch-bound variant (batch_variants of them, see
 // batch_variant_waves: waves per SIMD the bound keeps, 0 = none).

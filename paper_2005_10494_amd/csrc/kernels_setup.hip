@@ -721,6 +721,8 @@ int64_t draw_tiles(const bmd_problem* p, int prec, int64_t M) {
     return (M + n - 1) / n;
 }
 
+size_t draw_tile_lds(const bmd_problem* p, int prec) { return draw_lds(p->P.d, p->tab[prec].K); }
+
 hipError_t launch_draws(const bmd_problem* p, int prec, uint64_t k0, int64_t M, void* ws, hipStream_t s) {
     if (prec == BMD_FP64) launch_draws_typed<double, kNodeMajor>(p, prec, k0, M, ws, s);
     else launch_draws_typed<float, kNodeMajor>(p, prec, k0, M, ws, s);
@@ -751,8 +753,7 @@ void fill_draw_job(int prec, void* dst, const bmd_problem* p, void* draws_ws, in
     }
 }
 
-hipError_t launch_draws_batch(int prec, const void* jobs, int n_jobs, int64_t tiles, hipStream_t s) {
-    const size_t lds = 40 * 1024;   // the most a tile takes
+hipError_t launch_draws_batch(int prec, const void* jobs, int n_jobs, int64_t tiles, size_t lds, hipStream_t s) {
     for (int64_t t0 = 0; t0 < tiles; t0 += kDrawGrid) {
         const dim3 grid(static_cast<unsigned>(std::min(tiles - t0, kDrawGrid)));
         if (prec == BMD_FP64)
