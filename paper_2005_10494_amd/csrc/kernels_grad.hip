@@ -113,11 +113,11 @@ __global__ __launch_bounds__(256) void k_grad_rule(int64_t b0, int64_t B, int sh
 // x_m - c_j)/sqrt(1 - rho_b), weights folded into j = 0.  (One thread per
 // point walked 128 nodes of up to six CDFs seven times over and the node
 // tables in turn: 1.7 ms however few the points; a wavefront each takes 50 us
-// for 8, 104 for 2,048.)  L = 64 keeps the latency of few points low; beyond
-// kGradWidePoints points, where throughput counts, 16 lanes waste less on the
-// values that all of them form alike (9,000 points, five biomarkers: 305 -> 267 us
-// a call of 100 draws).
-constexpr int64_t kGradWidePoints = 2048;
+// for 8, 104 for 2,048.)  L = 64 keeps the latency of few points low as long as
+// its workgroups of four points have a compute unit each; beyond that 16 lanes waste
+// less on the values that all of them form alike.  A call of 100 draws, 64 / 16 lanes,
+// FP64, one and five biomarkers: 1,024 points 94 / 100 and 148 / 171 us, 1,536 points
+// 109 / 100 and 172 / 167, 4,096 points 157 / 104 and 275 / 218.
 template <typename T, int L>
 __global__ __launch_bounds__(256) void k_grad_points(DevProblem P, const double* __restrict__ q_in, int64_t b0, int64_t B,
                                                      const double* __restrict__ ghp, int Kp,
@@ -583,7 +583,7 @@ template <typename T>
 hipError_t run_grad(const bmd_problem* p, int prec, const double* d_q, int64_t B, int64_t M, char* ws, const GradPlan& g,
                     bool draws_ready, double* info, double* part, T* rec, T* AD, hipStream_t s) {
     const int d = p->P.d, K = p->tab[prec].K;
-    const int per = B > kGradWidePoints ? 16 : 4;   // points per workgroup of 256: 16 or 64 lanes each
+    const int per = B > 4 * static_cast<int64_t>(p->n_cu) ? 16 : 4;   // points per workgroup of 256: 16 or 64 lanes each
     for (int64_t b0 = 0; b0 < B; b0 += per * kGradGrid) {
         const dim3 grid(static_cast<unsigned>(std::min((B - b0 + per - 1) / per, kGradGrid)));
         if (per == 16)
