@@ -135,6 +135,11 @@ __device__ __forceinline__ double exp2_fast(double t) {
     return __builtin_amdgcn_ldexp(p, static_cast<int>(n));
 }
 
+// 2^t for any t <= 0, -infinity included (NaN stays NaN): where t is a product, the
+// compiler contracts it into exp2_fast's t - n, whose result then carries t's own
+// rounding, past |t| = 1e44 enough to overflow the polynomial.
+__device__ __forceinline__ double exp2_low(double t) { return exp2_fast(t < -2000.0 ? -2000.0 : t); }
+
 // Mills' ratio M(y) = (1 - Phi(y))/phi(y), y >= 0, by the fit of mills_fit.hpp (4e-16
 // relative); the reciprocal by two Newton steps.
 __device__ __forceinline__ double mills(double y) {

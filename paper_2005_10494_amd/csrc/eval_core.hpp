@@ -124,7 +124,7 @@ struct DesignState {
 // +infinity (zinf bit 1) leaves phi(h) alone, as the one-test derivative of
 // Appendix A.3.
 __device__ __forceinline__ float gauss_factor(float x) { return exp(-0.5f * x * x); }
-__device__ __forceinline__ double gauss_factor(double x) { return exp2_fast(x * x * -0.72134752044448170368); }
+__device__ __forceinline__ double gauss_factor(double x) { return exp2_low(x * x * -0.72134752044448170368); }
 
 template <typename T, int D, int NMAX>
 __device__ __forceinline__ T dalpha_term(const DevProblem& P, const DesignState<T, D, NMAX>& s, T h, T kq,
@@ -134,7 +134,7 @@ __device__ __forceinline__ T dalpha_term(const DevProblem& P, const DesignState<
     T ph = gauss_factor(h), pk = gauss_factor(kq);
     if constexpr (sizeof(T) == 8) {
         // phi(h) phi(u) = phi(k) phi(v), here without one of its 1/sqrt(2 pi) as well
-        const T joint = 0.39894228040143267794 * exp2_fast(fma(h, h, u * u) * -0.72134752044448170368);
+        const T joint = 0.39894228040143267794 * exp2_low(fma(h, h, u * u) * -0.72134752044448170368);
         ph = density_cdf(ph, joint, u);
         pk = density_cdf(pk, joint, v);
     } else {

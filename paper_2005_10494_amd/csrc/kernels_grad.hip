@@ -243,11 +243,11 @@ __device__ __forceinline__ double lgst(double x) { return 1.0 / (1.0 + exp2_fast
 __device__ __forceinline__ float lgst(float x) {
     return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634074f * x));
 }
-// e^x; FP32 with the hardware exp2.
-__device__ __forceinline__ double expT(double x) { return exp2_fast(1.4426950408889634074 * x); }
+// e^x, x <= 0; FP32 with the hardware exp2.
+__device__ __forceinline__ double expT(double x) { return exp2_low(1.4426950408889634074 * x); }
 __device__ __forceinline__ float expT(float x) { return __builtin_amdgcn_exp2f(1.4426950408889634074f * x); }
 __device__ __forceinline__ double norm_pdf_fast(double x) {
-    return 0.39894228040143267794 * exp2_fast(x * x * -0.72134752044448170368);
+    return 0.39894228040143267794 * exp2_low(x * x * -0.72134752044448170368);
 }
 __device__ __forceinline__ float norm_pdf_fast(float x) { return norm_pdf(x); }
 
@@ -327,6 +327,7 @@ __global__ __launch_bounds__(kGradThreads, sizeof(T) == 8 ? (D == 6 ? 2 : 3) : 1
     const bool logistic = P.width > 0.0;
     const double iw64 = logistic ? 1.0 / P.width : 0.0;
     const T iw = static_cast<T>(iw64);
+    const double sw64 = fmin(iw64, 1e30);   // as sharp, and finite through exp2_fast (see exp2_low)
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int dw = kGradThreads / 64 / a.pw;
@@ -352,7 +353,7 @@ __global__ __launch_bounds__(kGradThreads, sizeof(T) == 8 ? (D == 6 ? 2 : 3) : 1
 #pragma unroll
             for (int p = 0; p < PP; ++p) {
                 const double dq = info[b[p] * kInfoFields + 1 + j] - tau;
-                s[p][j] = logistic ? lgst(static_cast<T>(dq * iw64)) : dq > 0.0 ? T(1) : T(0);
+                s[p][j] = logistic ? lgst(static_cast<T>(dq * sw64)) : dq > 0.0 ? T(1) : T(0);
                 U[p][j] = T(0);
                 V[p][j] = kSplit || !logistic ? T(0) : s[p][j] * (T(1) - s[p][j]) * iw;
             }
