@@ -19,16 +19,19 @@ struct GradPlan {
 // groups: rows of points; step: draws a workgroup has in flight (slices are whole
 // steps); resident: workgroups the chip holds at once; rounds of them the call
 // is cut into; per_draw: bytes of a draw; budget: bytes of a pass.
+// window, most (0: none): slices of at most `window` draws, as far as `most` slices
+// allow.
 // Many groups fill the chip by themselves and would take few, long slices, so a
 // slice is also bounded by what one pass may hold: by kGradDrawBudget whatever
 // `budget` is, so that the slices, and with them the order of the sums, do not
 // depend on it (a budget below one slice holds one slice).
 inline GradPlan grad_plan_of(int64_t groups, int64_t step, int64_t resident, int64_t rounds, int64_t M, double per_draw,
-                             size_t budget) {
+                             size_t budget, int64_t window = 0, int64_t most = 0) {
     const int64_t fits = static_cast<int64_t>(static_cast<double>(kGradDrawBudget) / per_draw);
     const int64_t longest = std::max<int64_t>(1, std::min(fits, kGradPassDraws) / step) * step;
     int64_t n = (rounds * resident + groups - 1) / groups;
     n = std::max<int64_t>(1, std::min<int64_t>({n, (M + step - 1) / step, 65528}));
+    if (window > 0) n = std::max(n, std::min(most, (M + window - 1) / window));
     n = std::max(n, (M + longest - 1) / longest);
     if (n >= 8) n = (n + 7) / 8 * 8;   // the XCDs take slices in turn
     int64_t len = (M + n - 1) / n;

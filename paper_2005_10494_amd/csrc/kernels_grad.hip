@@ -294,9 +294,10 @@ struct GradArgs {
 // 200,000 draws FP64 1,056 -> 260 us.
 // FP64 is held to 168 registers, three wavefronts per SIMD (a refinement call 2.00 ->
 // 1.90 ms against two); six biomarkers, which would spill 276 bytes a thread,
-// take two (256 points x 50,000 draws: 2.50 -> 1.62 ms).
+// take two (256 points x 50,000 draws: 2.50 -> 1.62 ms).  FP32 with six takes three in
+// place of two, 143 registers (1,024 points x 1e6 draws 60.8 -> 48.3 ms; four spill, 52.3).
 template <typename T, int D, int PP>
-__global__ __launch_bounds__(kGradThreads, sizeof(T) == 8 ? (D == 6 ? 2 : 3) : 1) void k_grad(GradArgs<T> a, const double* __restrict__ info,
+__global__ __launch_bounds__(kGradThreads, sizeof(T) == 8 ? (D == 6 ? 2 : 3) : D == 6 ? 3 : 1) void k_grad(GradArgs<T> a, const double* __restrict__ info,
                                                        const T* __restrict__ rec, const T* __restrict__ AD,
                                                        const T* __restrict__ glw, DrawArrays<T> Dr) {
     constexpr int NMAX = kGradNmax<T>;
@@ -558,6 +559,15 @@ int64_t grad_groups(int64_t B) {
     return (B + per - 1) / per;
 }
 
+// Node-table bytes of a slice, at most: the rows of points that read a slice drift
+// apart along it, and past the XCD's 4 MB L2 each fetches it for itself.  4,096
+// points x 1e6 draws, five biomarkers, FP32 (slices of 30 MB by the rounds alone): 144.7 ms
+// without a bound, 106.6 / 105.9 / 105.9 / 104.9 / 103.7 at 16 / 8 / 4 / 2 / 1 MB; FP64, 1,024 points
+// x 200,000 draws, six: 33.6 at 16 MB, 24.4 at 2, 25.5 at 1.
+constexpr int64_t kGradWindow = int64_t(2) << 20;
+// Partial sums that more slices than the rounds need may take.
+constexpr size_t kGradPartials = size_t(1) << 30;
+
 // Points go in launches of at most kGradGrid groups or wavefronts (the grid's
 // thread count stays below 2^32).
 constexpr int64_t kGradGrid = 1 << 22;
@@ -652,8 +662,11 @@ GradPlan grad_plan(const bmd_problem* p, int prec, int64_t B, int64_t M) {
         if (v > 0) budget = static_cast<size_t>(v);
     }
     const double per = static_cast<double>(draw_workspace_bytes(p, prec, 1 << 20)) / (1 << 20);
+    const int d = p->P.d;
+    const int64_t row = static_cast<int64_t>(prec == BMD_FP64 ? 8 : 4) * d * p->tab[prec].K;
     return grad_plan_of(grad_groups(B), kGradThreads / grad_point_waves(B), static_cast<int64_t>(p->n_cu) * nb,
-                        kSweepRounds, M, per, budget);
+                        kSweepRounds, M, per, budget, d >= 2 ? kGradWindow / row : 0,
+                        static_cast<int64_t>(kGradPartials / (sizeof(double) * (d + 3) * B)));
 }
 
 hipError_t launch_grad(const bmd_problem* p, int prec, const double* d_q, int64_t B, int64_t M, void* ws,

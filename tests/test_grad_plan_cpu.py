@@ -86,3 +86,24 @@ def test_passes_stay_within_their_bounds(tmp_path):
                     }
     std::printf("%ld %ld %ld\\n", bad, kept, cut);""")
     assert bad == 0 and kept > 0 and cut > 0
+
+
+def test_slices_within_the_window(tmp_path):
+    """Slices no longer than the window (in whole steps) unless the partial sums' bound
+    is reached; calls within it anyway keep their slices (counted: both)."""
+    bad, kept, cut, bound = _run(tmp_path, """
+    long bad = 0, kept = 0, cut = 0, bound = 0;
+    for (int64_t groups : {1L, 128L, 512L, 8192L, 1L << 20})
+        for (int64_t window : {650L, 4369L, 65536L})
+            for (int64_t most : {0L, 3L, 40L, 100000L})
+                for (int64_t M = 1; M < 200000000; M = M * 3 + 1) {
+                    const GradPlan a = grad_plan_of(groups, 64, 768, 8, M, 700.0, kGradDrawBudget);
+                    const GradPlan b = grad_plan_of(groups, 64, 768, 8, M, 700.0, kGradDrawBudget, window, most);
+                    const int64_t w = (window + 63) / 64 * 64;
+                    bad += b.n_slices * b.slice_len < M || (b.n_slices - 1) * b.slice_len >= M || b.slice_len > a.slice_len;
+                    if (a.slice_len <= window) { bad += b.slice_len != a.slice_len; ++kept; }
+                    else if (most >= (M + window - 1) / window) { bad += b.slice_len > w; ++cut; }
+                    else { bad += b.n_slices > std::max(a.n_slices, (most + 7) / 8 * 8); ++bound; }
+                }
+    std::printf("%ld %ld %ld %ld\\n", bad, kept, cut, bound);""")
+    assert bad == 0 and kept > 0 and cut > 0 and bound > 0
