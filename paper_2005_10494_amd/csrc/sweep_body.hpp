@@ -301,8 +301,9 @@ __device__ __forceinline__ void mfma_tile_body(const EvalArgs<T>& a, const MfmaG
         if (k0 + CH < ke) stage(k0 + CH, static_cast<int>(min<int64_t>(CH, ke - k0 - CH)), sq0 + (buf ^ 1) * CH);
         // phase B: bivariate normal part for this thread's design, R draws at a
         // time (their node sums share the exit tests and interleave); with
-        // kDAlpha also the summands' derivatives in alpha_1 (dalpha_term)
-        auto phase_b = [&](auto count, int i0) {
+        // kDAlpha also the summands' derivatives in alpha_1 (dalpha_term).
+        // one: where a single draw's value goes in place of the sums.
+        auto phase_b = [&](auto count, int i0, T* one = nullptr) {
             constexpr int R = decltype(count)::value;
             T h[R], kk[R], v[R];
 #pragma unroll
@@ -327,16 +328,17 @@ __device__ __forceinline__ void mfma_tile_body(const EvalArgs<T>& a, const MfmaG
                 for (int r = 0; r < R; ++r)
                     v[r] = a.P.zinf == 1 ? T(1) - cdf.scaled(kk[r]) : a.P.zinf == 2 ? T(1) - cdf.scaled(h[r]) : T(0);
             }
-            if constexpr (sizeof(T) == 4 && MODE == kSums && R % 2 == 0) {
-#pragma unroll
-                for (int r = 0; r < R; r += 2) s1 += static_cast<double>(v[r] + v[r + 1]);   // pairs of draws in FP32
-            } else {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const double vd = static_cast<double>(v[r]);
-                    s1 += vd;
-                    if constexpr (MODE == kSquares) s2 = fma(vd, vd, s2);
+            if constexpr (R == 1) {
+                if (one) {
+                    *one = v[0];
+                    return;
                 }
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const double vd = static_cast<double>(v[r]);
+                s1 += vd;
+                if constexpr (MODE == kSquares) s2 = fma(vd, vd, s2);
             }
             if constexpr (MODE == kDAlpha) {
 #pragma unroll
@@ -360,9 +362,20 @@ __device__ __forceinline__ void mfma_tile_body(const EvalArgs<T>& a, const MfmaG
                 }
             }
         };
-        // (FP32 with squares: one, 20^4 designs x 10,000 draws 3.43 -> 3.37 ms)
-        constexpr int kDraws = sizeof(T) == 4 && MODE == kSquares ? 1 : 2;
+        // FP32 values go one at a time (their sums add pairs of draws in FP32 first): two
+        // at once cost small problems more than they gave large ones.  With two / one:
+        // batch of 256 at half scale 680 / 666 ms, 64^3 x 100,000 draws 47.9 / 47.2,
+        // 24^4 x 50,000 33.3 / 32.6, 20^4 x 10,000 with squares 3.43 / 3.36.
+        constexpr int kDraws = sizeof(T) == 4 && MODE != kDAlpha ? 1 : 2;
         int i = 0;
+        if constexpr (sizeof(T) == 4 && MODE == kSums) {
+            for (; i + 1 < nk; i += 2) {
+                T v0, v1;
+                phase_b(std::integral_constant<int, 1>{}, i, &v0);
+                phase_b(std::integral_constant<int, 1>{}, i + 1, &v1);
+                s1 += static_cast<double>(v0 + v1);
+            }
+        }
         for (; i + kDraws <= nk; i += kDraws) phase_b(std::integral_constant<int, kDraws>{}, i);
         for (; i < nk; ++i) phase_b(std::integral_constant<int, 1>{}, i);
     }
