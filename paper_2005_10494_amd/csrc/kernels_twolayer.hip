@@ -492,9 +492,9 @@ void launch_bits(const TwoLayerArgs& a, const int32_t* order, int64_t shared, in
 // every compute unit busy four times over.  The tables cost a workgroup about
 // 20 us; with fewer than kBitMinOuter (outer draw, design) pairs to use them on
 // the comparing kernel runs (also beyond the grid's second dimension).
-// Measured, comparing / bit sets: at 4,096 pairs 1.6 (1,600 designs, 256 outer
-// draws, 16,384 inner) to 6.0 (512 designs, 4,096 outer); at 512 to 1,024 pairs
-// 0.64 (201 cutoffs, FP64) to 2.0.
+// Measured, comparing / bit sets, over 45 to 2,401 designs of two to four populations,
+// 64 to 8,192 outer and 1,024 to 16,384 inner draws, both precisions: at 4,096 pairs 1.14 to
+// 5.2 (median 2.6), at 2,048 0.77 to 3.2, at 1,024 0.52 to 2.0, at 512 0.30 to 1.4.
 constexpr int64_t kBitMinOuter = 4096;
 
 template <typename T>

@@ -146,8 +146,9 @@ __device__ __forceinline__ float tvn(float h1, float h2, float h3, const TvnCons
 }
 
 // Phi_3(h1, h2, h3) over c.np panels (wave-uniform).  Every lane runs the
-// same node count: an empty range (U <= -L) becomes a zero panel width, and
-// NaN inputs give NaN.
+// same node count: an empty range (U <= -L) becomes a zero panel width.  A NaN
+// does not get through the table of Phi; the sweeps write NaN for designs
+// without a level themselves.
 template <bool UNI>
 __device__ __forceinline__ double tvn(double h1, double h2, double h3, const TvnConst<double, UNI>& c,
                                       const NormCdf<double>& cdf) {
